@@ -15,6 +15,26 @@ namespace smat {
 // thread).
 constexpr uint32_t max_grid_blocks(int threads) { return 0xFFFFFFFFu / (uint32_t)threads; }
 
+// ---------------------------------------------------------------- resident blocks
+// HBM streams fastest when the loads in flight on a compute unit hold about 50 KB: with less the
+// memory system idles between requests, with more the waves of many tiles compete for open DRAM rows.
+// A CU holds up to 32 one-wave blocks, so a kernel whose waves load much each passes that mark; it
+// reserves LDS it never touches, which bounds the blocks that are resident together (LDS is granted
+// in 1,280-byte granules out of 160 KB).  Arrays of a few times the 256 MB Infinity Cache and less are
+// partly served from there, where more requests only help: the fused optimizer step of 9.6e6
+// parameters (251 MB) took 53.4 us capped and 52.4 us uncapped, of 31.5e6 (820 MB) 147.1 and 148.8 us.
+// So a launch is capped from 512 MB up.
+constexpr uint32_t kLdsBytes = 160u * 1024u, kLdsGranule = 1280u, kBytesInFlight = 50u * 1024u;
+constexpr uint64_t kCapFromBytes = 512ull << 20;
+constexpr uint32_t lds_for_blocks(uint32_t blocks) {
+  return blocks >= 32u ? 0u : kLdsBytes / blocks / kLdsGranule * kLdsGranule;
+}
+// LDS to reserve per block of a kernel whose one-wave blocks each keep wave_bytes of loads in flight
+// and whose launch streams `bytes` in all.
+constexpr uint32_t lds_for_loads(uint32_t wave_bytes, uint64_t bytes) {
+  return bytes < kCapFromBytes ? 0u : lds_for_blocks(kBytesInFlight / wave_bytes);
+}
+
 // fn(first, count) over consecutive pieces [first, first + count) of `total` units, count <= per,
 // stopping at the first launch error.
 template <typename F>

@@ -364,23 +364,35 @@ __global__ __launch_bounds__(kSumBlock) void k_sqnorm_finalize(const double* __r
 // ranges of a list's chunk table).
 static inline uint32_t blocks_for(int64_t n, int64_t per_block) { return (uint32_t)((n + per_block - 1) / per_block); }
 
+// A wave of the fused optimizer step loads theta, both moments, g~ and, when accumulating, grad_theta:
+// 3.5 KB (bf16 g~) to 5 KB (fp32 g~, accumulating).  Uncapped, 32 such waves keep 112-160 KB in flight
+// per CU, twice what streams best, and the rate then depends on where the arrays happen to lie: on
+// 1.54e9 parameters (40.1 GB) 6.24-6.69 ms over two boxes uncapped, 6.07-6.20 ms with the 14 blocks this
+// gives; on 124M parameters accumulating (3.7 GB) 0.585 against 0.55 ms with 11.  16 or 12 blocks are
+// within 1.5 % of 14, 9 lose 5 %.
+static inline uint32_t adamw_lds(int grad_dtype, bool accumulate, uint64_t elems) {
+  const size_t loaded = storage_bytes(grad_dtype) + (accumulate ? 4 : 3) * sizeof(float);  // an element; 12 B stored
+  return lds_for_loads((uint32_t)(tile_elems(kAdamQuads) * loaded), elems * (loaded + 12));
+}
+
 hipError_t launch_adamw_one(const TensorRec& rec, const AdamRec& st, const ParamRec& prm, const AdamConsts& A,
                             int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
                             const float* dev_scale, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
+  const uint32_t lds = adamw_lds(grad_dtype, accumulate, (uint64_t)rec.n);
   constexpr int64_t tile = tile_elems(kAdamQuads);
   return for_pieces((uint64_t)rec.n, (uint64_t)max_grid_blocks(kBlock) * tile, [&](uint64_t off, uint64_t len) {
     const TensorRec r = rec_piece(rec, off, len, 0, 0, grad_dtype);
     const AdamRec m{step_ptr(st.exp_avg, off, 4), step_ptr(st.exp_avg_sq, off, 4)};
     const dim3 grid(blocks_for((int64_t)len, tile)), block(kBlock);
     if (grad_dtype == 1 && accumulate)
-      k_adamw_one<Bf16, true><<<grid, block, 0, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
+      k_adamw_one<Bf16, true><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
     else if (grad_dtype == 1)
-      k_adamw_one<Bf16, false><<<grid, block, 0, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
+      k_adamw_one<Bf16, false><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
     else if (accumulate)
-      k_adamw_one<float, true><<<grid, block, 0, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
+      k_adamw_one<float, true><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
     else
-      k_adamw_one<float, false><<<grid, block, 0, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
+      k_adamw_one<float, false><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
   });
 }
 
@@ -388,18 +400,19 @@ hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, cons
                               uint32_t nchunks, const AdamConsts& A, int grad_dtype, bool accumulate, float lambda,
                               uint64_t seed, uint32_t step, const float* dev_scale, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
+  const uint32_t lds = adamw_lds(grad_dtype, accumulate, (uint64_t)nchunks * kChunk);
   constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
     if (grad_dtype == 1 && accumulate)
-      k_adamw_multi<Bf16, true><<<grid, block, 0, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
+      k_adamw_multi<Bf16, true><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
     else if (grad_dtype == 1)
-      k_adamw_multi<Bf16, false><<<grid, block, 0, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
+      k_adamw_multi<Bf16, false><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
     else if (accumulate)
-      k_adamw_multi<float, true><<<grid, block, 0, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
+      k_adamw_multi<float, true><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
     else
-      k_adamw_multi<float, false><<<grid, block, 0, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
+      k_adamw_multi<float, false><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
   });
 }
 
@@ -467,21 +480,22 @@ hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, 
   k_adam_consts<<<dim3(1), dim3(64), 0, stream>>>(adam_state, h, consts);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  const uint32_t lds = adamw_lds(grad_dtype, accumulate, (uint64_t)nchunks * kChunk);
   constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
     if (grad_dtype == 1 && accumulate)
-      k_adamw_multi_dev<Bf16, true><<<grid, block, 0, stream>>>(recs, states, prms, scales, ch, consts, state, lambda,
+      k_adamw_multi_dev<Bf16, true><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state, lambda,
                                                                 dev_scale);
     else if (grad_dtype == 1)
-      k_adamw_multi_dev<Bf16, false><<<grid, block, 0, stream>>>(recs, states, prms, scales, ch, consts, state,
+      k_adamw_multi_dev<Bf16, false><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state,
                                                                  lambda, dev_scale);
     else if (accumulate)
-      k_adamw_multi_dev<float, true><<<grid, block, 0, stream>>>(recs, states, prms, scales, ch, consts, state,
+      k_adamw_multi_dev<float, true><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state,
                                                                  lambda, dev_scale);
     else
-      k_adamw_multi_dev<float, false><<<grid, block, 0, stream>>>(recs, states, prms, scales, ch, consts, state,
+      k_adamw_multi_dev<float, false><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state,
                                                                   lambda, dev_scale);
   });
 }
