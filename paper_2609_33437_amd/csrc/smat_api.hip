@@ -1293,11 +1293,13 @@ extern "C" smat_status smat_merge(const void* const* experts, int32_t n_experts,
   if (n < 0) return fail(SMAT_ERR_INVALID, "smat_merge: n < 0");
   if (!terms || !experts) return fail(SMAT_ERR_INVALID, "smat_merge: null terms or experts");
   MergeArgs A{};
+  bool plain = true;  // no expert draws a mask or is left out
   for (int32_t j = 0; j < n_experts; ++j) {
     char where[64];
     std::snprintf(where, sizeof(where), "smat_merge: expert %d", j);
     smat_status st = make_merge(terms[j], &A.r[j], where);
     if (st != SMAT_OK) return st;
+    plain = plain && A.r[j].flags == 0;
     A.x[j] = experts[j];
   }
   if (n == 0) return SMAT_OK;
@@ -1313,7 +1315,7 @@ extern "C" smat_status smat_merge(const void* const* experts, int32_t n_experts,
   rec.elem_offset = elem_offset;
   rec.tensor_id = tensor_id;
   rec.sflags = merge_flags(experts, n_experts, expert_dtype, theta0, theta0_dtype, out, out_dtype, elem_offset);
-  SMAT_HIP(smat::launch_merge_one(rec, A, n_experts, expert_dtype, theta0_dtype, out_dtype, stream));
+  SMAT_HIP(smat::launch_merge_one(rec, A, n_experts, expert_dtype, theta0_dtype, out_dtype, plain, stream));
   return SMAT_OK;
 }
 
@@ -1479,12 +1481,14 @@ extern "C" smat_status smat_merge_multi(smat_merge_plan* p, const smat_merge_ter
   if (!p->ws) return fail(SMAT_ERR_STATE, "smat_merge_multi: no workspace bound");
   if (smat_status st = refuse_capture(stream, "smat_merge_multi"); st != SMAT_OK) return st;
   std::vector<MergeRec> recs(cells);
+  bool plain = true;  // no expert draws a mask or is left out
   for (size_t c = 0; c < cells; ++c) {
     if (make_merge(terms[c], &recs[c], "") != SMAT_OK) {  // the message names the cell, formed only on failure
       char where[80];
       std::snprintf(where, sizeof(where), "smat_merge_multi: tensor %zu, expert %zu", c / p->nexp, c % p->nexp);
       return make_merge(terms[c], &recs[c], where);
     }
+    plain = plain && recs[c].flags == 0;
   }
   const int slot = p->slot;
   if (p->terms_pending[slot]) SMAT_HIP(hipEventSynchronize(p->ev_terms[slot]));  // slot still being read
@@ -1500,7 +1504,7 @@ extern "C" smat_status smat_merge_multi(smat_merge_plan* p, const smat_merge_ter
                                       reinterpret_cast<const void* const*>(p->ws + p->off_experts),
                                       reinterpret_cast<const MergeRec*>(p->ws + p->off_terms),
                                       reinterpret_cast<const uint2*>(p->ws + p->off_chunks), (uint32_t)p->chunks.size(),
-                                      p->nexp, p->e_dt, p->t0_dt, p->out_dt, stream));
+                                      p->nexp, p->e_dt, p->t0_dt, p->out_dt, plain, stream));
   return SMAT_OK;
 }
 

@@ -134,18 +134,18 @@ struct alignas(8) MergeRec {
 };
 static_assert(sizeof(MergeRec) == 104, "MergeRec layout");
 constexpr int kMaxExperts = 16;
-constexpr int kMergeQuads = 2;
 constexpr uint32_t kVecMerge = 16u;  // TensorRec::sflags: theta0, out and every expert quad-aligned, offset % 4 == 0
 // Arguments of the one-tensor merge, passed by value (no device tables).
 struct MergeArgs {
   const void* x[kMaxExperts];
   MergeRec r[kMaxExperts];
 };
+// `plain`: no term draws a mask or leaves its expert out.
 hipError_t launch_merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, int expert_dtype, int theta0_dtype,
-                            int out_dtype, hipStream_t stream);
+                            int out_dtype, bool plain, hipStream_t stream);
 hipError_t launch_merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
                               const uint2* chunks, uint32_t nchunks, int nexp, int expert_dtype, int theta0_dtype,
-                              int out_dtype, hipStream_t stream);
+                              int out_dtype, bool plain, hipStream_t stream);
 
 // Plain streaming copy of n16 16-byte vectors (the measured HBM reference).
 constexpr int kCopyVecs = 1;  // 16-byte vectors per thread of the reference copy

@@ -6,15 +6,17 @@
 // The accumulation acc = fma(t_j, theta_j, fma(-t_j, theta0, acc)) starting from theta0 is the
 // simulate's exact-endpoint lerp for one expert, so a one-expert merge reproduces the simulated
 // state without noise bit for bit.  A pure HBM stream (N + 2 arrays), built like the other
-// kernels: one-wave blocks over tiles of kMergeQuads quads per thread, loads issued before the
-// mask draws and at raised wave priority, the list form mapping blocks to (tensor, chunk) through
+// kernels: one-wave blocks over tiles of one or two quads per thread (merge_form), loads issued before
+// the mask draws and at raised wave priority, the list form mapping blocks to (tensor, chunk) through
 // the chunk table.
 #include "smat_launch.h"
 #include "smat_tile.h"
 
 namespace smat {
 
-template <typename TE, typename T0, typename TO, typename XAT, typename RAT>
+// Thread x owns quads x + u kBlock, u < Q, of the tile.  AHEAD: for terms without masks, the loads run
+// one expert ahead of the sums.
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD, typename XAT, typename RAT>
 __device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t e0, uint32_t len, uint32_t tensor_id,
                                            bool vec, int nexp, XAT expert_at, RAT rec_at) {
   auto one = [&](uint32_t i) {
@@ -34,10 +36,10 @@ __device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t
     QuadIO<TO>::store1(outp, i, acc);
   };
 
-  if (!vec || groups_wrap(e0, kMergeQuads * kBlock)) {
+  if (!vec || groups_wrap(e0, Q * kBlock)) {
     normal_priority();
 #pragma unroll
-    for (int u = 0; u < kMergeQuads; ++u) {
+    for (int u = 0; u < Q; ++u) {
       const uint32_t i0 = (u * kBlock + threadIdx.x) * 4u;
       for (uint32_t i = i0; i < len && i < i0 + 4u; ++i) one(i);
     }
@@ -45,66 +47,83 @@ __device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t
   }
   const uint32_t nq = len >> 2;
   if (nq > 0) {
-    float b[kMergeQuads][4], acc[kMergeQuads][4];
+    float b[Q][4], acc[Q][4];
     // the experts' masks of a group differ only in the key, so they share round 1's product
     const TileGroups G = tile_groups(e0);
-    uint64_t p0[kMergeQuads];
+    uint64_t p0[Q];
 #pragma unroll
-    for (int u = 0; u < kMergeQuads; ++u) p0[u] = philox_p0(G.lo + u * kBlock + threadIdx.x);
+    for (int u = 0; u < Q; ++u) p0[u] = philox_p0(G.lo + u * kBlock + threadIdx.x);
+    typename QuadIO<TE>::Raw rx[Q];
+    auto load = [&](const void* xp) {
+#pragma unroll
+      for (int u = 0; u < Q; ++u)
+        rx[u] = QuadIO<TE>::load_raw(xp, min((uint32_t)(u * kBlock + threadIdx.x), nq - 1u));
+    };
     {
-      typename QuadIO<T0>::Raw r0[kMergeQuads];
+      typename QuadIO<T0>::Raw r0[Q];
 #pragma unroll
-      for (int u = 0; u < kMergeQuads; ++u) {
+      for (int u = 0; u < Q; ++u) {
         const uint32_t q = u * kBlock + threadIdx.x;
         r0[u] = QuadIO<T0>::load_raw(t0p, min(q, nq - 1u));
       }
+      if (AHEAD) load(expert_at(0));
       normal_priority();
 #pragma unroll
-      for (int u = 0; u < kMergeQuads; ++u) {
+      for (int u = 0; u < Q; ++u) {
         QuadIO<T0>::unpack(r0[u], b[u]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[u][j] = b[u][j];
       }
     }
-    for (int x = 0; x < nexp; ++x) {
-      const MergeRec R = rec_at(x);
-      const void* xp = expert_at(x);
-      // the expert's pointer and its term's fields in one round of scalar loads, before any branch
-      asm volatile("" ::"s"(xp), "s"(R.t), "s"(R.flags), "s"(R.thr), "s"(R.step));
-      if (R.flags & kFlagDropAll) continue;
-      // each expert's loads go out at raised priority, ahead of other waves' draws (as in the simulate)
-      typename QuadIO<TE>::Raw rx[kMergeQuads];
-      raise_priority();
+    auto fold = [&](const typename QuadIO<TE>::Raw* r, const bool(*kept)[4], float t) {
 #pragma unroll
-      for (int u = 0; u < kMergeQuads; ++u) {
-        const uint32_t q = u * kBlock + threadIdx.x;
-        rx[u] = QuadIO<TE>::load_raw(xp, min(q, nq - 1u));
-      }
-      normal_priority();
-      bool kept[kMergeQuads][4];
-#pragma unroll
-      for (int u = 0; u < kMergeQuads; ++u) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) kept[u][j] = true;
-        if (R.flags & kFlagMask) {
-          const Words w = philox_tile_rk(p0[u], G.hi, tensor_id, (R.step << 2) | kStreamMask, R.rk0, R.rk1);
-          kept[u][0] = w.w0 < R.thr;
-          kept[u][1] = w.w1 < R.thr;
-          kept[u][2] = w.w2 < R.thr;
-          kept[u][3] = w.w3 < R.thr;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kMergeQuads; ++u) {
+      for (int u = 0; u < Q; ++u) {
         float v[4];
-        QuadIO<TE>::unpack(rx[u], v);
+        QuadIO<TE>::unpack(r[u], v);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (kept[u][j]) acc[u][j] = __builtin_fmaf(R.t, v[j], __builtin_fmaf(-R.t, b[u][j], acc[u][j]));
+          if (!kept || kept[u][j]) acc[u][j] = __builtin_fmaf(t, v[j], __builtin_fmaf(-t, b[u][j], acc[u][j]));
+      }
+    };
+    if (AHEAD) {
+      // no expert draws a mask or is left out: the next expert's loads are in flight during this one's sum
+      for (int x = 0; x < nexp; ++x) {
+        const float t = rec_at(x).t;
+        typename QuadIO<TE>::Raw now[Q];
+#pragma unroll
+        for (int u = 0; u < Q; ++u) now[u] = rx[u];
+        if (x + 1 < nexp) load(expert_at(x + 1));
+        fold(now, nullptr, t);
+      }
+    } else {
+      for (int x = 0; x < nexp; ++x) {
+        const MergeRec R = rec_at(x);
+        const void* xp = expert_at(x);
+        // the expert's pointer and its term's fields in one round of scalar loads, before any branch
+        asm volatile("" ::"s"(xp), "s"(R.t), "s"(R.flags), "s"(R.thr), "s"(R.step));
+        if (R.flags & kFlagDropAll) continue;
+        // each expert's loads go out at raised priority, ahead of other waves' draws (as in the simulate)
+        raise_priority();
+        load(xp);
+        normal_priority();
+        bool kept[Q][4];
+#pragma unroll
+        for (int u = 0; u < Q; ++u) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) kept[u][j] = true;
+          if (R.flags & kFlagMask) {
+            const Words w = philox_tile_rk(p0[u], G.hi, tensor_id, (R.step << 2) | kStreamMask, R.rk0, R.rk1);
+            kept[u][0] = w.w0 < R.thr;
+            kept[u][1] = w.w1 < R.thr;
+            kept[u][2] = w.w2 < R.thr;
+            kept[u][3] = w.w3 < R.thr;
+          }
+        }
+        fold(rx, kept, R.t);
       }
     }
 #pragma unroll
-    for (int u = 0; u < kMergeQuads; ++u) {
+    for (int u = 0; u < Q; ++u) {
       const uint32_t q = u * kBlock + threadIdx.x;
       if (q < nq) QuadIO<TO>::store(outp, q, acc[u]);
     }
@@ -114,31 +133,31 @@ __device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t
   }
 }
 
-template <typename TE, typename T0, typename TO>
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void k_merge_one(TensorRec R, MergeArgs A, int nexp) {
   raise_priority();
-  constexpr int64_t tile = tile_elems(kMergeQuads);
+  constexpr int64_t tile = tile_elems(Q);
   const int64_t begin = (int64_t)blockIdx.x * tile;
-  merge_tile<TE, T0, TO>(
+  merge_tile<TE, T0, TO, Q, AHEAD>(
       advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)), R.elem_offset + (uint64_t)begin,
       tile_len(R.n, begin, tile), R.tensor_id, (R.sflags & kVecMerge) != 0, nexp,
       [&](int j) { return advance<TE>(A.x[j], begin); }, [&](int j) { return A.r[j]; });
 }
 
-template <typename TE, typename T0, typename TO>
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void k_merge_multi(const TensorRec* __restrict__ recs,
                                                         const void* const* __restrict__ experts,
                                                         const MergeRec* __restrict__ terms,
                                                         const uint2* __restrict__ chunks, int nexp) {
   raise_priority();
-  constexpr int64_t tile = tile_elems(kMergeQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kMergeQuads);
+  constexpr int64_t tile = tile_elems(Q);
+  constexpr uint32_t tpc = tiles_per_chunk(Q);
   const uint2 ch = chunks[blockIdx.x / tpc];
   const TensorRec R = recs[ch.x];
   const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(blockIdx.x % tpc) * tile;
   if (begin >= R.n) return;  // unused tile of a tensor's last chunk
   const size_t row = (size_t)ch.x * (size_t)nexp;
-  merge_tile<TE, T0, TO>(
+  merge_tile<TE, T0, TO, Q, AHEAD>(
       advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)), R.elem_offset + (uint64_t)begin,
       tile_len(R.n, begin, tile), R.tensor_id, (R.sflags & kVecMerge) != 0, nexp,
       [&](int j) { return advance<TE>(experts[row + j], begin); }, [&](int j) { return terms[row + j]; });
@@ -147,9 +166,10 @@ __global__ __launch_bounds__(kBlock) void k_merge_multi(const TensorRec* __restr
 // ---------------------------------------------------------------- launchers
 // Jobs whose grid would pass max_grid_blocks run as several launches (element ranges of one tensor,
 // ranges of a list's chunk table).
-template <typename TE, typename T0, typename TO>
-static hipError_t merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, hipStream_t stream) {
-  constexpr int64_t tile = tile_elems(kMergeQuads);
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
+static hipError_t merge_one_as(const TensorRec& rec, const MergeArgs& args, int nexp, uint32_t lds,
+                               hipStream_t stream) {
+  constexpr int64_t tile = tile_elems(Q);
   constexpr int e_dt = std::is_same<TE, Bf16>::value ? 1 : 0, t0_dt = std::is_same<T0, Bf16>::value ? 1 : 0,
                 o_dt = std::is_same<TO, Bf16>::value ? 1 : 0;
   return for_pieces((uint64_t)rec.n, (uint64_t)max_grid_blocks(kBlock) * tile, [&](uint64_t off, uint64_t len) {
@@ -157,17 +177,63 @@ static hipError_t merge_one(const TensorRec& rec, const MergeArgs& args, int nex
     MergeArgs a = args;
     for (int j = 0; j < nexp; ++j) a.x[j] = step_ptr(args.x[j], off, storage_bytes(e_dt));
     const dim3 grid((uint32_t)((len + tile - 1) / tile)), block(kBlock);
-    k_merge_one<TE, T0, TO><<<grid, block, 0, stream>>>(r, a, nexp);
+    k_merge_one<TE, T0, TO, Q, AHEAD><<<grid, block, lds, stream>>>(r, a, nexp);
+  });
+}
+
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
+static hipError_t merge_multi_as(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
+                                 const uint2* chunks, uint32_t nchunks, int nexp, uint32_t lds, hipStream_t stream) {
+  constexpr uint32_t tpc = tiles_per_chunk(Q);
+  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
+    const dim3 grid((uint32_t)count * tpc), block(kBlock);
+    k_merge_multi<TE, T0, TO, Q, AHEAD><<<grid, block, lds, stream>>>(recs, experts, terms, chunks + first, nexp);
+  });
+}
+
+// The form a merge of `bytes` in all takes: go(quads per thread, experts loaded ahead, LDS to reserve).
+// A merge's waves live long (one round of loads per expert), so which tiles are open together decides
+// how well its N + 2 streams use the DRAM rows.  Measured on lists of 0.1-1.5e9 parameters:
+//   - fp32 experts, one quad per thread with 25 resident blocks: 3 experts 2.12 -> 1.77 ms (fp32 out),
+//     1.81 -> 1.65 (bf16 out), 8 experts 4.31 -> 3.75, with masks 2.11 -> 1.76; two quads at their best
+//     cap (12) 1.83.  Below 128 MB two quads are as fast or faster (2M parameters 15.0 against 15.7 us).
+//   - bf16 experts, two quads, none masked: the next expert's loads issued ahead with 25 resident
+//     blocks take 7 experts from 4.37 to 4.25 ms, 16 from 2.43 to 2.40, 4 from 1.134 to 1.115; with 3
+//     the gain is gone, with 2 it loses 1 %, and lists under 1 GB lose 1-4 %.
+//   - masked bf16 experts are bound by their draws and want every block resident (5.10 ms; 5.39 with
+//     25 blocks and loads ahead).
+template <typename TE, typename F>
+static hipError_t merge_form(int nexp, bool plain, uint64_t bytes, F&& go) {
+  using std::integral_constant;
+  constexpr uint32_t lds = lds_for_blocks(25);
+  if constexpr (std::is_same<TE, float>::value) {
+    if (bytes >= (128ull << 20))
+      return go(integral_constant<int, 1>(), std::false_type(), bytes >= kCapFromBytes ? lds : 0u);
+  } else {
+    if (plain && nexp >= 4 && bytes >= (1ull << 30)) return go(integral_constant<int, 2>(), std::true_type(), lds);
+  }
+  return go(integral_constant<int, 2>(), std::false_type(), 0u);
+}
+
+template <typename TE, typename T0, typename TO>
+constexpr uint64_t merge_bytes(uint64_t elems, int nexp) {
+  return elems * (uint64_t)(nexp * StorageBytes<TE>::value + StorageBytes<T0>::value + StorageBytes<TO>::value);
+}
+
+template <typename TE, typename T0, typename TO>
+static hipError_t merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, bool plain, hipStream_t stream) {
+  const uint64_t bytes = merge_bytes<TE, T0, TO>((uint64_t)rec.n, nexp);
+  return merge_form<TE>(nexp, plain, bytes, [&](auto q, auto ahead, uint32_t lds) {
+    return merge_one_as<TE, T0, TO, q(), ahead()>(rec, args, nexp, lds, stream);
   });
 }
 
 template <typename TE, typename T0, typename TO>
 static hipError_t merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
-                              const uint2* chunks, uint32_t nchunks, int nexp, hipStream_t stream) {
-  constexpr uint32_t tpc = tiles_per_chunk(kMergeQuads);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    k_merge_multi<TE, T0, TO><<<grid, block, 0, stream>>>(recs, experts, terms, chunks + first, nexp);
+                              const uint2* chunks, uint32_t nchunks, int nexp, bool plain, hipStream_t stream) {
+  const uint64_t bytes = merge_bytes<TE, T0, TO>((uint64_t)nchunks * kChunk, nexp);
+  return merge_form<TE>(nexp, plain, bytes, [&](auto q, auto ahead, uint32_t lds) {
+    return merge_multi_as<TE, T0, TO, q(), ahead()>(recs, experts, terms, chunks, nchunks, nexp, lds, stream);
   });
 }
 
@@ -185,14 +251,14 @@ static hipError_t merge_multi(const TensorRec* recs, const void* const* experts,
   }
 
 hipError_t launch_merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, int expert_dtype, int theta0_dtype,
-                            int out_dtype, hipStream_t stream) {
-  SMAT_MERGE_DISPATCH(merge_one, rec, args, nexp, stream)
+                            int out_dtype, bool plain, hipStream_t stream) {
+  SMAT_MERGE_DISPATCH(merge_one, rec, args, nexp, plain, stream)
 }
 
 hipError_t launch_merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
                               const uint2* chunks, uint32_t nchunks, int nexp, int expert_dtype, int theta0_dtype,
-                              int out_dtype, hipStream_t stream) {
-  SMAT_MERGE_DISPATCH(merge_multi, recs, experts, terms, chunks, nchunks, nexp, stream)
+                              int out_dtype, bool plain, hipStream_t stream) {
+  SMAT_MERGE_DISPATCH(merge_multi, recs, experts, terms, chunks, nchunks, nexp, plain, stream)
 }
 
 #undef SMAT_MERGE_DISPATCH

@@ -197,3 +197,37 @@ def test_plan_tiles_across_a_high_counter_word_boundary():
         torch.cuda.synchronize()
     for i in range(2):
         oracle_check(outs[i], [e[i] for e in ex], t0[i], terms[i], ids[i], offs[i])
+
+
+@pytest.mark.parametrize("e_dt,out_dt,nexp,keep,n", [
+    ("f32", "f32", 1, 1.0, (128 << 20) // 12 + 261),   # fp32 experts from 128 MB: one quad per thread
+    ("f32", "bf16", 3, 0.5, (512 << 20) // 18 + 3),    # from 512 MB with bounded resident blocks
+    ("f32", "f32", 4, 0.0, (512 << 20) // 24 + 1),
+    ("bf16", "bf16", 4, 1.0, (1 << 30) // 12 + 515),   # bf16 experts from 1 GB: loads one expert ahead
+    ("bf16", "f32", 5, 1.0, (1 << 30) // 16 + 2),
+    ("bf16", "bf16", 4, 0.5, (1 << 30) // 12 + 515)])  # masked: the form of the smaller lists
+def test_large_merge_is_its_shards_bit_for_bit(e_dt, out_dt, nexp, keep, n):
+    """A merge large enough for another form of the kernel gives the bytes of shards small enough for
+    the form that the oracle tests run, as one tensor and as a list of ragged tensors; the sizes sit
+    just past each form's line, so tile remainders and tails are crossed."""
+    t0, ex = make(n, nexp, e_dt, e_dt, 17 + nexp)
+    terms = [dict(gamma=0.3 + 0.1 * j, keep=keep if j != 1 else min(keep * 2, 1.0), seed=50 + j, step=j)
+             for j in range(nexp)]
+    one = torch.full((n,), float("nan"), dtype=DT[out_dt], device=DEV)
+    parts = torch.full((n,), float("nan"), dtype=DT[out_dt], device=DEV)
+    smat.smat_merge(ex, t0, one, terms, 5)
+    piece = 4 << 20
+    for a in range(0, n, piece):
+        cut = slice(a, min(a + piece, n))
+        smat.smat_merge([x[cut] for x in ex], t0[cut], parts[cut], terms, 5, a)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(one), bits(parts))
+    # the list form: a ragged split whose pieces keep whole quads except at the tensor's end
+    cuts = [0, 64, 4096 * 3 + 8, n // 3 // 4 * 4, n // 2 // 256 * 256, n]
+    split = lambda x: [x[a:b] for a, b in zip(cuts, cuts[1:])]  # noqa: E731
+    one.fill_(float("nan"))
+    with smat.MergePlan(split(t0), split(one), [split(x) for x in ex], tensor_ids=[5] * 5,
+                        elem_offsets=cuts[:-1]) as plan:
+        plan.merge(terms)
+    torch.cuda.synchronize()
+    assert torch.equal(bits(one), bits(parts))
