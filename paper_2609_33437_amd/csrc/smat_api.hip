@@ -44,7 +44,6 @@ constexpr uint32_t kMaxStep = 1u << 30;
 
 bool valid_dtype(int d) { return d == SMAT_F32 || d == SMAT_BF16; }
 size_t dtype_bytes(int d) { return d == SMAT_F32 ? 4 : 2; }
-size_t quad_align(int d) { return d == SMAT_F32 ? 16 : 8; }
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 bool overlap(const void* a, size_t abytes, const void* b, size_t bbytes) {
@@ -93,18 +92,25 @@ ScaleRec make_scale(const smat_op_params& p) {
   return r;
 }
 
+// Flags of the vector paths: every array aligned to its element.
 uint32_t sim_flags(const float* theta, const void* theta0, int t0_dt, const void* out, int out_dt,
                    uint64_t elem_offset, int64_t n) {
-  if (!(elem_offset % 4 == 0 && aligned(theta, 16) && aligned(theta0, quad_align(t0_dt)) &&
-        aligned(out, quad_align(out_dt))))
-    return 0u;
+  if (!(aligned(theta, 4) && aligned(theta0, dtype_bytes(t0_dt)) && aligned(out, dtype_bytes(out_dt)))) return 0u;
   const bool whole = n % 4 == 0 && elem_offset % (uint64_t)smat::tile_elems(smat::kSimQuads) == 0;
   return smat::kVecSim | (whole ? smat::kSimWhole : 0u);
 }
 
-uint32_t bwd_flags(const void* grad_sim, int g_dt, const float* grad_theta, uint64_t elem_offset) {
-  return (elem_offset % 4 == 0 && aligned(grad_sim, quad_align(g_dt)) && aligned(grad_theta, 16)) ? smat::kVecBwd
-                                                                                                  : 0u;
+uint32_t bwd_flags(const void* grad_sim, int g_dt, const float* grad_theta) {
+  return aligned(grad_sim, dtype_bytes(g_dt)) && aligned(grad_theta, 4) ? smat::kVecBwd : 0u;
+}
+
+// Tiles and chunks of a tensor count from the start of its first Philox group.
+uint64_t group_span(uint64_t elem_offset, int64_t n) { return n > 0 ? (uint64_t)n + smat::group_head(elem_offset) : 0; }
+uint64_t chunk_count(uint64_t elem_offset, int64_t n) {
+  return (group_span(elem_offset, n) + smat::kChunk - 1) / smat::kChunk;
+}
+bool too_many_tiles(uint64_t elem_offset, int64_t n) {
+  return (group_span(elem_offset, n) + smat::tile_elems(1) - 1) / smat::tile_elems(1) > 0x7FFFFFFF;
 }
 
 smat_status check_simulate_ptrs(const float* theta, const void* theta0, int t0_dt, const void* out, int out_dt,
@@ -182,11 +188,10 @@ smat_status make_adam(const smat_adamw_params& hp, AdamConsts* A, const char* wh
 }
 
 uint32_t adam_flags(const float* theta, const float* m1, const float* m2, const void* grad_sim, int g_dt,
-                    const float* grad_acc, uint64_t elem_offset) {
-  const bool base = elem_offset % 4 == 0 && aligned(theta, 16) && aligned(m1, 16) && aligned(m2, 16) &&
-                    aligned(grad_sim, quad_align(g_dt));
+                    const float* grad_acc) {
+  const bool base = aligned(theta, 4) && aligned(m1, 4) && aligned(m2, 4) && aligned(grad_sim, dtype_bytes(g_dt));
   uint32_t f = base ? smat::kVecAdam : 0u;
-  if (base && grad_acc && aligned(grad_acc, 16)) f |= smat::kVecAdamAcc;
+  if (base && grad_acc && aligned(grad_acc, 4)) f |= smat::kVecAdamAcc;
   return f;
 }
 
@@ -219,7 +224,7 @@ extern "C" smat_status smat_simulate(const float* theta, const void* theta0, sma
   if (st != SMAT_OK) return st;
   if (n == 0) return SMAT_OK;
   if (key.elem_offset > UINT64_MAX - (uint64_t)n) return fail(SMAT_ERR_INVALID, "smat_simulate: elem_offset + n overflows");
-  if ((n + smat::tile_elems(1) - 1) / smat::tile_elems(1) > 0x7FFFFFFF) return fail(SMAT_ERR_INVALID, "smat_simulate: n too large");
+  if (too_many_tiles(key.elem_offset, n)) return fail(SMAT_ERR_INVALID, "smat_simulate: n too large");
   st = check_simulate_ptrs(theta, theta0, theta0_dtype, out, out_dtype, n, "smat_simulate");
   if (st != SMAT_OK) return st;
   TensorRec rec{};
@@ -230,7 +235,8 @@ extern "C" smat_status smat_simulate(const float* theta, const void* theta0, sma
   rec.elem_offset = key.elem_offset;
   rec.tensor_id = key.tensor_id;
   rec.sflags = sim_flags(theta, theta0, theta0_dtype, out, out_dtype, key.elem_offset, n);
-  SMAT_HIP(smat::launch_simulate_one(rec, prm, theta0_dtype, out_dtype, key.seed, key.step, stream));
+  SMAT_HIP(smat::launch_simulate_one(smat::device_rec(rec, theta0_dtype, out_dtype, 0), prm, theta0_dtype, out_dtype,
+                                     key.seed, key.step, stream));
   return SMAT_OK;
 }
 
@@ -246,7 +252,7 @@ extern "C" smat_status smat_backward_accum(const void* grad_sim, smat_dtype grad
   if (n == 0) return SMAT_OK;
   if (key.elem_offset > UINT64_MAX - (uint64_t)n)
     return fail(SMAT_ERR_INVALID, "smat_backward_accum: elem_offset + n overflows");
-  if ((n + smat::tile_elems(1) - 1) / smat::tile_elems(1) > 0x7FFFFFFF) return fail(SMAT_ERR_INVALID, "smat_backward_accum: n too large");
+  if (too_many_tiles(key.elem_offset, n)) return fail(SMAT_ERR_INVALID, "smat_backward_accum: n too large");
   if (!grad_sim || !grad_theta) return fail(SMAT_ERR_INVALID, "smat_backward_accum: null pointer with n > 0");
   if (overlap(grad_sim, (size_t)n * dtype_bytes(grad_dtype), grad_theta, (size_t)n * 4))
     return fail(SMAT_ERR_INVALID, "smat_backward_accum: grad_sim must not overlap grad_theta");
@@ -256,8 +262,9 @@ extern "C" smat_status smat_backward_accum(const void* grad_sim, smat_dtype grad
   rec.n = n;
   rec.elem_offset = key.elem_offset;
   rec.tensor_id = key.tensor_id;
-  rec.sflags = bwd_flags(grad_sim, grad_dtype, grad_theta, key.elem_offset);
-  SMAT_HIP(smat::launch_backward_one(rec, prm, grad_dtype, lambda, key.seed, key.step, stream));
+  rec.sflags = bwd_flags(grad_sim, grad_dtype, grad_theta);
+  SMAT_HIP(smat::launch_backward_one(smat::device_rec(rec, 0, 0, grad_dtype), prm, grad_dtype, lambda, key.seed, key.step,
+                                     stream));
   return SMAT_OK;
 }
 
@@ -292,7 +299,7 @@ extern "C" smat_status smat_adamw_fused(const void* grad_sim, smat_dtype grad_dt
   if (n == 0) return SMAT_OK;
   if (key.elem_offset > UINT64_MAX - (uint64_t)n)
     return fail(SMAT_ERR_INVALID, "smat_adamw_fused: elem_offset + n overflows");
-  if ((n + smat::tile_elems(1) - 1) / smat::tile_elems(1) > 0x7FFFFFFF)
+  if (too_many_tiles(key.elem_offset, n))
     return fail(SMAT_ERR_INVALID, "smat_adamw_fused: n too large");
   if (!grad_sim) return fail(SMAT_ERR_INVALID, "smat_adamw_fused: null grad_sim with n > 0");
   st = check_adam_ptrs(theta, exp_avg, exp_avg_sq, grad_sim, grad_dtype, grad_acc, n, "smat_adamw_fused");
@@ -304,10 +311,10 @@ extern "C" smat_status smat_adamw_fused(const void* grad_sim, smat_dtype grad_dt
   rec.n = n;
   rec.elem_offset = key.elem_offset;
   rec.tensor_id = key.tensor_id;
-  rec.sflags = adam_flags(theta, exp_avg, exp_avg_sq, grad_sim, grad_dtype, grad_acc, key.elem_offset);
+  rec.sflags = adam_flags(theta, exp_avg, exp_avg_sq, grad_sim, grad_dtype, grad_acc);
   const AdamRec sr{exp_avg, exp_avg_sq};
-  SMAT_HIP(smat::launch_adamw_one(rec, sr, prm, A, grad_dtype, grad_acc != nullptr, lambda, key.seed, key.step,
-                                  grad_scale_dev, stream));
+  SMAT_HIP(smat::launch_adamw_one(smat::device_rec(rec, 0, 0, grad_dtype), smat::device_adam(sr, rec), prm, A,
+                                  grad_dtype, grad_acc != nullptr, lambda, key.seed, key.step, grad_scale_dev, stream));
   return SMAT_OK;
 }
 
@@ -419,6 +426,12 @@ smat_status check_plan_spans(const smat_plan* p, const std::vector<TensorRec>& r
     }
   }
   return check_spans(s.data(), s.size(), where);
+}
+
+// The list's records as the kernels read them, into a staging buffer.
+void device_recs(const smat_plan* p, const std::vector<TensorRec>& recs, char* staging) {
+  TensorRec* out = reinterpret_cast<TensorRec*>(staging);
+  for (size_t i = 0; i < recs.size(); ++i) out[i] = smat::device_rec(recs[i], p->t0_dt, p->out_dt, p->g_dt);
 }
 
 smat_status release(smat_plan* p) {
@@ -536,11 +549,11 @@ extern "C" smat_status smat_plan_create(const smat_tensor_desc* descs, int32_t c
     r.tensor_id = d.tensor_id;
     if (d.n > 0) {
       r.sflags = sim_flags(r.theta, r.theta0, theta0_dtype, r.out, out_dtype, d.elem_offset, d.n);
-      if (d.grad_sim) r.sflags |= bwd_flags(d.grad_sim, grad_dtype, d.grad_theta, d.elem_offset);
+      if (d.grad_sim) r.sflags |= bwd_flags(d.grad_sim, grad_dtype, d.grad_theta);
     }
     p->expert_ptrs[i] = const_cast<float*>(d.theta);
     p->sim_ptrs[i] = d.out;
-    nchunks += (uint64_t)((d.n + smat::kChunk - 1) / smat::kChunk);
+    nchunks += chunk_count(d.elem_offset, d.n);
   }
   if (smat_status st = check_plan_spans(p, p->recs, nullptr, "smat_plan_create"); st != SMAT_OK) {
     delete p;
@@ -552,7 +565,7 @@ extern "C" smat_status smat_plan_create(const smat_tensor_desc* descs, int32_t c
   }
   p->chunks.reserve(nchunks);
   for (int32_t i = 0; i < count; ++i) {
-    const uint32_t nc = (uint32_t)((p->descs[i].n + smat::kChunk - 1) / smat::kChunk);
+    const uint32_t nc = (uint32_t)chunk_count(p->descs[i].elem_offset, p->descs[i].n);
     for (uint32_t c = 0; c < nc; ++c) p->chunks.push_back(make_uint2((uint32_t)i, c));
   }
 
@@ -604,7 +617,7 @@ extern "C" smat_status smat_plan_bind_workspace(smat_plan* p, void* workspace, s
       SMAT_HIP(hipHostMalloc((void**)&s, (sizeof(ParamRec) + sizeof(ScaleRec)) * std::max(p->count, 1),
                              hipHostMallocDefault));
   std::memset(p->static_staging, 0, static_bytes);
-  std::memcpy(p->static_staging + p->off_recs, p->recs.data(), sizeof(TensorRec) * p->count);
+  device_recs(p, p->recs, p->static_staging + p->off_recs);
   std::memcpy(p->static_staging + p->off_chunks, p->chunks.data(), sizeof(uint2) * p->chunks.size());
   std::memcpy(p->static_staging + p->off_expert, p->expert_ptrs.data(), sizeof(void*) * p->count);
   std::memcpy(p->static_staging + p->off_sim, p->sim_ptrs.data(), sizeof(void*) * p->count);
@@ -841,8 +854,7 @@ extern "C" smat_status smat_plan_bind_adam_state(smat_plan* p, const smat_adam_s
           overlap(m, (size_t)r.n * 4, r.theta0, (size_t)r.n * dtype_bytes(p->t0_dt)))
         return fail(SMAT_ERR_INVALID, "%s: moments must not overlap theta0 or the simulated buffer", where);
     recs[i].sflags = (r.sflags & ~(smat::kVecAdam | smat::kVecAdamAcc)) |
-                     adam_flags(r.theta, adam[i].exp_avg, adam[i].exp_avg_sq, r.grad_sim, p->g_dt, r.grad_theta,
-                                r.elem_offset);
+                     adam_flags(r.theta, adam[i].exp_avg, adam[i].exp_avg_sq, r.grad_sim, p->g_dt, r.grad_theta);
   }
   if (smat_status st = check_plan_spans(p, recs, &adam, "smat_plan_bind_adam_state"); st != SMAT_OK) return st;
   const size_t rec_bytes = sizeof(TensorRec) * p->count, adam_bytes = sizeof(AdamRec) * p->count;
@@ -852,8 +864,9 @@ extern "C" smat_status smat_plan_bind_adam_state(smat_plan* p, const smat_adam_s
   } else {
     SMAT_HIP(hipEventSynchronize(p->ev_adam));  // the previous upload has left the staging buffer
   }
-  std::memcpy(p->adam_staging, recs.data(), rec_bytes);
-  std::memcpy(p->adam_staging + rec_bytes, adam.data(), adam_bytes);
+  device_recs(p, recs, p->adam_staging);
+  AdamRec* staged = reinterpret_cast<AdamRec*>(p->adam_staging + rec_bytes);
+  for (int32_t i = 0; i < p->count; ++i) staged[i] = smat::device_adam(adam[i], recs[i]);
   if (p->count > 0) {
     SMAT_HIP(hipMemcpyAsync(p->ws + p->off_recs, p->adam_staging, rec_bytes, hipMemcpyHostToDevice, stream));
     SMAT_HIP(hipMemcpyAsync(p->ws + p->off_adam, p->adam_staging + rec_bytes, adam_bytes, hipMemcpyHostToDevice, stream));
@@ -892,9 +905,9 @@ extern "C" smat_status smat_plan_set_grads(smat_plan* p, const void* const* grad
     r.grad_sim = gs;
     r.grad_theta = gt;
     r.sflags &= ~(smat::kVecBwd | smat::kVecAdam | smat::kVecAdamAcc);
-    if (gs) r.sflags |= bwd_flags(gs, p->g_dt, gt, r.elem_offset);
+    if (gs) r.sflags |= bwd_flags(gs, p->g_dt, gt);
     if (p->adam_bound)
-      r.sflags |= adam_flags(r.theta, p->adam[i].exp_avg, p->adam[i].exp_avg_sq, gs, p->g_dt, gt, r.elem_offset);
+      r.sflags |= adam_flags(r.theta, p->adam[i].exp_avg, p->adam[i].exp_avg_sq, gs, p->g_dt, gt);
   }
   if (smat_status st = check_plan_spans(p, recs, p->adam_bound ? &p->adam : nullptr, "smat_plan_set_grads");
       st != SMAT_OK)
@@ -906,7 +919,7 @@ extern "C" smat_status smat_plan_set_grads(smat_plan* p, const void* const* grad
   } else {
     SMAT_HIP(hipEventSynchronize(p->ev_adam));  // the previous table upload has left the staging buffer
   }
-  std::memcpy(p->adam_staging, recs.data(), rec_bytes);
+  device_recs(p, recs, p->adam_staging);
   if (p->count > 0)
     SMAT_HIP(hipMemcpyAsync(p->ws + p->off_recs, p->adam_staging, rec_bytes, hipMemcpyHostToDevice, stream));
   SMAT_HIP(hipEventRecord(p->ev_adam, stream));
@@ -1168,6 +1181,7 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
     st = check_simulate_ptrs(d.theta, d.theta0, theta0_dtype, d.out, out_dtype, d.n, where);
     if (st != SMAT_OK) return st;
     r.sflags = sim_flags(d.theta, d.theta0, theta0_dtype, d.out, out_dtype, d.elem_offset, d.n);
+    r = smat::device_rec(r, theta0_dtype, out_dtype, 0);
     const size_t n = (size_t)d.n;
     g_scratch_spans[nspans++] = Span{reinterpret_cast<uintptr_t>(d.theta), reinterpret_cast<uintptr_t>(d.theta) + n * 4,
                                      false, i, "theta"};
@@ -1179,7 +1193,7 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
                                        reinterpret_cast<uintptr_t>(d.theta0) + n * dtype_bytes(theta0_dtype), false, i,
                                        "theta0"};
     g_scratch_ranges[nranges++] = {d.tensor_id, {d.elem_offset, d.elem_offset + (uint64_t)d.n}};
-    const uint64_t nc = (uint64_t)((d.n + smat::kChunk - 1) / smat::kChunk);
+    const uint64_t nc = chunk_count(d.elem_offset, d.n);
     if (nchunks + nc > max_chunks)
       return fail(SMAT_ERR_INVALID, "%s: the list needs more than the %zu chunks of %lld elements that the %zu-byte "
                   "static tables hold for %d tensors (use a plan)", where0, max_chunks, (long long)smat::kChunk,
@@ -1257,9 +1271,9 @@ smat_status make_merge(const smat_merge_term& m, MergeRec* out, const char* wher
 }
 
 uint32_t merge_flags(const void* const* experts, int nexp, int e_dt, const void* theta0, int t0_dt, const void* out,
-                     int out_dt, uint64_t elem_offset) {
-  bool ok = elem_offset % 4 == 0 && aligned(theta0, quad_align(t0_dt)) && aligned(out, quad_align(out_dt));
-  for (int j = 0; j < nexp && ok; ++j) ok = aligned(experts[j], quad_align(e_dt));
+                     int out_dt) {
+  bool ok = aligned(theta0, dtype_bytes(t0_dt)) && aligned(out, dtype_bytes(out_dt));
+  for (int j = 0; j < nexp && ok; ++j) ok = aligned(experts[j], dtype_bytes(e_dt));
   return ok ? smat::kVecMerge : 0u;
 }
 
@@ -1304,7 +1318,7 @@ extern "C" smat_status smat_merge(const void* const* experts, int32_t n_experts,
   }
   if (n == 0) return SMAT_OK;
   if (elem_offset > UINT64_MAX - (uint64_t)n) return fail(SMAT_ERR_INVALID, "smat_merge: elem_offset + n overflows");
-  if ((n + smat::tile_elems(1) - 1) / smat::tile_elems(1) > 0x7FFFFFFF) return fail(SMAT_ERR_INVALID, "smat_merge: n too large");
+  if (too_many_tiles(elem_offset, n)) return fail(SMAT_ERR_INVALID, "smat_merge: n too large");
   smat_status st = check_merge_ptrs(experts, n_experts, expert_dtype, theta0, theta0_dtype, out, out_dtype, n,
                                     "smat_merge");
   if (st != SMAT_OK) return st;
@@ -1314,8 +1328,11 @@ extern "C" smat_status smat_merge(const void* const* experts, int32_t n_experts,
   rec.n = n;
   rec.elem_offset = elem_offset;
   rec.tensor_id = tensor_id;
-  rec.sflags = merge_flags(experts, n_experts, expert_dtype, theta0, theta0_dtype, out, out_dtype, elem_offset);
-  SMAT_HIP(smat::launch_merge_one(rec, A, n_experts, expert_dtype, theta0_dtype, out_dtype, plain, stream));
+  rec.sflags = merge_flags(experts, n_experts, expert_dtype, theta0, theta0_dtype, out, out_dtype);
+  for (int32_t j = 0; j < n_experts; ++j)
+    A.x[j] = smat::back_ptr(experts[j], smat::group_head(elem_offset), dtype_bytes(expert_dtype));
+  SMAT_HIP(smat::launch_merge_one(smat::device_rec(rec, theta0_dtype, out_dtype, 0), A, n_experts, expert_dtype,
+                                  theta0_dtype, out_dtype, plain, stream));
   return SMAT_OK;
 }
 
@@ -1376,7 +1393,7 @@ extern "C" smat_status smat_merge_plan_create(const smat_merge_desc* descs, int3
                                       d.out, out_dtype, d.n, where);
     if (st != SMAT_OK) return st;
     ranges.push_back({d.tensor_id, {d.elem_offset, d.elem_offset + (uint64_t)d.n}});
-    nchunks += (uint64_t)((d.n + smat::kChunk - 1) / smat::kChunk);
+    nchunks += chunk_count(d.elem_offset, d.n);
   }
   // a tensor id may cover disjoint shards of one tensor, never overlapping ranges (same draws twice)
   std::sort(ranges.begin(), ranges.end());
@@ -1419,8 +1436,13 @@ extern "C" smat_status smat_merge_plan_create(const smat_merge_desc* descs, int3
     r.tensor_id = d.tensor_id;
     if (d.n > 0)
       r.sflags = merge_flags(experts + (size_t)i * n_experts, n_experts, expert_dtype, d.theta0, theta0_dtype, d.out,
-                             out_dtype, d.elem_offset);
-    const uint32_t nc = (uint32_t)((d.n + smat::kChunk - 1) / smat::kChunk);
+                             out_dtype);
+    r = smat::device_rec(r, theta0_dtype, out_dtype, 0);
+    for (int32_t j = 0; j < n_experts && d.n > 0; ++j) {
+      const void*& x = p->experts[(size_t)i * n_experts + j];
+      x = smat::back_ptr(x, smat::group_head(d.elem_offset), dtype_bytes(expert_dtype));
+    }
+    const uint32_t nc = (uint32_t)chunk_count(d.elem_offset, d.n);
     for (uint32_t c = 0; c < nc; ++c) p->chunks.push_back(make_uint2((uint32_t)i, c));
   }
   const size_t cells = (size_t)count * n_experts;

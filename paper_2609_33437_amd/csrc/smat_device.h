@@ -24,12 +24,20 @@ enum : uint32_t {
 
 // Noise forms (smat_noise_kind).
 enum NoiseKind : int { kGaussian = 0, kUniform = 1, kLaplace = 2 };
-// Static flags of a tensor (TensorRec::sflags): pointers aligned for quad vectors and
-// elem_offset a multiple of 4, so quads line up with Philox groups.  kSimWhole adds that every
-// simulate tile of the tensor takes the vector path: n is a multiple of 4 (no ragged last tile) and
-// elem_offset a multiple of the 256-element tile (no tile's groups cross a multiple of 2^32), so a
-// block tests one bit instead of the three conditions.
+// Static flags of a tensor (TensorRec::sflags): every array of the operation aligned to its element
+// (4 B fp32, 2 B bf16), so whole quads move as vectors.  gfx950 loads and stores a vector at any
+// element's address in one instruction; a tensor off its vector boundary costs only the cache lines
+// that its waves' spans share at their ends.  kSimWhole adds that every simulate tile of the tensor
+// takes the vector path whole: n is a multiple of 4 (no ragged last tile) and elem_offset a multiple of
+// the 256-element tile (no head, no tile's groups cross a multiple of 2^32), so a block tests one bit
+// instead of the conditions.
+//
+// The kernels see a tensor from the start of its first Philox group (device_rec): where elem_offset is
+// not a multiple of 4, its record's pointers lie head = elem_offset mod 4 elements before the tensor's
+// first one, n counts them, and bits kHeadShift.. of sflags hold head.  Quads then are Philox groups for
+// every offset; the first quad's leading `head` elements belong to nobody and are never accessed.
 enum : uint32_t { kVecSim = 1u, kVecBwd = 2u, kSimWhole = 32u };
+constexpr uint32_t kHeadShift = 8u;
 
 struct alignas(16) TensorRec {
   const float* theta;
@@ -147,7 +155,7 @@ __host__ __device__ inline AdamConsts adam_consts(const AdamHyper& h, float lr, 
   A.grad_scale = h.grad_scale;
   return A;
 }
-// Static flag: theta, the moments, grad_sim (and grad_theta when accumulating) aligned for quads.
+// Static flag: theta, the moments, grad_sim (and grad_theta when accumulating) aligned to their elements.
 enum : uint32_t { kVecAdam = 4u, kVecAdamAcc = 8u };
 
 // Work decomposition: a block of kBlock threads (one wave) handles one tile of Q quads per
@@ -438,6 +446,9 @@ __device__ __forceinline__ float sim_value(float th, float b, bool kept, float t
 // ---------------------------------------------------------------- memory
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// The same in memory, at any element's address (the instruction is the aligned one).
+typedef f32x4 f32x4_mem __attribute__((aligned(4)));
+typedef u32x2 u32x2_mem __attribute__((aligned(2)));
 
 struct Bf16 {};  // storage tag: bfloat16 stored as 16-bit words
 
@@ -484,14 +495,14 @@ template <>
 struct QuadIO<float> {
   typedef f32x4 Raw;
   static __device__ __forceinline__ Raw load_raw(const void* base, uint32_t q) {
-    return __builtin_nontemporal_load(gload_at<f32x4>(base, q));
+    return __builtin_nontemporal_load(gload_at<f32x4_mem>(base, q));
   }
   static __device__ __forceinline__ void unpack(const Raw& x, float v[4]) {
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
   }
   static __device__ __forceinline__ void store(void* base, uint32_t q, const float v[4]) {
     const f32x4 x = {v[0], v[1], v[2], v[3]};
-    __builtin_nontemporal_store(x, gstore_at<f32x4>(base, q));
+    __builtin_nontemporal_store(x, gstore_at<f32x4_mem>(base, q));
   }
   static __device__ __forceinline__ float load1(const void* base, uint32_t i) { return *gload_at<float>(base, i); }
   static __device__ __forceinline__ void store1(void* base, uint32_t i, float v) { *gstore_at<float>(base, i) = v; }
@@ -501,7 +512,7 @@ template <>
 struct QuadIO<Bf16> {
   typedef u32x2 Raw;
   static __device__ __forceinline__ Raw load_raw(const void* base, uint32_t q) {
-    return __builtin_nontemporal_load(gload_at<u32x2>(base, q));
+    return __builtin_nontemporal_load(gload_at<u32x2_mem>(base, q));
   }
   static __device__ __forceinline__ void unpack(const Raw& x, float v[4]) {
     v[0] = bf16_to_f32(x.x & 0xFFFFu);
@@ -511,7 +522,7 @@ struct QuadIO<Bf16> {
   }
   static __device__ __forceinline__ void store(void* base, uint32_t q, const float v[4]) {
     const u32x2 x = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-    __builtin_nontemporal_store(x, gstore_at<u32x2>(base, q));
+    __builtin_nontemporal_store(x, gstore_at<u32x2_mem>(base, q));
   }
   static __device__ __forceinline__ float load1(const void* base, uint32_t i) {
     return bf16_to_f32(*gload_at<uint16_t>(base, i));

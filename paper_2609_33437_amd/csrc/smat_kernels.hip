@@ -43,21 +43,29 @@ __device__ __forceinline__ void simulate_tile_case(const Tile& T, const ParamRec
   void* out = T.out;
   const uint64_t e0 = T.e0;
 
-  // element by element: tensors whose pointers or offset break quad alignment, the tile that holds
-  // a tensor's last 1-3 elements, and a tile whose groups cross a multiple of 2^32 (kSimWhole rules
-  // out all three for the whole tensor; otherwise they are tested as one word, in scalar registers)
+  // element by element, from the quad's draws: tensors whose pointers are not aligned to their
+  // elements, the tiles that hold a tensor's first or last partial quad, and a tile whose groups cross a
+  // multiple of 2^32 (kSimWhole rules out all for the whole tensor; otherwise they are tested as one
+  // word, in scalar registers)
   if (!(T.sflags & kSimWhole) &&
-      (((T.sflags & kVecSim) ^ kVecSim) | (len & 3u) | groups_wrap_bit(e0, kBlock)) != 0u) {
+      (((T.sflags & kVecSim) ^ kVecSim) | (len & 3u) | T.head | groups_wrap_bit(e0, kBlock)) != 0u) {
     normal_priority();
-    const uint32_t i0 = threadIdx.x * 4u;
-    for (uint32_t i = i0; i < len && i < i0 + 4u; ++i) {
-      const uint64_t e = e0 + i;
-      const uint64_t g = e >> 2;
-      const uint32_t lane = (uint32_t)e & 3u;
-      bool kept = all_kept;
-      if (MASK) kept = pick(group_words(g, tensor_id, cmask, K), lane) < thr;
+    const uint32_t q = threadIdx.x;
+    const uint32_t lo = max(4u * q, T.head), hi = min(4u * q + 4u, len);
+    if (lo >= hi) return;
+    const uint64_t g = (e0 >> 2) + q;
+    Words wm;
+    if (MASK) wm = group_words(g, tensor_id, cmask, K);
+    float z[4];
+    if (NOISE) quad_noise<KIND>(group_words(g, tensor_id, cnoise, K), z);
+    const uint32_t mw[4] = {wm.w0, wm.w1, wm.w2, wm.w3};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t i = 4u * q + j;
+      if (i < lo || i >= hi) continue;
+      const bool kept = MASK ? mw[j] < thr : all_kept;
       float y = sim_value(QuadIO<float>::load1(th, i), QuadIO<T0>::load1(t0, i), kept, t);
-      if (NOISE) y = __builtin_fmaf(sigma, lane_noise<KIND>(group_words(g, tensor_id, cnoise, K), lane), y);
+      if (NOISE) y = __builtin_fmaf(sigma, z[j], y);
       QuadIO<TO>::store1(out, i, y);
     }
     return;
@@ -162,34 +170,36 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
   float* gt = T.grad_theta;
   const uint64_t e0 = T.e0;
 
-  auto one = [&](uint32_t i) {
-    const uint64_t e = e0 + i;
-    bool kept = all_kept;
-    if (use_mask) kept = pick(group_words(e >> 2, tensor_id, cmask, K), (uint32_t)e & 3u) < thr;
-    if (ACC) {
-      if (kept) QuadIO<float>::store1(gt, i, __builtin_fmaf(c, QuadIO<TG>::load1(gs, i), QuadIO<float>::load1(gt, i)));
-    } else {
-      QuadIO<float>::store1(gt, i, kept ? __builtin_fmaf(c, QuadIO<TG>::load1(gs, i), 0.0f) : 0.0f);
+  // the elements of quad q that are the tensor's, one at a time
+  auto edge = [&](uint32_t q) {
+    const uint32_t lo = max(4u * q, T.head), hi = min(4u * q + 4u, len);
+    if (lo >= hi) return;
+    Words w;
+    if (use_mask) w = group_words((e0 >> 2) + q, tensor_id, cmask, K);
+    for (uint32_t i = lo; i < hi; ++i) {
+      const bool kept = use_mask ? pick(w, i & 3u) < thr : all_kept;
+      if (ACC) {
+        if (kept)
+          QuadIO<float>::store1(gt, i, __builtin_fmaf(c, QuadIO<TG>::load1(gs, i), QuadIO<float>::load1(gt, i)));
+      } else {
+        QuadIO<float>::store1(gt, i, kept ? __builtin_fmaf(c, QuadIO<TG>::load1(gs, i), 0.0f) : 0.0f);
+      }
     }
   };
 
   if (!(T.sflags & kVecBwd) || groups_wrap(e0, Q * kBlock)) {
 #pragma unroll
-    for (int u = 0; u < Q; ++u) {
-      const uint32_t i0 = (u * kBlock + threadIdx.x) * 4u;
-      for (uint32_t i = i0; i < len && i < i0 + 4u; ++i) one(i);
-    }
+    for (int u = 0; u < Q; ++u) edge(u * kBlock + threadIdx.x);
     return;
   }
   // loads first (clamped, unguarded), the regenerated mask while they are in flight, then the update
-  const uint32_t nq = len >> 2;
-  if (nq > 0) {
+  const WholeQuads W = whole_quads(len, T.head);
+  if (W.any()) {
     typename QuadIO<TG>::Raw ra[Q];
     typename QuadIO<float>::Raw rb[Q];
 #pragma unroll
     for (int u = 0; u < Q; ++u) {
-      const uint32_t q = u * kBlock + threadIdx.x;
-      const uint32_t qc = min(q, nq - 1u);
+      const uint32_t qc = W.clamp(u * kBlock + threadIdx.x);
       ra[u] = QuadIO<TG>::load_raw(gs, qc);
       if (ACC) rb[u] = QuadIO<float>::load_raw(gt, qc);
     }
@@ -210,7 +220,7 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
 #pragma unroll
     for (int u = 0; u < Q; ++u) {
       const uint32_t q = u * kBlock + threadIdx.x;
-      if (q < nq) {
+      if (W.has(q)) {
         float a[4], b[4] = {0.f, 0.f, 0.f, 0.f}, o[4];
         QuadIO<TG>::unpack(ra[u], a);
         if (ACC) QuadIO<float>::unpack(rb[u], b);
@@ -220,9 +230,7 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
       }
     }
   }
-  if ((len & 3u) && threadIdx.x == (nq & (kBlock - 1))) {
-    for (uint32_t i = nq * 4u; i < len; ++i) one(i);
-  }
+  for_edges(len, T.head, edge);
 }
 
 // ---------------------------------------------------------------- kernels

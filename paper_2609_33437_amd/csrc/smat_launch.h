@@ -56,8 +56,38 @@ inline P* step_ptr(P* p, uint64_t elems, size_t bytes) {
   return p ? reinterpret_cast<P*>(reinterpret_cast<uintptr_t>(p) + elems * bytes) : p;
 }
 
-// Elements [off, off + len) of a one-tensor record as a record of its own.  off is a multiple of the
-// tile, hence of 4 elements, so every pointer keeps its alignment and the quad flags still hold.
+// p moved back by `elems` elements of `bytes` each (a null pointer stays null).
+template <typename P>
+inline P* back_ptr(P* p, uint64_t elems, size_t bytes) {
+  return p ? reinterpret_cast<P*>(reinterpret_cast<uintptr_t>(p) - elems * bytes) : p;
+}
+
+// Elements before a tensor's first one in its first Philox group.
+inline uint32_t group_head(uint64_t elem_offset) { return (uint32_t)elem_offset & 3u; }
+
+// A tensor's record as the kernels read it: from the start of its first Philox group, with the head in
+// sflags (see TensorRec::sflags in smat_device.h).  A record without a head is unchanged.
+inline TensorRec device_rec(const TensorRec& R, int t0_dtype, int out_dtype, int g_dtype) {
+  const uint32_t head = R.n > 0 ? group_head(R.elem_offset) : 0u;
+  TensorRec r = R;
+  r.theta = back_ptr(R.theta, head, 4);
+  r.theta0 = back_ptr(R.theta0, head, storage_bytes(t0_dtype));
+  r.out = back_ptr(R.out, head, storage_bytes(out_dtype));
+  r.grad_sim = back_ptr(R.grad_sim, head, storage_bytes(g_dtype));
+  r.grad_theta = back_ptr(R.grad_theta, head, 4);
+  r.n = R.n + head;
+  r.elem_offset = R.elem_offset - head;
+  r.sflags = R.sflags | (head << kHeadShift);
+  return r;
+}
+inline AdamRec device_adam(const AdamRec& A, const TensorRec& R) {
+  const uint32_t head = R.n > 0 ? group_head(R.elem_offset) : 0u;
+  return AdamRec{back_ptr(A.exp_avg, head, 4), back_ptr(A.exp_avg_sq, head, 4)};
+}
+
+// Elements [off, off + len) of a one-tensor record (as device_rec gives it) as a record of its own.  off
+// is a multiple of the tile, hence of 4 elements, so every pointer keeps its alignment, the flags still
+// hold and only the first piece has the head.
 inline TensorRec rec_piece(const TensorRec& R, uint64_t off, uint64_t len, int t0_dtype, int out_dtype,
                            int g_dtype) {
   TensorRec r = R;
@@ -68,6 +98,7 @@ inline TensorRec rec_piece(const TensorRec& R, uint64_t off, uint64_t len, int t
   r.grad_theta = step_ptr(R.grad_theta, off, 4);
   r.n = (int64_t)len;
   r.elem_offset = R.elem_offset + off;
+  if (off) r.sflags &= (1u << kHeadShift) - 1u;
   return r;
 }
 
@@ -134,7 +165,7 @@ struct alignas(8) MergeRec {
 };
 static_assert(sizeof(MergeRec) == 104, "MergeRec layout");
 constexpr int kMaxExperts = 16;
-constexpr uint32_t kVecMerge = 16u;  // TensorRec::sflags: theta0, out and every expert quad-aligned, offset % 4 == 0
+constexpr uint32_t kVecMerge = 16u;  // TensorRec::sflags: theta0, out and every expert aligned to their elements
 // Arguments of the one-tensor merge, passed by value (no device tables).
 struct MergeArgs {
   const void* x[kMaxExperts];

@@ -17,36 +17,49 @@ namespace smat {
 // Thread x owns quads x + u kBlock, u < Q, of the tile.  AHEAD: for terms without masks, the loads run
 // one expert ahead of the sums.
 template <typename TE, typename T0, typename TO, int Q, bool AHEAD, typename XAT, typename RAT>
-__device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t e0, uint32_t len, uint32_t tensor_id,
-                                           bool vec, int nexp, XAT expert_at, RAT rec_at) {
-  auto one = [&](uint32_t i) {
-    const uint64_t e = e0 + i;
-    const float b = QuadIO<T0>::load1(t0p, i);
-    float acc = b;
-    for (int j = 0; j < nexp; ++j) {
-      const MergeRec R = rec_at(j);
-      if (R.flags & kFlagDropAll) continue;
-      bool kept = true;
-      if (R.flags & kFlagMask)
-        kept = pick(group_words(e >> 2, tensor_id, (R.step << 2) | kStreamMask, (uint32_t)R.seed,
-                                (uint32_t)(R.seed >> 32)),
-                    (uint32_t)e & 3u) < R.thr;
-      if (kept) acc = __builtin_fmaf(R.t, QuadIO<TE>::load1(expert_at(j), i), __builtin_fmaf(-R.t, b, acc));
+__device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t e0, uint32_t len, uint32_t head,
+                                           uint32_t tensor_id, bool vec, int nexp, XAT expert_at, RAT rec_at) {
+  // the elements of quad q that are the tensor's, one at a time within each expert
+  auto edge = [&](uint32_t q) {
+    const uint32_t lo = max(4u * q, head), hi = min(4u * q + 4u, len);
+    if (lo >= hi) return;
+    float b[4], acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t i = 4u * q + j;
+      acc[j] = b[j] = i >= lo && i < hi ? QuadIO<T0>::load1(t0p, i) : 0.0f;
     }
-    QuadIO<TO>::store1(outp, i, acc);
+    for (int x = 0; x < nexp; ++x) {
+      const MergeRec R = rec_at(x);
+      if (R.flags & kFlagDropAll) continue;
+      const void* xp = expert_at(x);
+      Words w{};
+      if (R.flags & kFlagMask)
+        w = group_words((e0 >> 2) + q, tensor_id, (R.step << 2) | kStreamMask, (uint32_t)R.seed,
+                        (uint32_t)(R.seed >> 32));
+      const uint32_t mw[4] = {w.w0, w.w1, w.w2, w.w3};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t i = 4u * q + j;
+        const bool kept = i >= lo && i < hi && (!(R.flags & kFlagMask) || mw[j] < R.thr);
+        if (kept) acc[j] = __builtin_fmaf(R.t, QuadIO<TE>::load1(xp, i), __builtin_fmaf(-R.t, b[j], acc[j]));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t i = 4u * q + j;
+      if (i >= lo && i < hi) QuadIO<TO>::store1(outp, i, acc[j]);
+    }
   };
 
   if (!vec || groups_wrap(e0, Q * kBlock)) {
     normal_priority();
-#pragma unroll
-    for (int u = 0; u < Q; ++u) {
-      const uint32_t i0 = (u * kBlock + threadIdx.x) * 4u;
-      for (uint32_t i = i0; i < len && i < i0 + 4u; ++i) one(i);
-    }
+#pragma unroll 1
+    for (int u = 0; u < Q; ++u) edge(u * kBlock + threadIdx.x);
     return;
   }
-  const uint32_t nq = len >> 2;
-  if (nq > 0) {
+  const WholeQuads W = whole_quads(len, head);
+  if (W.any()) {
     float b[Q][4], acc[Q][4];
     // the experts' masks of a group differ only in the key, so they share round 1's product
     const TileGroups G = tile_groups(e0);
@@ -57,15 +70,12 @@ __device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t
     auto load = [&](const void* xp) {
 #pragma unroll
       for (int u = 0; u < Q; ++u)
-        rx[u] = QuadIO<TE>::load_raw(xp, min((uint32_t)(u * kBlock + threadIdx.x), nq - 1u));
+        rx[u] = QuadIO<TE>::load_raw(xp, W.clamp(u * kBlock + threadIdx.x));
     };
     {
       typename QuadIO<T0>::Raw r0[Q];
 #pragma unroll
-      for (int u = 0; u < Q; ++u) {
-        const uint32_t q = u * kBlock + threadIdx.x;
-        r0[u] = QuadIO<T0>::load_raw(t0p, min(q, nq - 1u));
-      }
+      for (int u = 0; u < Q; ++u) r0[u] = QuadIO<T0>::load_raw(t0p, W.clamp(u * kBlock + threadIdx.x));
       if (AHEAD) load(expert_at(0));
       normal_priority();
 #pragma unroll
@@ -125,12 +135,10 @@ __device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t
 #pragma unroll
     for (int u = 0; u < Q; ++u) {
       const uint32_t q = u * kBlock + threadIdx.x;
-      if (q < nq) QuadIO<TO>::store(outp, q, acc[u]);
+      if (W.has(q)) QuadIO<TO>::store(outp, q, acc[u]);
     }
   }
-  if ((len & 3u) && threadIdx.x == (nq & (kBlock - 1))) {
-    for (uint32_t i = nq * 4u; i < len; ++i) one(i);
-  }
+  for_edges(len, head, edge);
 }
 
 template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
@@ -140,8 +148,8 @@ __global__ __launch_bounds__(kBlock) void k_merge_one(TensorRec R, MergeArgs A, 
   const int64_t begin = (int64_t)blockIdx.x * tile;
   merge_tile<TE, T0, TO, Q, AHEAD>(
       advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)), R.elem_offset + (uint64_t)begin,
-      tile_len(R.n, begin, tile), R.tensor_id, (R.sflags & kVecMerge) != 0, nexp,
-      [&](int j) { return advance<TE>(A.x[j], begin); }, [&](int j) { return A.r[j]; });
+      tile_len(R.n, begin, tile), begin == 0 ? R.sflags >> kHeadShift : 0u, R.tensor_id, (R.sflags & kVecMerge) != 0,
+      nexp, [&](int j) { return advance<TE>(A.x[j], begin); }, [&](int j) { return A.r[j]; });
 }
 
 template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
@@ -159,8 +167,8 @@ __global__ __launch_bounds__(kBlock) void k_merge_multi(const TensorRec* __restr
   const size_t row = (size_t)ch.x * (size_t)nexp;
   merge_tile<TE, T0, TO, Q, AHEAD>(
       advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)), R.elem_offset + (uint64_t)begin,
-      tile_len(R.n, begin, tile), R.tensor_id, (R.sflags & kVecMerge) != 0, nexp,
-      [&](int j) { return advance<TE>(experts[row + j], begin); }, [&](int j) { return terms[row + j]; });
+      tile_len(R.n, begin, tile), begin == 0 ? R.sflags >> kHeadShift : 0u, R.tensor_id, (R.sflags & kVecMerge) != 0,
+      nexp, [&](int j) { return advance<TE>(experts[row + j], begin); }, [&](int j) { return terms[row + j]; });
 }
 
 // ---------------------------------------------------------------- launchers

@@ -41,35 +41,36 @@ __device__ __forceinline__ void adamw_tile(const Tile& T, float* m1p, float* m2p
     const float gv = ACC ? (kept ? __builtin_fmaf(c, gsim, acc) : acc) : (kept ? c * gsim : 0.0f);
     return A.grad_scale * gv;
   };
-  auto one = [&](uint32_t i) {
-    const uint64_t e = e0 + i;
-    bool kept = all_kept;
-    if (use_mask) kept = pick(group_words(e >> 2, tensor_id, cmask, K), (uint32_t)e & 3u) < thr;
-    const float g = grad(kept, QuadIO<TG>::load1(gs, i), ACC ? QuadIO<float>::load1(ga, i) : 0.0f);
-    float t = QuadIO<float>::load1(th, i), a = QuadIO<float>::load1(m1p, i), b = QuadIO<float>::load1(m2p, i);
-    adam_element(g, t, a, b, A);
-    QuadIO<float>::store1(th, i, t);
-    QuadIO<float>::store1(m1p, i, a);
-    QuadIO<float>::store1(m2p, i, b);
+  // the elements of quad q that are the tensor's, one at a time
+  auto edge = [&](uint32_t q) {
+    const uint32_t lo = max(4u * q, T.head), hi = min(4u * q + 4u, len);
+    if (lo >= hi) return;
+    Words w;
+    if (use_mask) w = group_words((e0 >> 2) + q, tensor_id, cmask, K);
+    for (uint32_t i = lo; i < hi; ++i) {
+      const bool kept = use_mask ? pick(w, i & 3u) < thr : all_kept;
+      const float g = grad(kept, QuadIO<TG>::load1(gs, i), ACC ? QuadIO<float>::load1(ga, i) : 0.0f);
+      float t = QuadIO<float>::load1(th, i), a = QuadIO<float>::load1(m1p, i), b = QuadIO<float>::load1(m2p, i);
+      adam_element(g, t, a, b, A);
+      QuadIO<float>::store1(th, i, t);
+      QuadIO<float>::store1(m1p, i, a);
+      QuadIO<float>::store1(m2p, i, b);
+    }
   };
 
   const uint32_t vec = ACC ? kVecAdamAcc : kVecAdam;
   if (!(T.sflags & vec) || groups_wrap(e0, Q * kBlock)) {
 #pragma unroll
-    for (int u = 0; u < Q; ++u) {
-      const uint32_t i0 = (u * kBlock + threadIdx.x) * 4u;
-      for (uint32_t i = i0; i < len && i < i0 + 4u; ++i) one(i);
-    }
+    for (int u = 0; u < Q; ++u) edge(u * kBlock + threadIdx.x);
     return;
   }
-  const uint32_t nq = len >> 2;
-  if (nq > 0) {
+  const WholeQuads W = whole_quads(len, T.head);
+  if (W.any()) {
     typename QuadIO<TG>::Raw rg[Q];
     typename QuadIO<float>::Raw racc[Q], rt[Q], r1[Q], r2[Q];
 #pragma unroll
     for (int u = 0; u < Q; ++u) {
-      const uint32_t q = u * kBlock + threadIdx.x;
-      const uint32_t qc = min(q, nq - 1u);
+      const uint32_t qc = W.clamp(u * kBlock + threadIdx.x);
       rg[u] = QuadIO<TG>::load_raw(gs, qc);
       if (ACC) racc[u] = QuadIO<float>::load_raw(ga, qc);
       rt[u] = QuadIO<float>::load_raw(th, qc);
@@ -93,7 +94,7 @@ __device__ __forceinline__ void adamw_tile(const Tile& T, float* m1p, float* m2p
 #pragma unroll
     for (int u = 0; u < Q; ++u) {
       const uint32_t q = u * kBlock + threadIdx.x;
-      if (q < nq) {
+      if (W.has(q)) {
         float gsim[4], acc[4] = {0.f, 0.f, 0.f, 0.f}, t[4], a[4], b[4];
         QuadIO<TG>::unpack(rg[u], gsim);
         if (ACC) QuadIO<float>::unpack(racc[u], acc);
@@ -108,9 +109,7 @@ __device__ __forceinline__ void adamw_tile(const Tile& T, float* m1p, float* m2p
       }
     }
   }
-  if ((len & 3u) && threadIdx.x == (nq & (kBlock - 1))) {
-    for (uint32_t i = nq * 4u; i < len; ++i) one(i);
-  }
+  for_edges(len, T.head, edge);
 }
 
 template <typename TG, bool ACC>
@@ -217,30 +216,31 @@ __device__ __forceinline__ float tile_sqnorm(const Tile& T, const ParamRec& P, u
     return ACC ? (kept ? __builtin_fmaf(c, gsim, acc) : acc) : (kept ? c * gsim : 0.0f);
   };
   float s = 0.0f;
-  auto one = [&](uint32_t i) {
-    const uint64_t e = e0 + i;
-    bool kept = all_kept;
-    if (use_mask) kept = pick(group_words(e >> 2, tensor_id, cmask, k0, k1), (uint32_t)e & 3u) < thr;
-    const float g = gval(kept, QuadIO<TG>::load1(gs, i), ACC ? QuadIO<float>::load1(ga, i) : 0.0f);
-    s = __builtin_fmaf(g, g, s);
+  // the elements of quad q that are the tensor's, one at a time
+  auto edge = [&](uint32_t q) {
+    const uint32_t lo = max(4u * q, T.head), hi = min(4u * q + 4u, len);
+    if (lo >= hi) return;
+    Words w;
+    if (use_mask) w = group_words((e0 >> 2) + q, tensor_id, cmask, k0, k1);
+    for (uint32_t i = lo; i < hi; ++i) {
+      const bool kept = use_mask ? pick(w, i & 3u) < thr : all_kept;
+      const float g = gval(kept, QuadIO<TG>::load1(gs, i), ACC ? QuadIO<float>::load1(ga, i) : 0.0f);
+      s = __builtin_fmaf(g, g, s);
+    }
   };
 
   if (!(T.sflags & kVecBwd) || groups_wrap(e0, kNormQuads * kBlock)) {
-#pragma unroll
-    for (int u = 0; u < kNormQuads; ++u) {
-      const uint32_t i0 = (u * kBlock + threadIdx.x) * 4u;
-      for (uint32_t i = i0; i < len && i < i0 + 4u; ++i) one(i);
-    }
+#pragma unroll 1
+    for (int u = 0; u < kNormQuads; ++u) edge(u * kBlock + threadIdx.x);
     return s;
   }
-  const uint32_t nq = len >> 2;
-  if (nq > 0) {
+  const WholeQuads W = whole_quads(len, T.head);
+  if (W.any()) {
     typename QuadIO<TG>::Raw rg[kNormQuads];
     typename QuadIO<float>::Raw ra[kNormQuads];
 #pragma unroll
     for (int u = 0; u < kNormQuads; ++u) {
-      const uint32_t q = u * kBlock + threadIdx.x;
-      const uint32_t qc = min(q, nq - 1u);
+      const uint32_t qc = W.clamp(u * kBlock + threadIdx.x);
       rg[u] = QuadIO<TG>::load_raw(gs, qc);
       if (ACC) ra[u] = QuadIO<float>::load_raw(ga, qc);
     }
@@ -261,7 +261,7 @@ __device__ __forceinline__ float tile_sqnorm(const Tile& T, const ParamRec& P, u
 #pragma unroll
     for (int u = 0; u < kNormQuads; ++u) {
       const uint32_t q = u * kBlock + threadIdx.x;
-      if (q < nq) {
+      if (W.has(q)) {
         float a[4], b[4] = {0.f, 0.f, 0.f, 0.f};
         QuadIO<TG>::unpack(rg[u], a);
         if (ACC) QuadIO<float>::unpack(ra[u], b);
@@ -274,9 +274,7 @@ __device__ __forceinline__ float tile_sqnorm(const Tile& T, const ParamRec& P, u
       }
     }
   }
-  if ((len & 3u) && threadIdx.x == (nq & (kBlock - 1))) {
-    for (uint32_t i = nq * 4u; i < len; ++i) one(i);
-  }
+  for_edges(len, T.head, edge);
   return s;
 }
 

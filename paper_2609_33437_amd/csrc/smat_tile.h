@@ -17,8 +17,9 @@ struct StorageBytes<Bf16> {
   static constexpr int value = 2;
 };
 
-// A tile: pointers at the tile's first element, its global index e0, its length, the tensor id
-// and the alignment flags.  Thread x of the block owns quads x + u * (block size) of the tile.
+// A tile: pointers at the tile's first element, its global index e0 (a multiple of 4), its length, the
+// tensor id and the static flags.  Thread x of the block owns quads x + u * (block size) of the tile.
+// The first `head` elements of a tensor's first tile are not the tensor's (see TensorRec::sflags).
 struct Tile {
   const float* theta;
   const void* theta0;
@@ -29,6 +30,7 @@ struct Tile {
   uint32_t len;
   uint32_t tensor_id;
   uint32_t sflags;
+  uint32_t head;
 };
 
 template <typename T>
@@ -44,7 +46,7 @@ template <typename T0, typename TO>
 __device__ __forceinline__ Tile tensor_tile(const TensorRec& R, int64_t begin, int64_t tile) {
   return Tile{R.theta + begin, advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)),
               R.grad_sim, R.grad_theta, R.elem_offset + (uint64_t)begin, tile_len(R.n, begin, tile), R.tensor_id,
-              R.sflags};
+              R.sflags, begin == 0 ? R.sflags >> kHeadShift : 0u};
 }
 
 // Record i of a per-tensor table, addressed with a 32-bit byte offset that the scalar unit forms in
@@ -74,7 +76,26 @@ __device__ __forceinline__ Tile list_tile(const TensorRec& R, uint32_t chunk, ui
               R.elem_offset + (uint64_t)begin,
               ti < whole ? (uint32_t)tile : (ti == whole ? tail : 0u),
               R.tensor_id,
-              R.sflags};
+              R.sflags,
+              ti == 0u ? R.sflags >> kHeadShift : 0u};
+}
+
+// The whole quads [first, end) of a tile, which move as vectors, and edge(q) for the partial ones: the
+// first quad of a tensor with a head, and the quad that holds a tensor's last 1-3 elements, each given
+// to the thread that owns it.
+struct WholeQuads {
+  uint32_t first, end;
+  __device__ __forceinline__ bool any() const { return first < end; }
+  __device__ __forceinline__ bool has(uint32_t q) const { return q >= first && q < end; }
+  __device__ __forceinline__ uint32_t clamp(uint32_t q) const { return max(min(q, end - 1u), first); }
+};
+__device__ __forceinline__ WholeQuads whole_quads(uint32_t len, uint32_t head) { return {head ? 1u : 0u, len >> 2}; }
+
+template <typename F>
+__device__ __forceinline__ void for_edges(uint32_t len, uint32_t head, F&& edge) {
+  const uint32_t nq = len >> 2;
+  if (head && threadIdx.x == 0) edge(0u);
+  if ((len & 3u) && (nq > 0 || !head) && threadIdx.x == (nq & (kBlock - 1))) edge(nq);
 }
 
 }  // namespace smat
