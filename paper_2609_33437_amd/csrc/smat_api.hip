@@ -100,6 +100,27 @@ uint32_t sim_flags(const float* theta, const void* theta0, int t0_dt, const void
   return smat::kVecSim | (whole ? smat::kSimWhole : 0u);
 }
 
+// Whether the arrays that an operation streams begin inside a line (records as the kernels read them).
+// The optimizer step's fp32 arrays decide for it: with g~ alone 64 bytes off, runs are 0.6 % slower.
+bool sim_off_line(const TensorRec& r) {
+  return smat::off_line(r.theta) || smat::off_line(r.theta0) || smat::off_line(r.out);
+}
+bool bwd_off_line(const TensorRec& r) { return smat::off_line(r.grad_sim) || smat::off_line(r.grad_theta); }
+bool adam_off_line(const TensorRec& r, const AdamRec& a) {
+  return smat::off_line(r.theta) || smat::off_line(a.exp_avg) || smat::off_line(a.exp_avg_sq);
+}
+
+// The block order of a list: runs where at least a quarter of its elements lie in tensors that begin
+// inside a line.  Linear order costs those 13-20 %, runs cost the others 2-7 %.
+struct OffLine {
+  uint64_t off = 0, all = 0;
+  void add(int64_t n, bool is_off) {
+    all += (uint64_t)n;
+    if (is_off) off += (uint64_t)n;
+  }
+  bool runs() const { return off * 4 >= all && off > 0; }
+};
+
 uint32_t bwd_flags(const void* grad_sim, int g_dt, const float* grad_theta) {
   return aligned(grad_sim, dtype_bytes(g_dt)) && aligned(grad_theta, 4) ? smat::kVecBwd : 0u;
 }
@@ -235,8 +256,8 @@ extern "C" smat_status smat_simulate(const float* theta, const void* theta0, sma
   rec.elem_offset = key.elem_offset;
   rec.tensor_id = key.tensor_id;
   rec.sflags = sim_flags(theta, theta0, theta0_dtype, out, out_dtype, key.elem_offset, n);
-  SMAT_HIP(smat::launch_simulate_one(smat::device_rec(rec, theta0_dtype, out_dtype, 0), prm, theta0_dtype, out_dtype,
-                                     key.seed, key.step, stream));
+  rec = smat::device_rec(rec, theta0_dtype, out_dtype, 0);
+  SMAT_HIP(smat::launch_simulate_one(rec, prm, theta0_dtype, out_dtype, key.seed, key.step, sim_off_line(rec), stream));
   return SMAT_OK;
 }
 
@@ -263,8 +284,8 @@ extern "C" smat_status smat_backward_accum(const void* grad_sim, smat_dtype grad
   rec.elem_offset = key.elem_offset;
   rec.tensor_id = key.tensor_id;
   rec.sflags = bwd_flags(grad_sim, grad_dtype, grad_theta);
-  SMAT_HIP(smat::launch_backward_one(smat::device_rec(rec, 0, 0, grad_dtype), prm, grad_dtype, lambda, key.seed, key.step,
-                                     stream));
+  rec = smat::device_rec(rec, 0, 0, grad_dtype);
+  SMAT_HIP(smat::launch_backward_one(rec, prm, grad_dtype, lambda, key.seed, key.step, bwd_off_line(rec), stream));
   return SMAT_OK;
 }
 
@@ -312,9 +333,10 @@ extern "C" smat_status smat_adamw_fused(const void* grad_sim, smat_dtype grad_dt
   rec.elem_offset = key.elem_offset;
   rec.tensor_id = key.tensor_id;
   rec.sflags = adam_flags(theta, exp_avg, exp_avg_sq, grad_sim, grad_dtype, grad_acc);
-  const AdamRec sr{exp_avg, exp_avg_sq};
-  SMAT_HIP(smat::launch_adamw_one(smat::device_rec(rec, 0, 0, grad_dtype), smat::device_adam(sr, rec), prm, A,
-                                  grad_dtype, grad_acc != nullptr, lambda, key.seed, key.step, grad_scale_dev, stream));
+  const AdamRec sr = smat::device_adam(AdamRec{exp_avg, exp_avg_sq}, rec);
+  rec = smat::device_rec(rec, 0, 0, grad_dtype);
+  SMAT_HIP(smat::launch_adamw_one(rec, sr, prm, A, grad_dtype, grad_acc != nullptr, lambda, key.seed, key.step,
+                                  grad_scale_dev, adam_off_line(rec, sr), stream));
   return SMAT_OK;
 }
 
@@ -323,6 +345,7 @@ struct smat_plan {
   int32_t count = 0;
   int t0_dt = 0, out_dt = 0, g_dt = 0;
   bool offload = false;
+  bool runs_sim = false, runs_bwd = false, runs_adam = false;  // block order of each operation (OffLine)
   bool has_gs = false, has_gt = false;  // gradient arrays (grad_sim, grad_theta) known for every tensor
   std::vector<smat_tensor_desc> descs;
   std::vector<TensorRec> recs;
@@ -428,10 +451,21 @@ smat_status check_plan_spans(const smat_plan* p, const std::vector<TensorRec>& r
   return check_spans(s.data(), s.size(), where);
 }
 
-// The list's records as the kernels read them, into a staging buffer.
-void device_recs(const smat_plan* p, const std::vector<TensorRec>& recs, char* staging) {
+// The list's records as the kernels read them, into a staging buffer, and the block order that the
+// operations on them take (`adam`: the bound moments, if any).
+void device_recs(smat_plan* p, const std::vector<TensorRec>& recs, const std::vector<AdamRec>* adam, char* staging) {
   TensorRec* out = reinterpret_cast<TensorRec*>(staging);
-  for (size_t i = 0; i < recs.size(); ++i) out[i] = smat::device_rec(recs[i], p->t0_dt, p->out_dt, p->g_dt);
+  OffLine sim, bwd, opt;
+  for (size_t i = 0; i < recs.size(); ++i) {
+    const TensorRec r = smat::device_rec(recs[i], p->t0_dt, p->out_dt, p->g_dt);
+    out[i] = r;
+    sim.add(r.n, sim_off_line(r));
+    bwd.add(r.n, bwd_off_line(r));
+    if (adam) opt.add(r.n, adam_off_line(r, smat::device_adam((*adam)[i], recs[i])));
+  }
+  p->runs_sim = sim.runs();
+  p->runs_bwd = bwd.runs();
+  p->runs_adam = opt.runs();
 }
 
 smat_status release(smat_plan* p) {
@@ -617,7 +651,7 @@ extern "C" smat_status smat_plan_bind_workspace(smat_plan* p, void* workspace, s
       SMAT_HIP(hipHostMalloc((void**)&s, (sizeof(ParamRec) + sizeof(ScaleRec)) * std::max(p->count, 1),
                              hipHostMallocDefault));
   std::memset(p->static_staging, 0, static_bytes);
-  device_recs(p, p->recs, p->static_staging + p->off_recs);
+  device_recs(p, p->recs, nullptr, p->static_staging + p->off_recs);
   std::memcpy(p->static_staging + p->off_chunks, p->chunks.data(), sizeof(uint2) * p->chunks.size());
   std::memcpy(p->static_staging + p->off_expert, p->expert_ptrs.data(), sizeof(void*) * p->count);
   std::memcpy(p->static_staging + p->off_sim, p->sim_ptrs.data(), sizeof(void*) * p->count);
@@ -713,7 +747,8 @@ extern "C" smat_status smat_simulate_multi(smat_plan* p, uint64_t seed, uint32_t
     SMAT_HIP(smat::launch_simulate_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                          reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
                                          reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
-                                         (uint32_t)p->chunks.size(), p->t0_dt, p->out_dt, seed, step, stream));
+                                         (uint32_t)p->chunks.size(), p->t0_dt, p->out_dt, seed, step, p->runs_sim,
+                                         stream));
   p->fresh = true;
   return SMAT_OK;
 }
@@ -733,7 +768,7 @@ extern "C" smat_status smat_backward_multi(smat_plan* p, uint64_t seed, uint32_t
                                          reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
                                          reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
                                          (uint32_t)p->chunks.size(), p->g_dt, accumulate != 0, lambda, seed, step,
-                                         stream));
+                                         p->runs_bwd, stream));
   return SMAT_OK;
 }
 
@@ -810,7 +845,7 @@ extern "C" smat_status smat_simulate_multi_dev(smat_plan* p, const smat_step_sta
                                              reinterpret_cast<const ScaleRec*>(p->ws + p->off_scales),
                                              reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
                                              (uint32_t)p->chunks.size(), p->t0_dt, p->out_dt,
-                                             reinterpret_cast<const StepState*>(state), stream));
+                                             reinterpret_cast<const StepState*>(state), p->runs_sim, stream));
   p->fresh = true;
   return SMAT_OK;
 }
@@ -830,7 +865,7 @@ extern "C" smat_status smat_backward_multi_dev(smat_plan* p, const smat_step_sta
                                              reinterpret_cast<const ScaleRec*>(p->ws + p->off_scales),
                                              reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
                                              (uint32_t)p->chunks.size(), p->g_dt, accumulate != 0, lambda,
-                                             reinterpret_cast<const StepState*>(state), stream));
+                                             reinterpret_cast<const StepState*>(state), p->runs_bwd, stream));
   return SMAT_OK;
 }
 
@@ -864,7 +899,7 @@ extern "C" smat_status smat_plan_bind_adam_state(smat_plan* p, const smat_adam_s
   } else {
     SMAT_HIP(hipEventSynchronize(p->ev_adam));  // the previous upload has left the staging buffer
   }
-  device_recs(p, recs, p->adam_staging);
+  device_recs(p, recs, &adam, p->adam_staging);
   AdamRec* staged = reinterpret_cast<AdamRec*>(p->adam_staging + rec_bytes);
   for (int32_t i = 0; i < p->count; ++i) staged[i] = smat::device_adam(adam[i], recs[i]);
   if (p->count > 0) {
@@ -919,7 +954,7 @@ extern "C" smat_status smat_plan_set_grads(smat_plan* p, const void* const* grad
   } else {
     SMAT_HIP(hipEventSynchronize(p->ev_adam));  // the previous table upload has left the staging buffer
   }
-  device_recs(p, recs, p->adam_staging);
+  device_recs(p, recs, p->adam_bound ? &p->adam : nullptr, p->adam_staging);
   if (p->count > 0)
     SMAT_HIP(hipMemcpyAsync(p->ws + p->off_recs, p->adam_staging, rec_bytes, hipMemcpyHostToDevice, stream));
   SMAT_HIP(hipEventRecord(p->ev_adam, stream));
@@ -974,7 +1009,7 @@ extern "C" smat_status smat_adamw_fused_multi(smat_plan* p, uint64_t seed, uint3
                                       reinterpret_cast<const AdamRec*>(p->ws + p->off_adam),
                                       reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
                                       reinterpret_cast<const uint2*>(p->ws + p->off_chunks), (uint32_t)p->chunks.size(),
-                                      A, p->g_dt, accumulate != 0, lambda, seed, step, grad_scale_dev, stream));
+                                      A, p->g_dt, accumulate != 0, lambda, seed, step, grad_scale_dev, p->runs_adam, stream));
   return SMAT_OK;
 }
 
@@ -1029,7 +1064,7 @@ extern "C" smat_status smat_adamw_fused_multi_dev(smat_plan* p, const smat_step_
                                         reinterpret_cast<const smat::AdamStepState*>(adam_state),
                                         reinterpret_cast<AdamConsts*>(p->ws + p->off_aconsts), p->g_dt,
                                         accumulate != 0, lambda, reinterpret_cast<const StepState*>(state),
-                                        grad_scale_dev, stream));
+                                        grad_scale_dev, p->runs_adam, stream));
   return SMAT_OK;
 }
 
@@ -1160,6 +1195,7 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
   uint2* chunks = reinterpret_cast<uint2*>(g_scratch_host + off_chunks);
   const size_t max_chunks = (kScratchBytes - off_chunks) / sizeof(uint2);
   size_t nchunks = 0, nspans = 0, nranges = 0;
+  OffLine lines;
   for (int32_t i = 0; i < count; ++i) {
     const smat_tensor_desc& d = descs[i];
     char where[80];
@@ -1182,6 +1218,7 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
     if (st != SMAT_OK) return st;
     r.sflags = sim_flags(d.theta, d.theta0, theta0_dtype, d.out, out_dtype, d.elem_offset, d.n);
     r = smat::device_rec(r, theta0_dtype, out_dtype, 0);
+    lines.add(r.n, sim_off_line(r));
     const size_t n = (size_t)d.n;
     g_scratch_spans[nspans++] = Span{reinterpret_cast<uintptr_t>(d.theta), reinterpret_cast<uintptr_t>(d.theta) + n * 4,
                                      false, i, "theta"};
@@ -1219,7 +1256,7 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
   SMAT_HIP(smat::launch_simulate_multi(reinterpret_cast<const TensorRec*>(base),
                                        reinterpret_cast<const ParamRec*>(base + off_prms),
                                        reinterpret_cast<const uint2*>(base + off_chunks), (uint32_t)nchunks,
-                                       theta0_dtype, out_dtype, seed, step, stream));
+                                       theta0_dtype, out_dtype, seed, step, lines.runs(), stream));
   return SMAT_OK;
 }
 
@@ -1277,6 +1314,13 @@ uint32_t merge_flags(const void* const* experts, int nexp, int e_dt, const void*
   return ok ? smat::kVecMerge : 0u;
 }
 
+// Whether the arrays of a merge begin inside a line (as the kernels read them).
+bool merge_off_line(const TensorRec& r, const void* const* experts, int nexp) {
+  bool off = smat::off_line(r.theta0) || smat::off_line(r.out);
+  for (int j = 0; j < nexp; ++j) off = off || smat::off_line(experts[j]);
+  return off;
+}
+
 smat_status check_merge_ptrs(const void* const* experts, int nexp, int e_dt, const void* theta0, int t0_dt,
                              const void* out, int out_dt, int64_t n, const char* where) {
   if (!theta0 || !out) return fail(SMAT_ERR_INVALID, "%s: null theta0 or out with n > 0", where);
@@ -1331,14 +1375,16 @@ extern "C" smat_status smat_merge(const void* const* experts, int32_t n_experts,
   rec.sflags = merge_flags(experts, n_experts, expert_dtype, theta0, theta0_dtype, out, out_dtype);
   for (int32_t j = 0; j < n_experts; ++j)
     A.x[j] = smat::back_ptr(experts[j], smat::group_head(elem_offset), dtype_bytes(expert_dtype));
-  SMAT_HIP(smat::launch_merge_one(smat::device_rec(rec, theta0_dtype, out_dtype, 0), A, n_experts, expert_dtype,
-                                  theta0_dtype, out_dtype, plain, stream));
+  rec = smat::device_rec(rec, theta0_dtype, out_dtype, 0);
+  SMAT_HIP(smat::launch_merge_one(rec, A, n_experts, expert_dtype, theta0_dtype, out_dtype, plain,
+                                  merge_off_line(rec, A.x, n_experts), stream));
   return SMAT_OK;
 }
 
 struct smat_merge_plan {
   int32_t count = 0, nexp = 0;
   int e_dt = 0, t0_dt = 0, out_dt = 0;
+  bool runs = false;  // block order (OffLine)
   std::vector<TensorRec> recs;
   std::vector<uint2> chunks;
   std::vector<const void*> experts;  // [count][nexp]
@@ -1426,6 +1472,7 @@ extern "C" smat_status smat_merge_plan_create(const smat_merge_desc* descs, int3
   p->recs.resize(count);
   p->experts.assign(experts, experts + (size_t)count * n_experts);
   p->chunks.reserve(nchunks);
+  OffLine lines;
   for (int32_t i = 0; i < count; ++i) {
     const smat_merge_desc& d = descs[i];
     TensorRec& r = p->recs[i];
@@ -1442,9 +1489,11 @@ extern "C" smat_status smat_merge_plan_create(const smat_merge_desc* descs, int3
       const void*& x = p->experts[(size_t)i * n_experts + j];
       x = smat::back_ptr(x, smat::group_head(d.elem_offset), dtype_bytes(expert_dtype));
     }
+    if (d.n > 0) lines.add(r.n, merge_off_line(r, p->experts.data() + (size_t)i * n_experts, n_experts));
     const uint32_t nc = (uint32_t)chunk_count(d.elem_offset, d.n);
     for (uint32_t c = 0; c < nc; ++c) p->chunks.push_back(make_uint2((uint32_t)i, c));
   }
+  p->runs = lines.runs();
   const size_t cells = (size_t)count * n_experts;
   size_t off = 0;
   p->off_recs = off;
@@ -1526,7 +1575,7 @@ extern "C" smat_status smat_merge_multi(smat_merge_plan* p, const smat_merge_ter
                                       reinterpret_cast<const void* const*>(p->ws + p->off_experts),
                                       reinterpret_cast<const MergeRec*>(p->ws + p->off_terms),
                                       reinterpret_cast<const uint2*>(p->ws + p->off_chunks), (uint32_t)p->chunks.size(),
-                                      p->nexp, p->e_dt, p->t0_dt, p->out_dt, plain, stream));
+                                      p->nexp, p->e_dt, p->t0_dt, p->out_dt, plain, p->runs, stream));
   return SMAT_OK;
 }
 

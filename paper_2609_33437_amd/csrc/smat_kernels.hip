@@ -234,25 +234,26 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
 }
 
 // ---------------------------------------------------------------- kernels
-template <typename T0, typename TO>
+template <typename T0, typename TO, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_simulate_one(TensorRec R, ParamRec P, PhiloxKeys K, uint32_t step) {
   raise_priority();
   constexpr int64_t tile = tile_elems(kSimQuads);
-  simulate_tile<T0, TO>(tensor_tile<T0, TO>(R, (int64_t)blockIdx.x * tile, tile), P, K, step);
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(kSimQuads)) * tile;
+  simulate_tile<T0, TO>(tensor_tile<T0, TO>(R, begin, tile), P, K, step);
 }
 
-template <typename TG>
+template <typename TG, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_backward_one(TensorRec R, ParamRec P, PhiloxKeys K, uint32_t step,
                                                          float lambda) {
   constexpr int64_t tile = tile_elems(kBwdQuads);
-  const int64_t begin = (int64_t)blockIdx.x * tile;
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(kBwdQuads)) * tile;
   Tile T = tensor_tile<float, float>(R, begin, tile);
   T.grad_sim = advance<TG>(R.grad_sim, begin);
   T.grad_theta = R.grad_theta + begin;
   backward_tile<TG, kBwdQuads, true>(T, P, K, step, lambda);
 }
 
-template <typename T0, typename TO>
+template <typename T0, typename TO, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_simulate_multi(const TensorRec* __restrict__ recs,
                                                            const ParamRec* __restrict__ prms,
                                                            const uint2* __restrict__ chunks, PhiloxKeys K,
@@ -260,21 +261,23 @@ __global__ __launch_bounds__(kBlock) void k_simulate_multi(const TensorRec* __re
   raise_priority();
   constexpr int64_t tile = tile_elems(kSimQuads);
   constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
-  const Tile T = list_tile<T0, TO, float>(rec_at(recs, ch.x), ch.y, blockIdx.x % tpc, tile);
+  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
+  const uint2 ch = chunks[block / tpc];
+  const Tile T = list_tile<T0, TO, float>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
   if (T.len == 0) return;  // unused tile of a tensor's last chunk
   simulate_tile<T0, TO>(T, rec_at(prms, ch.x), K, step);
 }
 
-template <typename TG, bool ACC>
+template <typename TG, bool ACC, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_backward_multi(const TensorRec* __restrict__ recs,
                                                            const ParamRec* __restrict__ prms,
                                                            const uint2* __restrict__ chunks, PhiloxKeys K,
                                                            uint32_t step, float lambda) {
   constexpr int64_t tile = tile_elems(kBwdQuads);
   constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
-  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, blockIdx.x % tpc, tile);
+  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
+  const uint2 ch = chunks[block / tpc];
+  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
   if (T.len == 0) return;
   backward_tile<TG, kBwdQuads, ACC>(T, rec_at(prms, ch.x), K, step, lambda);
 }
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_multi(const TensorRec* __re
 // The same list kernels with the step's seed, step and scale read from device memory, so that a
 // captured graph replays them with whatever the caller last wrote there.  Each block forms its
 // tensor's coefficient from that scale and the tensor's ScaleRec exactly as the host forms it.
-template <typename T0, typename TO>
+template <typename T0, typename TO, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* __restrict__ recs,
                                                                const ParamRec* __restrict__ prms,
                                                                const ScaleRec* __restrict__ scales,
@@ -291,8 +294,9 @@ __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* 
   raise_priority();
   constexpr int64_t tile = tile_elems(kSimQuads);
   constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
-  const Tile T = list_tile<T0, TO, float>(rec_at(recs, ch.x), ch.y, blockIdx.x % tpc, tile);
+  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
+  const uint2 ch = chunks[block / tpc];
+  const Tile T = list_tile<T0, TO, float>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
   if (T.len == 0) return;
   const StepState S = *state;
   ParamRec P = rec_at(prms, ch.x);
@@ -300,7 +304,7 @@ __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* 
   simulate_tile<T0, TO>(T, P, philox_keys(S.seed), S.step);
 }
 
-template <typename TG, bool ACC>
+template <typename TG, bool ACC, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_backward_multi_dev(const TensorRec* __restrict__ recs,
                                                                const ParamRec* __restrict__ prms,
                                                                const ScaleRec* __restrict__ scales,
@@ -308,8 +312,9 @@ __global__ __launch_bounds__(kBlock) void k_backward_multi_dev(const TensorRec* 
                                                                const StepState* __restrict__ state, float lambda) {
   constexpr int64_t tile = tile_elems(kBwdQuads);
   constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
-  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, blockIdx.x % tpc, tile);
+  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
+  const uint2 ch = chunks[block / tpc];
+  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
   if (T.len == 0) return;
   const StepState S = *state;
   ParamRec P = rec_at(prms, ch.x);
@@ -359,107 +364,110 @@ __global__ __launch_bounds__(kDebugBlock) void k_debug_draws(uint64_t seed, uint
 static inline uint32_t blocks_for(int64_t n, int64_t per_block) { return (uint32_t)((n + per_block - 1) / per_block); }
 
 hipError_t launch_simulate_one(const TensorRec& rec, const ParamRec& prm, int theta0_dtype, int out_dtype,
-                               uint64_t seed, uint32_t step, hipStream_t stream) {
+                               uint64_t seed, uint32_t step, bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
   constexpr int64_t tile = tile_elems(kSimQuads);
   return for_pieces((uint64_t)rec.n, (uint64_t)max_grid_blocks(kBlock) * tile, [&](uint64_t off, uint64_t len) {
     const TensorRec r = rec_piece(rec, off, len, theta0_dtype, out_dtype, 0);
     const dim3 grid(blocks_for((int64_t)len, tile)), block(kBlock);
-    if (theta0_dtype == 1 && out_dtype == 1)
-      k_simulate_one<Bf16, Bf16><<<grid, block, 0, stream>>>(r, prm, K, step);
-    else if (theta0_dtype == 1 && out_dtype == 0)
-      k_simulate_one<Bf16, float><<<grid, block, 0, stream>>>(r, prm, K, step);
-    else if (theta0_dtype == 0 && out_dtype == 1)
-      k_simulate_one<float, Bf16><<<grid, block, 0, stream>>>(r, prm, K, step);
-    else
-      k_simulate_one<float, float><<<grid, block, 0, stream>>>(r, prm, K, step);
+    with_type(theta0_dtype, [&](auto t0) {
+      with_type(out_dtype, [&](auto to) {
+        with_flag(runs, [&](auto rn) {
+          k_simulate_one<typename decltype(t0)::type, typename decltype(to)::type, decltype(rn)::value>
+              <<<grid, block, 0, stream>>>(r, prm, K, step);
+        });
+      });
+    });
   });
 }
 
 hipError_t launch_backward_one(const TensorRec& rec, const ParamRec& prm, int grad_dtype, float lambda,
-                               uint64_t seed, uint32_t step, hipStream_t stream) {
+                               uint64_t seed, uint32_t step, bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
   constexpr int64_t tile = tile_elems(kBwdQuads);
   return for_pieces((uint64_t)rec.n, (uint64_t)max_grid_blocks(kBlock) * tile, [&](uint64_t off, uint64_t len) {
     const TensorRec r = rec_piece(rec, off, len, 0, 0, grad_dtype);
     const dim3 grid(blocks_for((int64_t)len, tile)), block(kBlock);
-    if (grad_dtype == 1)
-      k_backward_one<Bf16><<<grid, block, 0, stream>>>(r, prm, K, step, lambda);
-    else
-      k_backward_one<float><<<grid, block, 0, stream>>>(r, prm, K, step, lambda);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(runs, [&](auto rn) {
+        k_backward_one<typename decltype(tg)::type, decltype(rn)::value>
+            <<<grid, block, 0, stream>>>(r, prm, K, step, lambda);
+      });
+    });
   });
 }
 
 hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
-                                 int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, hipStream_t stream) {
+                                 int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, bool runs,
+                                 hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
   constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (theta0_dtype == 1 && out_dtype == 1)
-      k_simulate_multi<Bf16, Bf16><<<grid, block, 0, stream>>>(recs, prms, ch, K, step);
-    else if (theta0_dtype == 1 && out_dtype == 0)
-      k_simulate_multi<Bf16, float><<<grid, block, 0, stream>>>(recs, prms, ch, K, step);
-    else if (theta0_dtype == 0 && out_dtype == 1)
-      k_simulate_multi<float, Bf16><<<grid, block, 0, stream>>>(recs, prms, ch, K, step);
-    else
-      k_simulate_multi<float, float><<<grid, block, 0, stream>>>(recs, prms, ch, K, step);
+    with_type(theta0_dtype, [&](auto t0) {
+      with_type(out_dtype, [&](auto to) {
+        with_flag(runs, [&](auto rn) {
+          k_simulate_multi<typename decltype(t0)::type, typename decltype(to)::type, decltype(rn)::value>
+              <<<grid, block, 0, stream>>>(recs, prms, ch, K, step);
+        });
+      });
+    });
   });
 }
 
 hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
                                  int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
-                                 hipStream_t stream) {
+                                 bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
   constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (grad_dtype == 1 && accumulate)
-      k_backward_multi<Bf16, true><<<grid, block, 0, stream>>>(recs, prms, ch, K, step, lambda);
-    else if (grad_dtype == 1)
-      k_backward_multi<Bf16, false><<<grid, block, 0, stream>>>(recs, prms, ch, K, step, lambda);
-    else if (accumulate)
-      k_backward_multi<float, true><<<grid, block, 0, stream>>>(recs, prms, ch, K, step, lambda);
-    else
-      k_backward_multi<float, false><<<grid, block, 0, stream>>>(recs, prms, ch, K, step, lambda);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(accumulate, [&](auto acc) {
+        with_flag(runs, [&](auto rn) {
+          k_backward_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
+              <<<grid, block, 0, stream>>>(recs, prms, ch, K, step, lambda);
+        });
+      });
+    });
   });
 }
 
 hipError_t launch_simulate_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
                                      const uint2* chunks, uint32_t nchunks, int theta0_dtype, int out_dtype,
-                                     const StepState* state, hipStream_t stream) {
+                                     const StepState* state, bool runs, hipStream_t stream) {
   constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (theta0_dtype == 1 && out_dtype == 1)
-      k_simulate_multi_dev<Bf16, Bf16><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state);
-    else if (theta0_dtype == 1 && out_dtype == 0)
-      k_simulate_multi_dev<Bf16, float><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state);
-    else if (theta0_dtype == 0 && out_dtype == 1)
-      k_simulate_multi_dev<float, Bf16><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state);
-    else
-      k_simulate_multi_dev<float, float><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state);
+    with_type(theta0_dtype, [&](auto t0) {
+      with_type(out_dtype, [&](auto to) {
+        with_flag(runs, [&](auto rn) {
+          k_simulate_multi_dev<typename decltype(t0)::type, typename decltype(to)::type, decltype(rn)::value>
+              <<<grid, block, 0, stream>>>(recs, prms, scales, ch, state);
+        });
+      });
+    });
   });
 }
 
 hipError_t launch_backward_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
                                      const uint2* chunks, uint32_t nchunks, int grad_dtype, bool accumulate,
-                                     float lambda, const StepState* state, hipStream_t stream) {
+                                     float lambda, const StepState* state, bool runs, hipStream_t stream) {
   constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (grad_dtype == 1 && accumulate)
-      k_backward_multi_dev<Bf16, true><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state, lambda);
-    else if (grad_dtype == 1)
-      k_backward_multi_dev<Bf16, false><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state, lambda);
-    else if (accumulate)
-      k_backward_multi_dev<float, true><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state, lambda);
-    else
-      k_backward_multi_dev<float, false><<<grid, block, 0, stream>>>(recs, prms, scales, ch, state, lambda);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(accumulate, [&](auto acc) {
+        with_flag(runs, [&](auto rn) {
+          k_backward_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
+              <<<grid, block, 0, stream>>>(recs, prms, scales, ch, state, lambda);
+        });
+      });
+    });
   });
 }
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "smat_device.h"
 
 namespace smat {
@@ -46,6 +48,30 @@ hipError_t for_pieces(uint64_t total, uint64_t per, F&& fn) {
   }
   return hipGetLastError();
 }
+
+// fn called with the storage type of a dtype code (0 = fp32, 1 = bf16) or with a flag, as a type.
+template <typename T>
+struct TypeTag {
+  using type = T;
+};
+template <typename F>
+void with_type(int dtype, F&& fn) {
+  if (dtype == 1)
+    fn(TypeTag<Bf16>());
+  else
+    fn(TypeTag<float>());
+}
+template <typename F>
+void with_flag(bool flag, F&& fn) {
+  if (flag)
+    fn(std::true_type());
+  else
+    fn(std::false_type());
+}
+
+// Whether an array's tiles begin inside a 128-byte line (its address as device_rec gives it; tiles are
+// multiples of 512 bytes).
+inline bool off_line(const void* p) { return reinterpret_cast<uintptr_t>(p) % 128 != 0; }
 
 // Storage bytes of a dtype code (0 = fp32, 1 = bf16).
 inline size_t storage_bytes(int dtype) { return dtype == 1 ? 2 : 4; }
@@ -102,32 +128,33 @@ inline TensorRec rec_piece(const TensorRec& R, uint64_t off, uint64_t len, int t
   return r;
 }
 
-// Storage codes match smat_dtype: 0 = fp32, 1 = bf16.
+// Storage codes match smat_dtype: 0 = fp32, 1 = bf16.  `runs`: the block order of tiles that begin inside
+// a line (block_order in smat_tile.h).
 hipError_t launch_simulate_one(const TensorRec& rec, const ParamRec& prm, int theta0_dtype, int out_dtype,
-                               uint64_t seed, uint32_t step, hipStream_t stream);
+                               uint64_t seed, uint32_t step, bool runs, hipStream_t stream);
 hipError_t launch_backward_one(const TensorRec& rec, const ParamRec& prm, int grad_dtype, float lambda,
-                               uint64_t seed, uint32_t step, hipStream_t stream);
+                               uint64_t seed, uint32_t step, bool runs, hipStream_t stream);
 hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
-                                 int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, hipStream_t stream);
+                                 int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, bool runs, hipStream_t stream);
 hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
                                  int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
-                                 hipStream_t stream);
+                                 bool runs, hipStream_t stream);
 // Graph-capturable forms: seed, step and scale read from `state` in device memory, each tensor's
 // coefficient formed from the scale and its ScaleRec.
 hipError_t launch_simulate_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
                                      const uint2* chunks, uint32_t nchunks, int theta0_dtype, int out_dtype,
-                                     const StepState* state, hipStream_t stream);
+                                     const StepState* state, bool runs, hipStream_t stream);
 hipError_t launch_backward_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
                                      const uint2* chunks, uint32_t nchunks, int grad_dtype, bool accumulate,
-                                     float lambda, const StepState* state, hipStream_t stream);
+                                     float lambda, const StepState* state, bool runs, hipStream_t stream);
 // step += increment and the scale of that step, in place (one thread).
 hipError_t launch_step_advance(StepState* state, uint32_t increment, float alpha_min, hipStream_t stream);
 hipError_t launch_adamw_one(const TensorRec& rec, const AdamRec& st, const ParamRec& prm, const AdamConsts& A,
                             int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
-                            const float* dev_scale, hipStream_t stream);
+                            const float* dev_scale, bool runs, hipStream_t stream);
 hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, const ParamRec* prms, const uint2* chunks,
                               uint32_t nchunks, const AdamConsts& A, int grad_dtype, bool accumulate, float lambda,
-                              uint64_t seed, uint32_t step, const float* dev_scale, hipStream_t stream);
+                              uint64_t seed, uint32_t step, const float* dev_scale, bool runs, hipStream_t stream);
 // Squared norm of the simulated step's expert gradient over the list: one fp32 partial per
 // one-wave block of kNormQuads quads per thread (kNormPartialsPerChunk per chunk), their fp64 block
 // sums (at most kNormSums doubles), then sumsq and/or the clipping factor.
@@ -149,7 +176,7 @@ hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, 
                                   const ScaleRec* scales, const uint2* chunks, uint32_t nchunks, const AdamHyper& h,
                                   const AdamStepState* adam_state, AdamConsts* consts, int grad_dtype,
                                   bool accumulate, float lambda, const StepState* state, const float* dev_scale,
-                                  hipStream_t stream);
+                                  bool runs, hipStream_t stream);
 // ---------------------------------------------------------------- N-expert merge
 // One expert's term on one tensor: its mask key (seed, step), threshold and coefficient
 // t = gamma/keep (rescaled) or gamma, and kFlagMask / kFlagDropAll, plus the ten Philox round keys of
@@ -173,10 +200,10 @@ struct MergeArgs {
 };
 // `plain`: no term draws a mask or leaves its expert out.
 hipError_t launch_merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, int expert_dtype, int theta0_dtype,
-                            int out_dtype, bool plain, hipStream_t stream);
+                            int out_dtype, bool plain, bool runs, hipStream_t stream);
 hipError_t launch_merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
                               const uint2* chunks, uint32_t nchunks, int nexp, int expert_dtype, int theta0_dtype,
-                              int out_dtype, bool plain, hipStream_t stream);
+                              int out_dtype, bool plain, bool runs, hipStream_t stream);
 
 // Plain streaming copy of n16 16-byte vectors (the measured HBM reference).
 constexpr int kCopyVecs = 1;  // 16-byte vectors per thread of the reference copy

@@ -141,18 +141,18 @@ __device__ __forceinline__ void merge_tile(const void* t0p, void* outp, uint64_t
   for_edges(len, head, edge);
 }
 
-template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_merge_one(TensorRec R, MergeArgs A, int nexp) {
   raise_priority();
   constexpr int64_t tile = tile_elems(Q);
-  const int64_t begin = (int64_t)blockIdx.x * tile;
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(Q)) * tile;
   merge_tile<TE, T0, TO, Q, AHEAD>(
       advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)), R.elem_offset + (uint64_t)begin,
       tile_len(R.n, begin, tile), begin == 0 ? R.sflags >> kHeadShift : 0u, R.tensor_id, (R.sflags & kVecMerge) != 0,
       nexp, [&](int j) { return advance<TE>(A.x[j], begin); }, [&](int j) { return A.r[j]; });
 }
 
-template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_merge_multi(const TensorRec* __restrict__ recs,
                                                         const void* const* __restrict__ experts,
                                                         const MergeRec* __restrict__ terms,
@@ -160,9 +160,10 @@ __global__ __launch_bounds__(kBlock) void k_merge_multi(const TensorRec* __restr
   raise_priority();
   constexpr int64_t tile = tile_elems(Q);
   constexpr uint32_t tpc = tiles_per_chunk(Q);
-  const uint2 ch = chunks[blockIdx.x / tpc];
+  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
+  const uint2 ch = chunks[block / tpc];
   const TensorRec R = recs[ch.x];
-  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(blockIdx.x % tpc) * tile;
+  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(block % tpc) * tile;
   if (begin >= R.n) return;  // unused tile of a tensor's last chunk
   const size_t row = (size_t)ch.x * (size_t)nexp;
   merge_tile<TE, T0, TO, Q, AHEAD>(
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_multi(const TensorRec* __restr
 // ranges of a list's chunk table).
 template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
 static hipError_t merge_one_as(const TensorRec& rec, const MergeArgs& args, int nexp, uint32_t lds,
-                               hipStream_t stream) {
+                               bool runs, hipStream_t stream) {
   constexpr int64_t tile = tile_elems(Q);
   constexpr int e_dt = std::is_same<TE, Bf16>::value ? 1 : 0, t0_dt = std::is_same<T0, Bf16>::value ? 1 : 0,
                 o_dt = std::is_same<TO, Bf16>::value ? 1 : 0;
@@ -185,17 +186,23 @@ static hipError_t merge_one_as(const TensorRec& rec, const MergeArgs& args, int 
     MergeArgs a = args;
     for (int j = 0; j < nexp; ++j) a.x[j] = step_ptr(args.x[j], off, storage_bytes(e_dt));
     const dim3 grid((uint32_t)((len + tile - 1) / tile)), block(kBlock);
-    k_merge_one<TE, T0, TO, Q, AHEAD><<<grid, block, lds, stream>>>(r, a, nexp);
+    with_flag(runs, [&](auto rn) {
+      k_merge_one<TE, T0, TO, Q, AHEAD, decltype(rn)::value><<<grid, block, lds, stream>>>(r, a, nexp);
+    });
   });
 }
 
 template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
 static hipError_t merge_multi_as(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
-                                 const uint2* chunks, uint32_t nchunks, int nexp, uint32_t lds, hipStream_t stream) {
+                                 const uint2* chunks, uint32_t nchunks, int nexp, uint32_t lds, bool runs,
+                                 hipStream_t stream) {
   constexpr uint32_t tpc = tiles_per_chunk(Q);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    k_merge_multi<TE, T0, TO, Q, AHEAD><<<grid, block, lds, stream>>>(recs, experts, terms, chunks + first, nexp);
+    with_flag(runs, [&](auto rn) {
+      k_merge_multi<TE, T0, TO, Q, AHEAD, decltype(rn)::value>
+          <<<grid, block, lds, stream>>>(recs, experts, terms, chunks + first, nexp);
+    });
   });
 }
 
@@ -229,19 +236,21 @@ constexpr uint64_t merge_bytes(uint64_t elems, int nexp) {
 }
 
 template <typename TE, typename T0, typename TO>
-static hipError_t merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, bool plain, hipStream_t stream) {
+static hipError_t merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, bool plain, bool runs,
+                            hipStream_t stream) {
   const uint64_t bytes = merge_bytes<TE, T0, TO>((uint64_t)rec.n, nexp);
   return merge_form<TE>(nexp, plain, bytes, [&](auto q, auto ahead, uint32_t lds) {
-    return merge_one_as<TE, T0, TO, q(), ahead()>(rec, args, nexp, lds, stream);
+    return merge_one_as<TE, T0, TO, q(), ahead()>(rec, args, nexp, lds, runs, stream);
   });
 }
 
 template <typename TE, typename T0, typename TO>
 static hipError_t merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
-                              const uint2* chunks, uint32_t nchunks, int nexp, bool plain, hipStream_t stream) {
+                              const uint2* chunks, uint32_t nchunks, int nexp, bool plain, bool runs,
+                              hipStream_t stream) {
   const uint64_t bytes = merge_bytes<TE, T0, TO>((uint64_t)nchunks * kChunk, nexp);
   return merge_form<TE>(nexp, plain, bytes, [&](auto q, auto ahead, uint32_t lds) {
-    return merge_multi_as<TE, T0, TO, q(), ahead()>(recs, experts, terms, chunks, nchunks, nexp, lds, stream);
+    return merge_multi_as<TE, T0, TO, q(), ahead()>(recs, experts, terms, chunks, nchunks, nexp, lds, runs, stream);
   });
 }
 
@@ -259,14 +268,14 @@ static hipError_t merge_multi(const TensorRec* recs, const void* const* experts,
   }
 
 hipError_t launch_merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, int expert_dtype, int theta0_dtype,
-                            int out_dtype, bool plain, hipStream_t stream) {
-  SMAT_MERGE_DISPATCH(merge_one, rec, args, nexp, plain, stream)
+                            int out_dtype, bool plain, bool runs, hipStream_t stream) {
+  SMAT_MERGE_DISPATCH(merge_one, rec, args, nexp, plain, runs, stream)
 }
 
 hipError_t launch_merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
                               const uint2* chunks, uint32_t nchunks, int nexp, int expert_dtype, int theta0_dtype,
-                              int out_dtype, bool plain, hipStream_t stream) {
-  SMAT_MERGE_DISPATCH(merge_multi, recs, experts, terms, chunks, nchunks, nexp, plain, stream)
+                              int out_dtype, bool plain, bool runs, hipStream_t stream) {
+  SMAT_MERGE_DISPATCH(merge_multi, recs, experts, terms, chunks, nchunks, nexp, plain, runs, stream)
 }
 
 #undef SMAT_MERGE_DISPATCH

@@ -112,19 +112,19 @@ __device__ __forceinline__ void adamw_tile(const Tile& T, float* m1p, float* m2p
   for_edges(len, T.head, edge);
 }
 
-template <typename TG, bool ACC>
+template <typename TG, bool ACC, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_adamw_one(TensorRec R, AdamRec S, ParamRec P, AdamConsts A, PhiloxKeys K,
                                                       uint32_t step, float lambda, const float* dev_scale) {
   constexpr int64_t tile = tile_elems(kAdamQuads);
   if (dev_scale) A.grad_scale *= *dev_scale;
-  const int64_t begin = (int64_t)blockIdx.x * tile;
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(kAdamQuads)) * tile;
   Tile T = tensor_tile<float, float>(R, begin, tile);
   T.grad_sim = advance<TG>(R.grad_sim, begin);
   T.grad_theta = R.grad_theta ? R.grad_theta + begin : nullptr;
   adamw_tile<TG, kAdamQuads, ACC>(T, S.exp_avg + begin, S.exp_avg_sq + begin, P, A, K, step, lambda);
 }
 
-template <typename TG, bool ACC>
+template <typename TG, bool ACC, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_adamw_multi(const TensorRec* __restrict__ recs,
                                                         const AdamRec* __restrict__ states,
                                                         const ParamRec* __restrict__ prms,
@@ -133,10 +133,11 @@ __global__ __launch_bounds__(kBlock) void k_adamw_multi(const TensorRec* __restr
   constexpr int64_t tile = tile_elems(kAdamQuads);
   if (dev_scale) A.grad_scale *= *dev_scale;
   constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
+  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
+  const uint2 ch = chunks[block / tpc];
   const TensorRec R = recs[ch.x];
-  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(blockIdx.x % tpc) * tile;
-  const Tile T = list_tile<float, float, TG>(R, ch.y, blockIdx.x % tpc, tile);
+  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(block % tpc) * tile;
+  const Tile T = list_tile<float, float, TG>(R, ch.y, block % tpc, tile);
   if (T.len == 0) return;
   const AdamRec S = states[ch.x];
   adamw_tile<TG, kAdamQuads, ACC>(T, S.exp_avg + begin, S.exp_avg_sq + begin, rec_at(prms, ch.x), A, K, step, lambda);
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(kBlock) void k_adamw_multi(const TensorRec* __restr
 // The same list kernel with seed, step and scale read from device memory (each tensor's coefficient
 // formed as the simulate forms it) and the step's constants from `Ad`, which k_adam_consts writes
 // from the device-side learning rate and step count: a captured graph replays it for every step.
-template <typename TG, bool ACC>
+template <typename TG, bool ACC, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_adamw_multi_dev(const TensorRec* __restrict__ recs,
                                                             const AdamRec* __restrict__ states,
                                                             const ParamRec* __restrict__ prms,
@@ -156,10 +157,11 @@ __global__ __launch_bounds__(kBlock) void k_adamw_multi_dev(const TensorRec* __r
                                                             const float* dev_scale) {
   constexpr int64_t tile = tile_elems(kAdamQuads);
   constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
+  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
+  const uint2 ch = chunks[block / tpc];
   const TensorRec R = recs[ch.x];
-  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(blockIdx.x % tpc) * tile;
-  const Tile T = list_tile<float, float, TG>(R, ch.y, blockIdx.x % tpc, tile);
+  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(block % tpc) * tile;
+  const Tile T = list_tile<float, float, TG>(R, ch.y, block % tpc, tile);
   if (T.len == 0) return;
   AdamConsts A = *Ad;
   if (dev_scale) A.grad_scale *= *dev_scale;
@@ -375,7 +377,7 @@ static inline uint32_t adamw_lds(int grad_dtype, bool accumulate, uint64_t elems
 
 hipError_t launch_adamw_one(const TensorRec& rec, const AdamRec& st, const ParamRec& prm, const AdamConsts& A,
                             int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
-                            const float* dev_scale, hipStream_t stream) {
+                            const float* dev_scale, bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
   const uint32_t lds = adamw_lds(grad_dtype, accumulate, (uint64_t)rec.n);
   constexpr int64_t tile = tile_elems(kAdamQuads);
@@ -383,34 +385,34 @@ hipError_t launch_adamw_one(const TensorRec& rec, const AdamRec& st, const Param
     const TensorRec r = rec_piece(rec, off, len, 0, 0, grad_dtype);
     const AdamRec m{step_ptr(st.exp_avg, off, 4), step_ptr(st.exp_avg_sq, off, 4)};
     const dim3 grid(blocks_for((int64_t)len, tile)), block(kBlock);
-    if (grad_dtype == 1 && accumulate)
-      k_adamw_one<Bf16, true><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
-    else if (grad_dtype == 1)
-      k_adamw_one<Bf16, false><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
-    else if (accumulate)
-      k_adamw_one<float, true><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
-    else
-      k_adamw_one<float, false><<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(accumulate, [&](auto acc) {
+        with_flag(runs, [&](auto rn) {
+          k_adamw_one<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
+              <<<grid, block, lds, stream>>>(r, m, prm, A, K, step, lambda, dev_scale);
+        });
+      });
+    });
   });
 }
 
 hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, const ParamRec* prms, const uint2* chunks,
                               uint32_t nchunks, const AdamConsts& A, int grad_dtype, bool accumulate, float lambda,
-                              uint64_t seed, uint32_t step, const float* dev_scale, hipStream_t stream) {
+                              uint64_t seed, uint32_t step, const float* dev_scale, bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
   const uint32_t lds = adamw_lds(grad_dtype, accumulate, (uint64_t)nchunks * kChunk);
   constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (grad_dtype == 1 && accumulate)
-      k_adamw_multi<Bf16, true><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
-    else if (grad_dtype == 1)
-      k_adamw_multi<Bf16, false><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
-    else if (accumulate)
-      k_adamw_multi<float, true><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
-    else
-      k_adamw_multi<float, false><<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(accumulate, [&](auto acc) {
+        with_flag(runs, [&](auto rn) {
+          k_adamw_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
+              <<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
+        });
+      });
+    });
   });
 }
 
@@ -474,7 +476,7 @@ hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, 
                                   const ScaleRec* scales, const uint2* chunks, uint32_t nchunks, const AdamHyper& h,
                                   const AdamStepState* adam_state, AdamConsts* consts, int grad_dtype,
                                   bool accumulate, float lambda, const StepState* state, const float* dev_scale,
-                                  hipStream_t stream) {
+                                  bool runs, hipStream_t stream) {
   k_adam_consts<<<dim3(1), dim3(64), 0, stream>>>(adam_state, h, consts);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -483,18 +485,14 @@ hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, 
   return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
     const uint2* ch = chunks + first;
     const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (grad_dtype == 1 && accumulate)
-      k_adamw_multi_dev<Bf16, true><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state, lambda,
-                                                                dev_scale);
-    else if (grad_dtype == 1)
-      k_adamw_multi_dev<Bf16, false><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state,
-                                                                 lambda, dev_scale);
-    else if (accumulate)
-      k_adamw_multi_dev<float, true><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state,
-                                                                 lambda, dev_scale);
-    else
-      k_adamw_multi_dev<float, false><<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state,
-                                                                  lambda, dev_scale);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(accumulate, [&](auto acc) {
+        with_flag(runs, [&](auto rn) {
+          k_adamw_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
+              <<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state, lambda, dev_scale);
+        });
+      });
+    });
   });
 }
 

@@ -16,10 +16,10 @@ SEED, STEP, LAM = 0xABCDEF0123, 5, 0.75
 HP = dict(lr=1e-3, beta1=0.9, beta2=0.99, eps=1e-8, weight_decay=0.1, step=3)
 
 
-def shards():
-    """(place in SIZES, first element in its tensor, elements, element shift of the buffers)"""
+def shards(sizes=SIZES, shifts=(0, 1, 2, 3)):
+    """(place in sizes, first element in its tensor, elements, element shift of the buffers)"""
     return [(i, 4 * i + (i * 7 + s) % 4 + (256 if i % 3 == 2 else 0), n, s)
-            for s in range(4) for i, n in enumerate(SIZES)]
+            for s in shifts for i, n in enumerate(sizes)]
 
 
 def random(n, g, scale, dtype=torch.float32):
@@ -30,9 +30,9 @@ class Packed:
     """Whole tensors, and the shards cut from them packed into one buffer per array: each shard begins
     `shift` elements past where the last one ended, and NaN fills what is between them."""
 
-    def __init__(self, arrays, seed):
+    def __init__(self, arrays, seed, cuts=None):
         g = torch.Generator(DEV).manual_seed(seed)
-        self.cuts = shards()
+        self.cuts = cuts or shards()
         self.whole = {k: [random(o + n + 3, g, scale, dt) for _, o, n, _ in self.cuts]
                       for k, (scale, dt) in arrays.items()}
         size = sum(n + s for _, _, n, s in self.cuts) + 8
@@ -130,10 +130,11 @@ def test_merge(e_dt, out_dt, keep):
     x.check("out")
 
 
-def test_single_tensor_calls():
+@pytest.mark.parametrize("cuts", [None, shards((131071, 131072, 300001), (1, 3))])  # one run and several of each XCD
+def test_single_tensor_calls(cuts):
     x = Packed(dict(theta=(0.02, torch.float32), theta0=(0.02, torch.bfloat16), out=(1.0, torch.bfloat16),
                     gs=(1e-2, torch.bfloat16), gt=(1e-3, torch.float32), m1=(1e-3, torch.float32),
-                    m2=(0.0, torch.float32), e=(0.02, torch.bfloat16), merged=(1.0, torch.bfloat16)), 31)
+                    m2=(0.0, torch.float32), e=(0.02, torch.bfloat16), merged=(1.0, torch.bfloat16)), 31, cuts)
     for side, offs in ((x.whole, [0] * len(x.cuts)), (x.part, x.offs)):
         for i, p in enumerate(params(len(x.cuts), 0)):
             a = {k: v[i] for k, v in side.items()}
