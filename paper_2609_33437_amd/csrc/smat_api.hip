@@ -1,12 +1,14 @@
 // C ABI of libsmat: argument checks, per-tensor constants, tensor-list plans, the storage
 // switch and the offload prefetch.  Kernels live in smat_kernels.hip.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -149,6 +151,69 @@ smat_status check_simulate_ptrs(const float* theta, const void* theta0, int t0_d
 }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Pinned staging of a plan's per-step tables: up to eight slots, used in turn, that upload kernels read
+// in place.  Each kernel writes its slot's sequence number to the slot's words once it has read it, so
+// reuse waits for exactly the upload that used the slot, whatever streams the calls name, and the
+// stream carries no event for it.  Eight slots let the host issue that many steps ahead of the GPU;
+// tables over 1 MB get two.
+struct Staging {
+  static constexpr uint32_t kMaxSlots = 8;
+  char* mem = nullptr;
+  size_t slot_bytes = 0;
+  uint32_t slots = 0, next = 0;
+  uint32_t seq[kMaxSlots] = {}, blocks[kMaxSlots] = {};
+
+  hipError_t init(size_t bytes) {
+    if (mem) return hipSuccess;
+    slot_bytes = align256(std::max<size_t>(bytes, 256));
+    slots = slot_bytes <= (size_t(1) << 20) ? kMaxSlots : 2;
+    const size_t words = slots * smat::kUploadBlocks * sizeof(uint32_t);
+    char* p = nullptr;
+    const hipError_t e = hipHostMalloc((void**)&p, slots * slot_bytes + words, hipHostMallocPortable | hipHostMallocMapped);
+    if (e != hipSuccess) return e;
+    std::memset(p + slots * slot_bytes, 0, words);
+    mem = p;
+    return hipSuccess;
+  }
+  char* data() const { return mem + next * slot_bytes; }
+  uint32_t* words(uint32_t slot) const {
+    return reinterpret_cast<uint32_t*>(mem + slots * slot_bytes) + slot * smat::kUploadBlocks;
+  }
+  bool read(uint32_t slot) const {
+    for (uint32_t b = 0; b < blocks[slot]; ++b)
+      if (__atomic_load_n(words(slot) + b, __ATOMIC_ACQUIRE) != seq[slot]) return false;
+    return true;
+  }
+  // Wait until the slot's last upload has read it.  A wait of seconds asks the runtime, which reports a
+  // device that will not finish.
+  hipError_t wait(uint32_t slot) const {
+    using clock = std::chrono::steady_clock;
+    auto until = clock::now() + std::chrono::seconds(2);
+    for (uint32_t k = 1; !read(slot); ++k) {
+      if (k % 1024) continue;
+      std::this_thread::yield();
+      if (clock::now() < until) continue;
+      if (const hipError_t e = hipDeviceSynchronize(); e != hipSuccess) return e;
+      until = clock::now() + std::chrono::seconds(2);
+    }
+    return hipSuccess;
+  }
+  // The next slot, free to be written: fill data(), launch its last upload with signal(), then sent().
+  hipError_t take() const { return wait(next); }
+  smat::UploadSignal signal() const { return {words(next), seq[next] + 1}; }
+  void sent(uint32_t used_blocks) {
+    ++seq[next];
+    blocks[next] = used_blocks;
+    next = (next + 1) % slots;
+  }
+  void release() {
+    if (!mem) return;
+    for (uint32_t k = 0; k < slots; ++k) (void)wait(k);
+    (void)hipHostFree(mem);
+    mem = nullptr;
+  }
+};
 
 // Calls that upload host tables through pinned staging (reused by the next call) and wait on their
 // own events cannot be recorded into a graph: a replay would copy whatever the staging holds then.
@@ -360,15 +425,11 @@ struct smat_plan {
   size_t off_partials = 0, off_sums = 0, off_aconsts = 0;
   char* ws = nullptr;
 
-  // pinned staging for the asynchronous uploads: the static tables once, the params (with their
-  // scale records) every step through two alternating slots, so a new upload only waits for the one
-  // before the last
+  // pinned staging of the static tables (uploaded once), the params with their scale records, and the
+  // tensor records with the optimizer state table
   char* static_staging = nullptr;
-  char* params_staging[2] = {nullptr, nullptr};
   hipEvent_t ev_static = nullptr;
-  hipEvent_t ev_params[2] = {nullptr, nullptr};
-  bool params_pending[2] = {false, false};
-  int params_slot = 0;
+  Staging params_staging, recs_staging;
   bool params_set = false;
   // the records the workspace holds since the last upload: set_params copies only the span from the
   // first record that changed to the last one, or nothing
@@ -381,8 +442,6 @@ struct smat_plan {
   // fused optimizer step: per-tensor moment pointers, uploaded with the tensor records' flags
   size_t off_adam = 0;
   std::vector<AdamRec> adam;
-  char* adam_staging = nullptr;
-  hipEvent_t ev_adam = nullptr;
   bool adam_bound = false;
 
   // offload mode: theta0 prefetch from pinned host memory on a copy stream
@@ -470,13 +529,12 @@ void device_recs(smat_plan* p, const std::vector<TensorRec>& recs, const std::ve
 
 smat_status release(smat_plan* p) {
   // wait for the plan's own work that still reads its pinned staging or owns its events
-  for (hipEvent_t e : {p->ev_static, p->ev_params[0], p->ev_params[1], p->ev_prefetch, p->ev_adam})
+  for (hipEvent_t e : {p->ev_static, p->ev_prefetch})
     if (e) (void)hipEventSynchronize(e);
   if (p->static_staging) (void)hipHostFree(p->static_staging);
-  if (p->adam_staging) (void)hipHostFree(p->adam_staging);
-  for (char* s : p->params_staging)
-    if (s) (void)hipHostFree(s);
-  for (hipEvent_t e : {p->ev_static, p->ev_params[0], p->ev_params[1], p->ev_release, p->ev_prefetch, p->ev_adam})
+  p->params_staging.release();
+  p->recs_staging.release();
+  for (hipEvent_t e : {p->ev_static, p->ev_release, p->ev_prefetch})
     if (e) (void)hipEventDestroy(e);
   if (p->copy_stream) (void)hipStreamDestroy(p->copy_stream);
   delete p;
@@ -646,18 +704,13 @@ extern "C" smat_status smat_plan_bind_workspace(smat_plan* p, void* workspace, s
   // each resource is created once: a call that failed part-way can be retried without leaking
   if (!p->static_staging)
     SMAT_HIP(hipHostMalloc((void**)&p->static_staging, std::max<size_t>(static_bytes, 256), hipHostMallocDefault));
-  for (char*& s : p->params_staging)
-    if (!s)
-      SMAT_HIP(hipHostMalloc((void**)&s, (sizeof(ParamRec) + sizeof(ScaleRec)) * std::max(p->count, 1),
-                             hipHostMallocDefault));
+  SMAT_HIP(p->params_staging.init((sizeof(ParamRec) + sizeof(ScaleRec)) * p->count));
   std::memset(p->static_staging, 0, static_bytes);
   device_recs(p, p->recs, nullptr, p->static_staging + p->off_recs);
   std::memcpy(p->static_staging + p->off_chunks, p->chunks.data(), sizeof(uint2) * p->chunks.size());
   std::memcpy(p->static_staging + p->off_expert, p->expert_ptrs.data(), sizeof(void*) * p->count);
   std::memcpy(p->static_staging + p->off_sim, p->sim_ptrs.data(), sizeof(void*) * p->count);
   if (!p->ev_static) SMAT_HIP(hipEventCreateWithFlags(&p->ev_static, hipEventDisableTiming));
-  for (hipEvent_t& e : p->ev_params)
-    if (!e) SMAT_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   if (p->offload) {
     if (!p->copy_stream) SMAT_HIP(hipStreamCreateWithFlags(&p->copy_stream, hipStreamNonBlocking));
     if (!p->ev_release) SMAT_HIP(hipEventCreateWithFlags(&p->ev_release, hipEventDisableTiming));
@@ -710,19 +763,16 @@ extern "C" smat_status smat_plan_set_params(smat_plan* p, const smat_op_params* 
       }
   }
   if (first < last) {
-    const int slot = p->params_slot;
-    if (p->params_pending[slot]) SMAT_HIP(hipEventSynchronize(p->ev_params[slot]));  // slot still being read
+    Staging& st = p->params_staging;
+    SMAT_HIP(st.take());
     // params and scale records are adjacent in the workspace: one upload carries the changed span
-    std::memcpy(p->params_staging[slot], recs.data(), prm_bytes);
-    std::memcpy(p->params_staging[slot] + prm_bytes, scales.data(), sizeof(ScaleRec) * p->count);
+    std::memcpy(st.data(), recs.data(), prm_bytes);
+    std::memcpy(st.data() + prm_bytes, scales.data(), sizeof(ScaleRec) * p->count);
     static_assert(sizeof(ParamRec) == sizeof(ScaleRec), "one record size indexes both arrays");
     const size_t lo = first * sizeof(ParamRec), hi = last * sizeof(ParamRec);
     p->params_set = false;  // until the upload is enqueued: a failed one leaves the plan without params
-    SMAT_HIP(hipMemcpyAsync(p->ws + p->off_params + lo, p->params_staging[slot] + lo, hi - lo,
-                            hipMemcpyHostToDevice, stream));
-    SMAT_HIP(hipEventRecord(p->ev_params[slot], stream));
-    p->params_pending[slot] = true;
-    p->params_slot = slot ^ 1;
+    SMAT_HIP(smat::launch_upload(st.data() + lo, p->ws + p->off_params + lo, hi - lo, st.signal(), stream));
+    st.sent(smat::upload_blocks((hi - lo) / 8));
     p->dev_params = recs;
     p->dev_scales = scales;
   }
@@ -893,20 +943,17 @@ extern "C" smat_status smat_plan_bind_adam_state(smat_plan* p, const smat_adam_s
   }
   if (smat_status st = check_plan_spans(p, recs, &adam, "smat_plan_bind_adam_state"); st != SMAT_OK) return st;
   const size_t rec_bytes = sizeof(TensorRec) * p->count, adam_bytes = sizeof(AdamRec) * p->count;
-  if (!p->adam_staging) {
-    SMAT_HIP(hipHostMalloc((void**)&p->adam_staging, std::max<size_t>(rec_bytes + adam_bytes, 256), hipHostMallocDefault));
-    SMAT_HIP(hipEventCreateWithFlags(&p->ev_adam, hipEventDisableTiming));
-  } else {
-    SMAT_HIP(hipEventSynchronize(p->ev_adam));  // the previous upload has left the staging buffer
-  }
-  device_recs(p, recs, &adam, p->adam_staging);
-  AdamRec* staged = reinterpret_cast<AdamRec*>(p->adam_staging + rec_bytes);
+  Staging& stage = p->recs_staging;
+  SMAT_HIP(stage.init(rec_bytes + adam_bytes));
+  SMAT_HIP(stage.take());
+  device_recs(p, recs, &adam, stage.data());
+  AdamRec* staged = reinterpret_cast<AdamRec*>(stage.data() + rec_bytes);
   for (int32_t i = 0; i < p->count; ++i) staged[i] = smat::device_adam(adam[i], recs[i]);
   if (p->count > 0) {
-    SMAT_HIP(hipMemcpyAsync(p->ws + p->off_recs, p->adam_staging, rec_bytes, hipMemcpyHostToDevice, stream));
-    SMAT_HIP(hipMemcpyAsync(p->ws + p->off_adam, p->adam_staging + rec_bytes, adam_bytes, hipMemcpyHostToDevice, stream));
+    SMAT_HIP(smat::launch_upload(stage.data(), p->ws + p->off_recs, rec_bytes, {}, stream));
+    SMAT_HIP(smat::launch_upload(stage.data() + rec_bytes, p->ws + p->off_adam, adam_bytes, stage.signal(), stream));
+    stage.sent(smat::upload_blocks(adam_bytes / 8));
   }
-  SMAT_HIP(hipEventRecord(p->ev_adam, stream));
   p->recs = recs;
   p->adam = adam;
   p->adam_bound = true;
@@ -948,16 +995,14 @@ extern "C" smat_status smat_plan_set_grads(smat_plan* p, const void* const* grad
       st != SMAT_OK)
     return st;
   const size_t rec_bytes = sizeof(TensorRec) * p->count, adam_bytes = sizeof(AdamRec) * p->count;
-  if (!p->adam_staging) {
-    SMAT_HIP(hipHostMalloc((void**)&p->adam_staging, std::max<size_t>(rec_bytes + adam_bytes, 256), hipHostMallocDefault));
-    SMAT_HIP(hipEventCreateWithFlags(&p->ev_adam, hipEventDisableTiming));
-  } else {
-    SMAT_HIP(hipEventSynchronize(p->ev_adam));  // the previous table upload has left the staging buffer
+  Staging& stage = p->recs_staging;
+  SMAT_HIP(stage.init(rec_bytes + adam_bytes));
+  SMAT_HIP(stage.take());
+  device_recs(p, recs, p->adam_bound ? &p->adam : nullptr, stage.data());
+  if (p->count > 0) {
+    SMAT_HIP(smat::launch_upload(stage.data(), p->ws + p->off_recs, rec_bytes, stage.signal(), stream));
+    stage.sent(smat::upload_blocks(rec_bytes / 8));
   }
-  device_recs(p, recs, p->adam_bound ? &p->adam : nullptr, p->adam_staging);
-  if (p->count > 0)
-    SMAT_HIP(hipMemcpyAsync(p->ws + p->off_recs, p->adam_staging, rec_bytes, hipMemcpyHostToDevice, stream));
-  SMAT_HIP(hipEventRecord(p->ev_adam, stream));
   for (int32_t i = 0; i < p->count; ++i) {
     p->descs[i].grad_sim = recs[i].grad_sim;
     p->descs[i].grad_theta = recs[i].grad_theta;
@@ -1278,22 +1323,18 @@ namespace {
 
 using smat::MergeArgs;
 using smat::MergeRec;
+using smat::MergeTerm;
 
 // One expert's term on one tensor (Eq. merged-state): weight gamma on the task vector, DARE keep
 // probability with its rescale, and the expert's mask key.
-smat_status make_merge(const smat_merge_term& m, MergeRec* out, const char* where) {
+smat_status make_merge(const smat_merge_term& m, MergeTerm* out, const char* where) {
   if (!std::isfinite(m.gamma)) return fail(SMAT_ERR_INVALID, "%s: gamma must be finite", where);
   if (!std::isfinite(m.keep) || m.keep < 0.f || m.keep > 1.f)
     return fail(SMAT_ERR_INVALID, "%s: keep must lie in [0, 1] (got %g)", where, (double)m.keep);
   if (m.step >= kMaxStep) return fail(SMAT_ERR_INVALID, "%s: step must be < 2^30", where);
-  MergeRec r{};
+  MergeTerm r{};
   r.seed = m.seed;
   r.step = m.step;
-  uint32_t a = (uint32_t)m.seed, b = (uint32_t)(m.seed >> 32);
-  for (int k = 0; k < 10; ++k, a += smat::kPhiloxW0, b += smat::kPhiloxW1) {
-    r.rk0[k] = a;
-    r.rk1[k] = b;
-  }
   if (m.keep >= 1.f) {
     r.t = m.gamma;
   } else if (m.keep <= 0.f) {
@@ -1355,8 +1396,10 @@ extern "C" smat_status smat_merge(const void* const* experts, int32_t n_experts,
   for (int32_t j = 0; j < n_experts; ++j) {
     char where[64];
     std::snprintf(where, sizeof(where), "smat_merge: expert %d", j);
-    smat_status st = make_merge(terms[j], &A.r[j], where);
+    MergeTerm term;
+    smat_status st = make_merge(terms[j], &term, where);
     if (st != SMAT_OK) return st;
+    A.r[j] = smat::merge_rec(term);
     plain = plain && A.r[j].flags == 0;
     A.x[j] = experts[j];
   }
@@ -1392,23 +1435,19 @@ struct smat_merge_plan {
   size_t off_recs = 0, off_chunks = 0, off_experts = 0, off_terms = 0, ws_bytes = 0;
   char* ws = nullptr;
   char* static_staging = nullptr;
-  MergeRec* terms_staging[2] = {nullptr, nullptr};
   hipEvent_t ev_static = nullptr;
-  hipEvent_t ev_terms[2] = {nullptr, nullptr};
-  bool terms_pending[2] = {false, false};
-  int slot = 0;
+  Staging terms_staging;
 };
 
 namespace {
 
 smat_status release_merge(smat_merge_plan* p) {
-  for (hipEvent_t e : {p->ev_static, p->ev_terms[0], p->ev_terms[1]})
-    if (e) (void)hipEventSynchronize(e);
+  if (p->ev_static) {
+    (void)hipEventSynchronize(p->ev_static);
+    (void)hipEventDestroy(p->ev_static);
+  }
   if (p->static_staging) (void)hipHostFree(p->static_staging);
-  for (MergeRec* s : p->terms_staging)
-    if (s) (void)hipHostFree(s);
-  for (hipEvent_t e : {p->ev_static, p->ev_terms[0], p->ev_terms[1]})
-    if (e) (void)hipEventDestroy(e);
+  p->terms_staging.release();
   delete p;
   return SMAT_OK;
 }
@@ -1529,15 +1568,12 @@ extern "C" smat_status smat_merge_plan_bind_workspace(smat_merge_plan* p, void* 
   // each resource is created once: a call that failed part-way can be retried without leaking
   if (!p->static_staging)
     SMAT_HIP(hipHostMalloc((void**)&p->static_staging, std::max<size_t>(static_bytes, 256), hipHostMallocDefault));
-  for (MergeRec*& s : p->terms_staging)
-    if (!s) SMAT_HIP(hipHostMalloc((void**)&s, sizeof(MergeRec) * std::max<size_t>(cells, 1), hipHostMallocDefault));
+  SMAT_HIP(p->terms_staging.init(sizeof(MergeTerm) * cells));
   std::memset(p->static_staging, 0, static_bytes);
   std::memcpy(p->static_staging + p->off_recs, p->recs.data(), sizeof(TensorRec) * p->count);
   std::memcpy(p->static_staging + p->off_chunks, p->chunks.data(), sizeof(uint2) * p->chunks.size());
   std::memcpy(p->static_staging + p->off_experts, p->experts.data(), sizeof(void*) * cells);
   if (!p->ev_static) SMAT_HIP(hipEventCreateWithFlags(&p->ev_static, hipEventDisableTiming));
-  for (hipEvent_t& e : p->ev_terms)
-    if (!e) SMAT_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   if (static_bytes > 0)
     SMAT_HIP(hipMemcpyAsync(workspace, p->static_staging, static_bytes, hipMemcpyHostToDevice, stream));
   SMAT_HIP(hipEventRecord(p->ev_static, stream));
@@ -1551,7 +1587,7 @@ extern "C" smat_status smat_merge_multi(smat_merge_plan* p, const smat_merge_ter
   if (cells > 0 && !terms) return fail(SMAT_ERR_INVALID, "smat_merge_multi: null terms");
   if (!p->ws) return fail(SMAT_ERR_STATE, "smat_merge_multi: no workspace bound");
   if (smat_status st = refuse_capture(stream, "smat_merge_multi"); st != SMAT_OK) return st;
-  std::vector<MergeRec> recs(cells);
+  std::vector<MergeTerm> recs(cells);
   bool plain = true;  // no expert draws a mask or is left out
   for (size_t c = 0; c < cells; ++c) {
     if (make_merge(terms[c], &recs[c], "") != SMAT_OK) {  // the message names the cell, formed only on failure
@@ -1561,15 +1597,14 @@ extern "C" smat_status smat_merge_multi(smat_merge_plan* p, const smat_merge_ter
     }
     plain = plain && recs[c].flags == 0;
   }
-  const int slot = p->slot;
-  if (p->terms_pending[slot]) SMAT_HIP(hipEventSynchronize(p->ev_terms[slot]));  // slot still being read
-  std::memcpy(p->terms_staging[slot], recs.data(), sizeof(MergeRec) * cells);
-  if (cells > 0)
-    SMAT_HIP(hipMemcpyAsync(p->ws + p->off_terms, p->terms_staging[slot], sizeof(MergeRec) * cells,
-                            hipMemcpyHostToDevice, stream));
-  SMAT_HIP(hipEventRecord(p->ev_terms[slot], stream));
-  p->terms_pending[slot] = true;
-  p->slot = slot ^ 1;
+  if (cells > 0) {
+    Staging& st = p->terms_staging;
+    SMAT_HIP(st.take());
+    std::memcpy(st.data(), recs.data(), sizeof(MergeTerm) * cells);
+    SMAT_HIP(smat::launch_upload_terms(reinterpret_cast<const MergeTerm*>(st.data()),
+                                       reinterpret_cast<MergeRec*>(p->ws + p->off_terms), cells, st.signal(), stream));
+    st.sent(smat::upload_blocks(cells));
+  }
   if (!p->chunks.empty())
     SMAT_HIP(smat::launch_merge_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                       reinterpret_cast<const void* const*>(p->ws + p->off_experts),

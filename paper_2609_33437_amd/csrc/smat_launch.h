@@ -177,10 +177,26 @@ hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, 
                                   const AdamStepState* adam_state, AdamConsts* consts, int grad_dtype,
                                   bool accumulate, float lambda, const StepState* state, const float* dev_scale,
                                   bool runs, hipStream_t stream);
+// ---------------------------------------------------------------- table uploads
+// What an upload kernel writes once it has read its staging: block b stores seq to done[b] (pinned host
+// memory; null: nothing).
+struct UploadSignal {
+  uint32_t* done;
+  uint32_t seq;
+};
+// Blocks of an upload of n items (16 blocks of 256 threads saturate the host link with 8-byte loads).
+constexpr uint32_t kUploadBlocks = 16;
+inline uint32_t upload_blocks(uint64_t n) {
+  return (uint32_t)(n >= kUploadBlocks * 256u ? kUploadBlocks : n ? (n + 255) / 256 : 1);
+}
+// Per-step tables from pinned host memory (`staged`, device-accessible) into a workspace; bytes is a
+// multiple of 8.
+hipError_t launch_upload(const void* staged, void* dst, size_t bytes, UploadSignal sig, hipStream_t stream);
+
 // ---------------------------------------------------------------- N-expert merge
 // One expert's term on one tensor: its mask key (seed, step), threshold and coefficient
 // t = gamma/keep (rescaled) or gamma, and kFlagMask / kFlagDropAll, plus the ten Philox round keys of
-// the seed, formed on the host so that no wave adds them up again for every expert.
+// the seed, formed once per term so that no wave adds them up again for every expert.
 struct alignas(8) MergeRec {
   uint64_t seed;
   uint32_t step;
@@ -191,6 +207,28 @@ struct alignas(8) MergeRec {
   uint32_t rk1[10];
 };
 static_assert(sizeof(MergeRec) == 104, "MergeRec layout");
+// A term without its round keys: what the host hands to launch_upload_terms.
+struct alignas(8) MergeTerm {
+  uint64_t seed;
+  uint32_t step;
+  uint32_t thr;
+  float t;
+  uint32_t flags;
+};
+static_assert(sizeof(MergeTerm) == 24, "MergeTerm layout");
+__host__ __device__ inline MergeRec merge_rec(const MergeTerm& m) {
+  const PhiloxKeys K = philox_keys(m.seed);
+  MergeRec r{m.seed, m.step, m.thr, m.t, m.flags, {}, {}};
+#pragma unroll
+  for (int k = 0; k < 10; ++k) {
+    r.rk0[k] = K.k0[k];
+    r.rk1[k] = K.k1[k];
+  }
+  return r;
+}
+// dst[i] = merge_rec(staged[i]) for `cells` terms in pinned host memory.
+hipError_t launch_upload_terms(const MergeTerm* staged, MergeRec* dst, uint64_t cells, UploadSignal sig,
+                               hipStream_t stream);
 constexpr int kMaxExperts = 16;
 constexpr uint32_t kVecMerge = 16u;  // TensorRec::sflags: theta0, out and every expert aligned to their elements
 // Arguments of the one-tensor merge, passed by value (no device tables).
