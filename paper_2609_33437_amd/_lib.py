@@ -101,7 +101,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "smat_plan_create": [POINTER(smat_tensor_desc), c_int32, c_int32, c_int32, c_int32, c_int32, POINTER(P)],
         "smat_plan_workspace_bytes": [P, POINTER(c_size_t)],
         "smat_plan_bind_workspace": [P, P, c_size_t, P],
-        "smat_plan_set_params": [P, POINTER(smat_op_params), P],
+        "smat_plan_set_params": [P, P, P],
         "smat_simulate_multi": [P, c_uint64, c_uint32, P],
         "smat_backward_accum_multi": [P, c_uint64, c_uint32, c_float, P],
         "smat_switch_storage": [P, c_int32, P],
@@ -159,34 +159,48 @@ def _check(status: int) -> None:
 
 
 # ------------------------------------------------------------------ marshalling helpers
+# A call's marshalling takes as long as a small kernel runs, so the helpers stay on torch's cheapest
+# accessors: pointers and stream handles travel as plain integers (ctypes converts them by argtypes),
+# and the current stream is read without building a torch.cuda.Stream.
+_TORCH = None
+_DTYPE_CODES: dict = {}
+
+
 def _torch():
-    import torch
-    return torch
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _DTYPE_CODES.update({torch.float32: SMAT_F32, torch.bfloat16: SMAT_BF16})
+        _TORCH = torch
+    return _TORCH
 
 
 def dtype_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return SMAT_F32
-    if t.dtype == torch.bfloat16:
-        return SMAT_BF16
-    raise SmatError(SMAT_ERR_DTYPE, f"unsupported tensor dtype {t.dtype}")
+    if _TORCH is None:
+        _torch()
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise SmatError(SMAT_ERR_DTYPE, f"unsupported tensor dtype {t.dtype}")
+    return code
 
 
-def _stream_handle(stream) -> c_void_p:
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return c_void_p(s.cuda_stream)
+def _stream_handle(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _TORCH or _torch()
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
-def _dev_ptr(t, what: str):
+def _dev_ptr(t, what: str) -> Optional[int]:
     if t is None:
         return None
     if not t.is_cuda:
         raise SmatError(SMAT_ERR_INVALID, f"{what} must be a GPU tensor")
     if not t.is_contiguous():
         raise SmatError(SMAT_ERR_INVALID, f"{what} must be contiguous")
-    return c_void_p(t.data_ptr()) if t.numel() else None
+    return t.data_ptr() if t.numel() else None
 
 
 def _scalar_ptr(t, what: str, dtype: str):
@@ -440,8 +454,8 @@ class Plan:
         if isinstance(params, np.ndarray):
             if params.dtype != OP_PARAMS_DTYPE:
                 raise SmatError(SMAT_ERR_INVALID, "a parameter array must have OP_PARAMS_DTYPE records")
-            arr = np.ascontiguousarray(params)
-            ptr = arr.ctypes.data_as(POINTER(smat_op_params)) if self.count else None
+            arr = params if params.flags.c_contiguous else np.ascontiguousarray(params)
+            ptr = arr.ctypes.data if self.count else None
         else:
             ptr = (smat_op_params * max(self.count, 1))(*[op_params(p) for p in params])
         _check(lib().smat_plan_set_params(self._plan, ptr, _stream_handle(stream)))
@@ -661,11 +675,13 @@ class MergePlan:
             if len(terms) != self.count or any(len(r) != self.nexp for r in terms):
                 raise SmatError(SMAT_ERR_INVALID, "one row of terms per tensor, one term per expert")
             flat = [merge_term(t) for row in terms for t in row]
+            arr = (smat_merge_term * max(len(flat), 1))(*flat)
         else:
             if len(terms) != self.nexp:
                 raise SmatError(SMAT_ERR_INVALID, "one term per expert")
-            flat = [merge_term(t) for _ in range(self.count) for t in terms]
-        arr = (smat_merge_term * max(len(flat), 1))(*flat)
+            # the experts' records are marshalled once and repeated for every tensor
+            row = (smat_merge_term * self.nexp)(*[merge_term(t) for t in terms])
+            arr = (smat_merge_term * (self.nexp * max(self.count, 1))).from_buffer_copy(bytes(row) * max(self.count, 1))
         _check(lib().smat_merge_multi(self._plan, arr, _stream_handle(stream)))
 
     def close(self) -> None:

@@ -96,10 +96,16 @@ def adam_hparams(optimizer: torch.optim.Optimizer, params: Sequence[torch.nn.Par
         hps.append((float(g["lr"]), float(b1), float(b2), float(g["eps"]), wd))
     if len(set(hps)) > 1:
         raise SmatError(SMAT_ERR_INVALID, "parameters of the fused update must share lr, betas, eps and weight decay")
-    steps = set()
+    steps, on_gpu = set(), []
     for p in params:
         st = optimizer.state.get(p)
-        steps.add(int(float(st["step"])) if st and "step" in st else 0)
+        count = st["step"] if st and "step" in st else 0
+        if isinstance(count, torch.Tensor) and count.is_cuda:
+            on_gpu.append(count)
+        else:
+            steps.add(int(float(count)))
+    if on_gpu:  # fused and capturable optimizers count on the GPU: one read for all of them
+        steps.update(int(c) for c in torch.stack([c.reshape(()).float() for c in on_gpu]).tolist())
     if len(steps) > 1:
         raise SmatError(SMAT_ERR_INVALID, "parameters of the fused update must share the optimizer step count")
     lr, b1, b2, eps, wd = hps[0] if hps else (0.0, 0.9, 0.999, 1e-8, 0.0)
@@ -332,8 +338,7 @@ class SimulatedMergeTraining:
             self.plan.grad_norm(self.seed, step, self.lam, accumulate, float(max_norm), sumsq, coef)
             norm = sumsq.sqrt()
         self.plan.adamw_fused(self.seed, step, self.lam, hp, accumulate=accumulate, grad_scale_dev=coef)
-        for c in counts:        # the optimizer's own step counts (CPU or GPU scalars)
-            c.add_(1)
+        torch._foreach_add_(counts, 1)      # the optimizer's own step counts (CPU or GPU scalars)
         return norm
 
     def close(self) -> None:
