@@ -132,6 +132,44 @@ uint64_t group_span(uint64_t elem_offset, int64_t n) { return n > 0 ? (uint64_t)
 uint64_t chunk_count(uint64_t elem_offset, int64_t n) {
   return (group_span(elem_offset, n) + smat::kChunk - 1) / smat::kChunk;
 }
+
+// A list's table (see ChunkTable): the chunks of every tensor, its last partial one included, or, where
+// `split`, its whole chunks and then the segments of its remainder.  put(entry) is called in table
+// order; returns how many entries are chunks.
+template <typename D, typename F>
+uint32_t build_table(const D* descs, int32_t count, bool split, F&& put) {
+  uint32_t chunks = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    const uint64_t span = group_span(descs[i].elem_offset, descs[i].n);
+    const uint64_t end = (span + (split ? 0 : smat::kChunk - 1)) / smat::kChunk;
+    for (uint64_t c = 0; c < end; ++c, ++chunks) put(make_uint2((uint32_t)i, (uint32_t)(c * smat::kChunkSegments)));
+  }
+  for (int32_t i = 0; i < count && split; ++i) {
+    const uint64_t span = group_span(descs[i].elem_offset, descs[i].n);
+    const uint64_t end = (span + smat::kSegment - 1) / smat::kSegment;
+    for (uint64_t k = span / smat::kChunk * smat::kChunkSegments; k < end; ++k)
+      put(make_uint2((uint32_t)i, (uint32_t)k));
+  }
+  return chunks;
+}
+
+// Whether a list's remainders go in segments.  A block without a tile costs 0.2 ns of a launch that has
+// little else to do and nothing of one that streams, while telling segments from chunks costs every
+// block a few scalar instructions (0.2-0.7 % of large lists).  So they are taken where they spare 16,384
+// one-quad blocks and an eighth of all: 818 tensors with 9.3M elements (38K of 75K blocks) 43.1 -> 34.7 us
+// a step, while 1,454 tensors with 305M (79K of 1.28M) gained nothing.
+template <typename D>
+bool split_table(const D* descs, int32_t count) {
+  uint64_t all = 0, spared = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    const uint64_t span = group_span(descs[i].elem_offset, descs[i].n), rest = span % smat::kChunk;
+    all += (span + smat::kChunk - 1) / smat::kChunk * smat::tiles_per_chunk(1);
+    if (rest)
+      spared += smat::tiles_per_chunk(1) - (rest + smat::kSegment - 1) / smat::kSegment * smat::tiles_per_segment(1);
+  }
+  return spared >= 16384 && spared * 8 >= all;
+}
+
 bool too_many_tiles(uint64_t elem_offset, int64_t n) {
   return (group_span(elem_offset, n) + smat::tile_elems(1) - 1) / smat::tile_elems(1) > 0x7FFFFFFF;
 }
@@ -414,12 +452,16 @@ struct smat_plan {
   bool has_gs = false, has_gt = false;  // gradient arrays (grad_sim, grad_theta) known for every tensor
   std::vector<smat_tensor_desc> descs;
   std::vector<TensorRec> recs;
-  std::vector<uint2> chunks;  // (tensor index, chunk index within the tensor)
+  std::vector<uint2> entries;  // the list's table, whose first nchunks entries are chunks
+  uint32_t nchunks = 0;
+  smat::ChunkTable table() const {
+    return {reinterpret_cast<const uint2*>(ws + off_chunks), nchunks, (uint32_t)entries.size() - nchunks};
+  }
   std::vector<void*> expert_ptrs, sim_ptrs;
 
   // workspace layout: [tensor records][chunk table][expert pointer table][simulated pointer table]
   // [params, then the scale records of the device-driven launches][optimizer state table]
-  // [gradient-norm partials: kNormPartialsPerChunk floats per chunk][their fp64 sums]
+  // [gradient-norm partials: one float per segment][their fp64 sums]
   // [the optimizer constants of a device-driven step]
   size_t off_recs = 0, off_chunks = 0, off_expert = 0, off_sim = 0, off_params = 0, off_scales = 0, ws_bytes = 0;
   size_t off_partials = 0, off_sums = 0, off_aconsts = 0;
@@ -655,17 +697,14 @@ extern "C" smat_status smat_plan_create(const smat_tensor_desc* descs, int32_t c
     delete p;
     return fail(SMAT_ERR_INVALID, "smat_plan_create: tensor list too large");
   }
-  p->chunks.reserve(nchunks);
-  for (int32_t i = 0; i < count; ++i) {
-    const uint32_t nc = (uint32_t)chunk_count(p->descs[i].elem_offset, p->descs[i].n);
-    for (uint32_t c = 0; c < nc; ++c) p->chunks.push_back(make_uint2((uint32_t)i, c));
-  }
+  p->entries.reserve(nchunks);
+  p->nchunks = build_table(descs, count, split_table(descs, count), [&](uint2 e) { p->entries.push_back(e); });
 
   size_t off = 0;
   p->off_recs = off;
   off = align256(off + sizeof(TensorRec) * count);
   p->off_chunks = off;
-  off = align256(off + sizeof(uint2) * p->chunks.size());
+  off = align256(off + sizeof(uint2) * p->entries.size());
   p->off_expert = off;
   off = align256(off + sizeof(void*) * count);
   p->off_sim = off;
@@ -676,7 +715,7 @@ extern "C" smat_status smat_plan_create(const smat_tensor_desc* descs, int32_t c
   p->off_adam = off;
   off = align256(off + sizeof(AdamRec) * count);
   p->off_partials = off;
-  off = align256(off + sizeof(float) * smat::kNormPartialsPerChunk * p->chunks.size());
+  off = align256(off + sizeof(float) * (size_t)smat::table_segments(p->table()));
   p->off_sums = off;
   off = align256(off + sizeof(double) * smat::kNormSums);
   p->off_aconsts = off;
@@ -707,7 +746,7 @@ extern "C" smat_status smat_plan_bind_workspace(smat_plan* p, void* workspace, s
   SMAT_HIP(p->params_staging.init((sizeof(ParamRec) + sizeof(ScaleRec)) * p->count));
   std::memset(p->static_staging, 0, static_bytes);
   device_recs(p, p->recs, nullptr, p->static_staging + p->off_recs);
-  std::memcpy(p->static_staging + p->off_chunks, p->chunks.data(), sizeof(uint2) * p->chunks.size());
+  std::memcpy(p->static_staging + p->off_chunks, p->entries.data(), sizeof(uint2) * p->entries.size());
   std::memcpy(p->static_staging + p->off_expert, p->expert_ptrs.data(), sizeof(void*) * p->count);
   std::memcpy(p->static_staging + p->off_sim, p->sim_ptrs.data(), sizeof(void*) * p->count);
   if (!p->ev_static) SMAT_HIP(hipEventCreateWithFlags(&p->ev_static, hipEventDisableTiming));
@@ -793,11 +832,10 @@ extern "C" smat_status smat_simulate_multi(smat_plan* p, uint64_t seed, uint32_t
     return fail(SMAT_ERR_STATE, "smat_simulate_multi: offload mode: the buffers hold theta~ of the last simulate; "
                 "switch to the simulated storage and back (the restore refills theta0) before simulating again");
   if (p->offload && p->prefetch_pending) SMAT_HIP(hipStreamWaitEvent(stream, p->ev_prefetch, 0));
-  if (!p->chunks.empty())
+  if (!p->entries.empty())
     SMAT_HIP(smat::launch_simulate_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                          reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
-                                         reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
-                                         (uint32_t)p->chunks.size(), p->t0_dt, p->out_dt, seed, step, p->runs_sim,
+                                         p->table(), p->t0_dt, p->out_dt, seed, step, p->runs_sim,
                                          stream));
   p->fresh = true;
   return SMAT_OK;
@@ -813,11 +851,10 @@ extern "C" smat_status smat_backward_multi(smat_plan* p, uint64_t seed, uint32_t
     return fail(SMAT_ERR_STATE, "smat_backward_multi: gradient arrays not set (smat_plan_set_grads)");
   if (!p->ws) return fail(SMAT_ERR_STATE, "smat_backward_multi: no workspace bound");
   if (!p->params_set) return fail(SMAT_ERR_STATE, "smat_backward_multi: parameters never set");
-  if (!p->chunks.empty())
+  if (!p->entries.empty())
     SMAT_HIP(smat::launch_backward_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                          reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
-                                         reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
-                                         (uint32_t)p->chunks.size(), p->g_dt, accumulate != 0, lambda, seed, step,
+                                         p->table(), p->g_dt, accumulate != 0, lambda, seed, step,
                                          p->runs_bwd, stream));
   return SMAT_OK;
 }
@@ -889,12 +926,11 @@ extern "C" smat_status smat_simulate_multi_dev(smat_plan* p, const smat_step_sta
   if (st != SMAT_OK) return st;
   if (p->state != SMAT_EXPERT)
     return fail(SMAT_ERR_STATE, "smat_simulate_multi_dev: the simulated storage is active (restore the expert first)");
-  if (!p->chunks.empty())
+  if (!p->entries.empty())
     SMAT_HIP(smat::launch_simulate_multi_dev(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                              reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
                                              reinterpret_cast<const ScaleRec*>(p->ws + p->off_scales),
-                                             reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
-                                             (uint32_t)p->chunks.size(), p->t0_dt, p->out_dt,
+                                             p->table(), p->t0_dt, p->out_dt,
                                              reinterpret_cast<const StepState*>(state), p->runs_sim, stream));
   p->fresh = true;
   return SMAT_OK;
@@ -909,12 +945,11 @@ extern "C" smat_status smat_backward_multi_dev(smat_plan* p, const smat_step_sta
     return fail(SMAT_ERR_INVALID, "smat_backward_multi_dev: accumulate must be 0 or 1");
   if (!p->has_gs || !p->has_gt)
     return fail(SMAT_ERR_STATE, "smat_backward_multi_dev: gradient arrays not set (smat_plan_set_grads)");
-  if (!p->chunks.empty())
+  if (!p->entries.empty())
     SMAT_HIP(smat::launch_backward_multi_dev(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                              reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
                                              reinterpret_cast<const ScaleRec*>(p->ws + p->off_scales),
-                                             reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
-                                             (uint32_t)p->chunks.size(), p->g_dt, accumulate != 0, lambda,
+                                             p->table(), p->g_dt, accumulate != 0, lambda,
                                              reinterpret_cast<const StepState*>(state), p->runs_bwd, stream));
   return SMAT_OK;
 }
@@ -1049,11 +1084,11 @@ extern "C" smat_status smat_adamw_fused_multi(smat_plan* p, uint64_t seed, uint3
     return fail(SMAT_ERR_STATE, "smat_adamw_fused_multi: gradient arrays not set (smat_plan_set_grads)");
   if (p->state != SMAT_EXPERT)
     return fail(SMAT_ERR_STATE, "smat_adamw_fused_multi: restore the expert storage before the optimizer step");
-  if (!p->chunks.empty())
+  if (!p->entries.empty())
     SMAT_HIP(smat::launch_adamw_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                       reinterpret_cast<const AdamRec*>(p->ws + p->off_adam),
                                       reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
-                                      reinterpret_cast<const uint2*>(p->ws + p->off_chunks), (uint32_t)p->chunks.size(),
+                                      p->table(),
                                       A, p->g_dt, accumulate != 0, lambda, seed, step, grad_scale_dev, p->runs_adam, stream));
   return SMAT_OK;
 }
@@ -1074,7 +1109,7 @@ extern "C" smat_status smat_grad_norm_multi(smat_plan* p, uint64_t seed, uint32_
   if (!p->params_set) return fail(SMAT_ERR_STATE, "smat_grad_norm_multi: parameters never set");
   SMAT_HIP(smat::launch_sqnorm_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                      reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
-                                     reinterpret_cast<const uint2*>(p->ws + p->off_chunks), (uint32_t)p->chunks.size(),
+                                     p->table(),
                                      reinterpret_cast<float*>(p->ws + p->off_partials),
                                      reinterpret_cast<double*>(p->ws + p->off_sums), p->g_dt, accumulate != 0, lambda,
                                      seed, step, sumsq, clip_coef, max_norm, stream));
@@ -1104,8 +1139,7 @@ extern "C" smat_status smat_adamw_fused_multi_dev(smat_plan* p, const smat_step_
                                         reinterpret_cast<const AdamRec*>(p->ws + p->off_adam),
                                         reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
                                         reinterpret_cast<const ScaleRec*>(p->ws + p->off_scales),
-                                        reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
-                                        (uint32_t)p->chunks.size(), adam_hyper(hp),
+                                        p->table(), adam_hyper(hp),
                                         reinterpret_cast<const smat::AdamStepState*>(adam_state),
                                         reinterpret_cast<AdamConsts*>(p->ws + p->off_aconsts), p->g_dt,
                                         accumulate != 0, lambda, reinterpret_cast<const StepState*>(state),
@@ -1129,8 +1163,7 @@ extern "C" smat_status smat_grad_norm_multi_dev(smat_plan* p, const smat_step_st
   SMAT_HIP(smat::launch_sqnorm_multi_dev(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                          reinterpret_cast<const ParamRec*>(p->ws + p->off_params),
                                          reinterpret_cast<const ScaleRec*>(p->ws + p->off_scales),
-                                         reinterpret_cast<const uint2*>(p->ws + p->off_chunks),
-                                         (uint32_t)p->chunks.size(), reinterpret_cast<float*>(p->ws + p->off_partials),
+                                         p->table(), reinterpret_cast<float*>(p->ws + p->off_partials),
                                          reinterpret_cast<double*>(p->ws + p->off_sums), p->g_dt, accumulate != 0,
                                          lambda, reinterpret_cast<const StepState*>(state), sumsq, clip_coef,
                                          max_norm, stream));
@@ -1275,12 +1308,11 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
                                        reinterpret_cast<uintptr_t>(d.theta0) + n * dtype_bytes(theta0_dtype), false, i,
                                        "theta0"};
     g_scratch_ranges[nranges++] = {d.tensor_id, {d.elem_offset, d.elem_offset + (uint64_t)d.n}};
-    const uint64_t nc = chunk_count(d.elem_offset, d.n);
-    if (nchunks + nc > max_chunks)
+    nchunks += (size_t)chunk_count(d.elem_offset, d.n);
+    if (nchunks > max_chunks)
       return fail(SMAT_ERR_INVALID, "%s: the list needs more than the %zu chunks of %lld elements that the %zu-byte "
                   "static tables hold for %d tensors (use a plan)", where0, max_chunks, (long long)smat::kChunk,
                   kScratchBytes, count);
-    for (uint64_t c = 0; c < nc; ++c) chunks[nchunks++] = make_uint2((uint32_t)i, (uint32_t)c);
   }
   std::sort(g_scratch_ranges, g_scratch_ranges + nranges);
   for (size_t i = 1; i < nranges; ++i)
@@ -1293,14 +1325,24 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
   if (smat_status st = refuse_capture(stream, where0); st != SMAT_OK) return st;
   void* dev = nullptr;
   if (smat_status st = scratch_address(&dev); st != SMAT_OK) return st;
+  // a list whose segments would not fit keeps its remainders in chunks, whose count was checked above
+  bool split = split_table(descs, count);
+  if (split) {
+    size_t used = 0;
+    build_table(descs, count, true, [&](uint2) { ++used; });
+    split = used <= max_chunks;
+  }
+  size_t used = 0;
+  const uint32_t table_chunks = build_table(descs, count, split, [&](uint2 e) { chunks[used++] = e; });
   // a copy from pageable host memory runs synchronously (HIP's documented behaviour), so the host
   // image is free for the next call once this returns; stream order puts the upload after any
   // earlier launch on `stream` that reads the device tables
-  SMAT_HIP(hipMemcpyAsync(dev, g_scratch_host, off_chunks + sizeof(uint2) * nchunks, hipMemcpyHostToDevice, stream));
+  SMAT_HIP(hipMemcpyAsync(dev, g_scratch_host, off_chunks + sizeof(uint2) * used, hipMemcpyHostToDevice, stream));
   char* base = static_cast<char*>(dev);
   SMAT_HIP(smat::launch_simulate_multi(reinterpret_cast<const TensorRec*>(base),
                                        reinterpret_cast<const ParamRec*>(base + off_prms),
-                                       reinterpret_cast<const uint2*>(base + off_chunks), (uint32_t)nchunks,
+                                       {reinterpret_cast<const uint2*>(base + off_chunks), table_chunks,
+                                        (uint32_t)used - table_chunks},
                                        theta0_dtype, out_dtype, seed, step, lines.runs(), stream));
   return SMAT_OK;
 }
@@ -1429,11 +1471,15 @@ struct smat_merge_plan {
   int e_dt = 0, t0_dt = 0, out_dt = 0;
   bool runs = false;  // block order (OffLine)
   std::vector<TensorRec> recs;
-  std::vector<uint2> chunks;
+  std::vector<uint2> entries;  // the list's table, as in smat_plan
+  uint32_t nchunks = 0;
   std::vector<const void*> experts;  // [count][nexp]
   // workspace layout: [tensor records][chunk table][expert pointer table][terms]
   size_t off_recs = 0, off_chunks = 0, off_experts = 0, off_terms = 0, ws_bytes = 0;
   char* ws = nullptr;
+  smat::ChunkTable table() const {
+    return {reinterpret_cast<const uint2*>(ws + off_chunks), nchunks, (uint32_t)entries.size() - nchunks};
+  }
   char* static_staging = nullptr;
   hipEvent_t ev_static = nullptr;
   Staging terms_staging;
@@ -1510,7 +1556,7 @@ extern "C" smat_status smat_merge_plan_create(const smat_merge_desc* descs, int3
   p->out_dt = out_dtype;
   p->recs.resize(count);
   p->experts.assign(experts, experts + (size_t)count * n_experts);
-  p->chunks.reserve(nchunks);
+  p->entries.reserve(nchunks);
   OffLine lines;
   for (int32_t i = 0; i < count; ++i) {
     const smat_merge_desc& d = descs[i];
@@ -1529,16 +1575,15 @@ extern "C" smat_status smat_merge_plan_create(const smat_merge_desc* descs, int3
       x = smat::back_ptr(x, smat::group_head(d.elem_offset), dtype_bytes(expert_dtype));
     }
     if (d.n > 0) lines.add(r.n, merge_off_line(r, p->experts.data() + (size_t)i * n_experts, n_experts));
-    const uint32_t nc = (uint32_t)chunk_count(d.elem_offset, d.n);
-    for (uint32_t c = 0; c < nc; ++c) p->chunks.push_back(make_uint2((uint32_t)i, c));
   }
+  p->nchunks = build_table(descs, count, split_table(descs, count), [&](uint2 e) { p->entries.push_back(e); });
   p->runs = lines.runs();
   const size_t cells = (size_t)count * n_experts;
   size_t off = 0;
   p->off_recs = off;
   off = align256(off + sizeof(TensorRec) * count);
   p->off_chunks = off;
-  off = align256(off + sizeof(uint2) * p->chunks.size());
+  off = align256(off + sizeof(uint2) * p->entries.size());
   p->off_experts = off;
   off = align256(off + sizeof(void*) * cells);
   p->off_terms = off;
@@ -1571,7 +1616,7 @@ extern "C" smat_status smat_merge_plan_bind_workspace(smat_merge_plan* p, void* 
   SMAT_HIP(p->terms_staging.init(sizeof(MergeTerm) * cells));
   std::memset(p->static_staging, 0, static_bytes);
   std::memcpy(p->static_staging + p->off_recs, p->recs.data(), sizeof(TensorRec) * p->count);
-  std::memcpy(p->static_staging + p->off_chunks, p->chunks.data(), sizeof(uint2) * p->chunks.size());
+  std::memcpy(p->static_staging + p->off_chunks, p->entries.data(), sizeof(uint2) * p->entries.size());
   std::memcpy(p->static_staging + p->off_experts, p->experts.data(), sizeof(void*) * cells);
   if (!p->ev_static) SMAT_HIP(hipEventCreateWithFlags(&p->ev_static, hipEventDisableTiming));
   if (static_bytes > 0)
@@ -1605,11 +1650,11 @@ extern "C" smat_status smat_merge_multi(smat_merge_plan* p, const smat_merge_ter
                                        reinterpret_cast<MergeRec*>(p->ws + p->off_terms), cells, st.signal(), stream));
     st.sent(smat::upload_blocks(cells));
   }
-  if (!p->chunks.empty())
+  if (!p->entries.empty())
     SMAT_HIP(smat::launch_merge_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),
                                       reinterpret_cast<const void* const*>(p->ws + p->off_experts),
                                       reinterpret_cast<const MergeRec*>(p->ws + p->off_terms),
-                                      reinterpret_cast<const uint2*>(p->ws + p->off_chunks), (uint32_t)p->chunks.size(),
+                                      p->table(),
                                       p->nexp, p->e_dt, p->t0_dt, p->out_dt, plain, p->runs, stream));
   return SMAT_OK;
 }

@@ -161,21 +161,35 @@ enum : uint32_t { kVecAdam = 4u, kVecAdamAcc = 8u };
 // Work decomposition: a block of kBlock threads (one wave) handles one tile of Q quads per
 // thread (tile = 4 * kBlock * Q elements); thread x owns quads x, x + kBlock, ... of the tile,
 // so every load/store instruction of the wave covers one contiguous span and consecutive blocks
-// stream consecutive memory.  A tensor list is cut into chunks of kChunk elements; block b of a
-// list launch takes tile (b mod tiles-per-chunk) of chunk (b / tiles-per-chunk), which keeps
-// the chunk table small.  The simulate, the backward and the fused optimizer step take one quad
-// per thread: each wave then keeps one 64-lane piece of every array in flight, the access shape
+// stream consecutive memory.  A list is cut into chunks of kChunk elements
+// through a table that keeps its entries few; where many small tensors would leave most blocks of
+// their chunks without a tile, the remainders go in segments of kSegment elements instead (ChunkTable).  The simulate, the backward and the fused optimizer step take one
+// quad per thread: each wave then keeps one 64-lane piece of every array in flight, the access shape
 // that streams fastest on MI355X.
 constexpr int kBlock = 64;
 constexpr int kSimQuads = 1;
 constexpr int kBwdQuads = 1;
 constexpr int kAdamQuads = 1;
 constexpr int64_t kChunk = 16384;
+constexpr int64_t kSegment = 2048;
+constexpr uint32_t kChunkSegments = (uint32_t)(kChunk / kSegment);
 constexpr int64_t tile_elems(int quads) { return 4 * kBlock * quads; }
-constexpr int tiles_per_chunk(int quads) { return (int)(kChunk / tile_elems(quads)); }
-static_assert(kChunk % tile_elems(kSimQuads) == 0 && kChunk % tile_elems(kBwdQuads) == 0 &&
-                  kChunk % tile_elems(kAdamQuads) == 0,
-              "tiles split chunks");
+constexpr uint32_t tiles_per_segment(int quads) { return (uint32_t)(kSegment / tile_elems(quads)); }
+constexpr uint32_t tiles_per_chunk(int quads) { return kChunkSegments * tiles_per_segment(quads); }
+static_assert(kSegment % tile_elems(kSimQuads) == 0 && kSegment % tile_elems(kBwdQuads) == 0 &&
+                  kSegment % tile_elems(kAdamQuads) == 0,
+              "tiles split segments");
+
+// A list's table in device memory: entries (tensor index, first segment within the tensor), `chunks` of
+// them for chunks, then `segments` for single segments.
+struct ChunkTable {
+  const uint2* entries;
+  uint32_t chunks, segments;
+};
+// How a list launch finds its tiles: chunks in linear block order or in runs per XCD (block_order), or a
+// table that also has segments.
+enum TableOrder : int { kLinear = 0, kRuns = 1, kMixed = 2 };
+constexpr uint32_t kMixedRuns = 1u << 31;  // on the chunk count of a kMixed launch: its chunks in runs
 
 constexpr uint32_t kStreamMask = 0u;
 constexpr uint32_t kStreamNoise = 1u;

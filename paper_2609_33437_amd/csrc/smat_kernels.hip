@@ -238,7 +238,7 @@ template <typename T0, typename TO, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_simulate_one(TensorRec R, ParamRec P, PhiloxKeys K, uint32_t step) {
   raise_priority();
   constexpr int64_t tile = tile_elems(kSimQuads);
-  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(kSimQuads)) * tile;
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, gridDim.x, tiles_per_chunk(kSimQuads)) * tile;
   simulate_tile<T0, TO>(tensor_tile<T0, TO>(R, begin, tile), P, K, step);
 }
 
@@ -246,79 +246,73 @@ template <typename TG, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_backward_one(TensorRec R, ParamRec P, PhiloxKeys K, uint32_t step,
                                                          float lambda) {
   constexpr int64_t tile = tile_elems(kBwdQuads);
-  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(kBwdQuads)) * tile;
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, gridDim.x, tiles_per_chunk(kBwdQuads)) * tile;
   Tile T = tensor_tile<float, float>(R, begin, tile);
   T.grad_sim = advance<TG>(R.grad_sim, begin);
   T.grad_theta = R.grad_theta + begin;
   backward_tile<TG, kBwdQuads, true>(T, P, K, step, lambda);
 }
 
-template <typename T0, typename TO, bool RUNS>
+template <typename T0, typename TO, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_simulate_multi(const TensorRec* __restrict__ recs,
                                                            const ParamRec* __restrict__ prms,
-                                                           const uint2* __restrict__ chunks, PhiloxKeys K,
+                                                           const uint2* __restrict__ entries, uint32_t chunks,
+                                                           PhiloxKeys K,
                                                            uint32_t step) {
   raise_priority();
   constexpr int64_t tile = tile_elems(kSimQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
-  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
-  const uint2 ch = chunks[block / tpc];
-  const Tile T = list_tile<T0, TO, float>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
+  const ListBlock B = list_block<kSimQuads, ORDER>(entries, chunks);
+  const Tile T = list_tile<T0, TO, float>(rec_at(recs, B.tensor), B.tile, tile);
   if (T.len == 0) return;  // unused tile of a tensor's last chunk
-  simulate_tile<T0, TO>(T, rec_at(prms, ch.x), K, step);
+  simulate_tile<T0, TO>(T, rec_at(prms, B.tensor), K, step);
 }
 
-template <typename TG, bool ACC, bool RUNS>
+template <typename TG, bool ACC, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_backward_multi(const TensorRec* __restrict__ recs,
                                                            const ParamRec* __restrict__ prms,
-                                                           const uint2* __restrict__ chunks, PhiloxKeys K,
+                                                           const uint2* __restrict__ entries, uint32_t chunks,
+                                                           PhiloxKeys K,
                                                            uint32_t step, float lambda) {
   constexpr int64_t tile = tile_elems(kBwdQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
-  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
-  const uint2 ch = chunks[block / tpc];
-  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
+  const ListBlock B = list_block<kBwdQuads, ORDER>(entries, chunks);
+  const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
   if (T.len == 0) return;
-  backward_tile<TG, kBwdQuads, ACC>(T, rec_at(prms, ch.x), K, step, lambda);
+  backward_tile<TG, kBwdQuads, ACC>(T, rec_at(prms, B.tensor), K, step, lambda);
 }
 
 // The same list kernels with the step's seed, step and scale read from device memory, so that a
 // captured graph replays them with whatever the caller last wrote there.  Each block forms its
 // tensor's coefficient from that scale and the tensor's ScaleRec exactly as the host forms it.
-template <typename T0, typename TO, bool RUNS>
+template <typename T0, typename TO, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* __restrict__ recs,
                                                                const ParamRec* __restrict__ prms,
                                                                const ScaleRec* __restrict__ scales,
-                                                               const uint2* __restrict__ chunks,
+                                                               const uint2* __restrict__ entries, uint32_t chunks,
                                                                const StepState* __restrict__ state) {
   raise_priority();
   constexpr int64_t tile = tile_elems(kSimQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
-  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
-  const uint2 ch = chunks[block / tpc];
-  const Tile T = list_tile<T0, TO, float>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
+  const ListBlock B = list_block<kSimQuads, ORDER>(entries, chunks);
+  const Tile T = list_tile<T0, TO, float>(rec_at(recs, B.tensor), B.tile, tile);
   if (T.len == 0) return;
   const StepState S = *state;
-  ParamRec P = rec_at(prms, ch.x);
-  P.t = device_coefficient(S.scale, rec_at(scales, ch.x));
+  ParamRec P = rec_at(prms, B.tensor);
+  P.t = device_coefficient(S.scale, rec_at(scales, B.tensor));
   simulate_tile<T0, TO>(T, P, philox_keys(S.seed), S.step);
 }
 
-template <typename TG, bool ACC, bool RUNS>
+template <typename TG, bool ACC, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_backward_multi_dev(const TensorRec* __restrict__ recs,
                                                                const ParamRec* __restrict__ prms,
                                                                const ScaleRec* __restrict__ scales,
-                                                               const uint2* __restrict__ chunks,
+                                                               const uint2* __restrict__ entries, uint32_t chunks,
                                                                const StepState* __restrict__ state, float lambda) {
   constexpr int64_t tile = tile_elems(kBwdQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
-  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
-  const uint2 ch = chunks[block / tpc];
-  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, block % tpc, tile);
+  const ListBlock B = list_block<kBwdQuads, ORDER>(entries, chunks);
+  const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
   if (T.len == 0) return;
   const StepState S = *state;
-  ParamRec P = rec_at(prms, ch.x);
-  P.t = device_coefficient(S.scale, rec_at(scales, ch.x));
+  ParamRec P = rec_at(prms, B.tensor);
+  P.t = device_coefficient(S.scale, rec_at(scales, B.tensor));
   backward_tile<TG, kBwdQuads, ACC>(T, P, philox_keys(S.seed), S.step, lambda);
 }
 
@@ -397,75 +391,59 @@ hipError_t launch_backward_one(const TensorRec& rec, const ParamRec& prm, int gr
   });
 }
 
-hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
+hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, const ChunkTable& table,
                                  int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, bool runs,
                                  hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
-  constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
+  return for_table<kSimQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
+    const dim3 block(kBlock);
     with_type(theta0_dtype, [&](auto t0) {
       with_type(out_dtype, [&](auto to) {
-        with_flag(runs, [&](auto rn) {
-          k_simulate_multi<typename decltype(t0)::type, typename decltype(to)::type, decltype(rn)::value>
-              <<<grid, block, 0, stream>>>(recs, prms, ch, K, step);
-        });
+        k_simulate_multi<typename decltype(t0)::type, typename decltype(to)::type, decltype(order)::value>
+            <<<grid, block, 0, stream>>>(recs, prms, entries, chunks, K, step);
       });
     });
   });
 }
 
-hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
+hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, const ChunkTable& table,
                                  int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
                                  bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
-  constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
+  return for_table<kBwdQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
+    const dim3 block(kBlock);
     with_type(grad_dtype, [&](auto tg) {
       with_flag(accumulate, [&](auto acc) {
-        with_flag(runs, [&](auto rn) {
-          k_backward_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
-              <<<grid, block, 0, stream>>>(recs, prms, ch, K, step, lambda);
-        });
+        k_backward_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
+            <<<grid, block, 0, stream>>>(recs, prms, entries, chunks, K, step, lambda);
       });
     });
   });
 }
 
 hipError_t launch_simulate_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
-                                     const uint2* chunks, uint32_t nchunks, int theta0_dtype, int out_dtype,
+                                     const ChunkTable& table, int theta0_dtype, int out_dtype,
                                      const StepState* state, bool runs, hipStream_t stream) {
-  constexpr uint32_t tpc = tiles_per_chunk(kSimQuads);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
+  return for_table<kSimQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
+    const dim3 block(kBlock);
     with_type(theta0_dtype, [&](auto t0) {
       with_type(out_dtype, [&](auto to) {
-        with_flag(runs, [&](auto rn) {
-          k_simulate_multi_dev<typename decltype(t0)::type, typename decltype(to)::type, decltype(rn)::value>
-              <<<grid, block, 0, stream>>>(recs, prms, scales, ch, state);
-        });
+        k_simulate_multi_dev<typename decltype(t0)::type, typename decltype(to)::type, decltype(order)::value>
+            <<<grid, block, 0, stream>>>(recs, prms, scales, entries, chunks, state);
       });
     });
   });
 }
 
 hipError_t launch_backward_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
-                                     const uint2* chunks, uint32_t nchunks, int grad_dtype, bool accumulate,
+                                     const ChunkTable& table, int grad_dtype, bool accumulate,
                                      float lambda, const StepState* state, bool runs, hipStream_t stream) {
-  constexpr uint32_t tpc = tiles_per_chunk(kBwdQuads);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
+  return for_table<kBwdQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
+    const dim3 block(kBlock);
     with_type(grad_dtype, [&](auto tg) {
       with_flag(accumulate, [&](auto acc) {
-        with_flag(runs, [&](auto rn) {
-          k_backward_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
-              <<<grid, block, 0, stream>>>(recs, prms, scales, ch, state, lambda);
-        });
+        k_backward_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
+            <<<grid, block, 0, stream>>>(recs, prms, scales, entries, chunks, state, lambda);
       });
     });
   });

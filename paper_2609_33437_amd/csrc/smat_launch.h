@@ -69,6 +69,35 @@ void with_flag(bool flag, F&& fn) {
     fn(std::false_type());
 }
 
+// fn(entries, chunks, grid, order, first segment) for the launches of a list's table with tiles of Q
+// quads, in pieces that each fit one launch, stopping at the first launch error.
+template <int Q, typename F>
+hipError_t for_table(const ChunkTable& t, bool runs, F&& fn) {
+  constexpr uint32_t tps = tiles_per_segment(Q), tpc = tiles_per_chunk(Q);
+  using Mixed = std::integral_constant<int, kMixed>;
+  const uint32_t mark = runs ? kMixedRuns : 0u;
+  const uint64_t blocks = (uint64_t)t.chunks * tpc + (uint64_t)t.segments * tps;
+  if (t.segments > 0 && blocks <= max_grid_blocks(kBlock)) {
+    fn(t.entries, t.chunks | mark, dim3((uint32_t)blocks), Mixed(), 0);
+    return hipGetLastError();
+  }
+  const hipError_t e = for_pieces(t.chunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
+    const dim3 grid((uint32_t)count * tpc);
+    if (runs)
+      fn(t.entries + first, 0u, grid, std::integral_constant<int, kRuns>(), first * kChunkSegments);
+    else
+      fn(t.entries + first, 0u, grid, std::integral_constant<int, kLinear>(), first * kChunkSegments);
+  });
+  if (e != hipSuccess) return e;
+  return for_pieces(t.segments, max_grid_blocks(kBlock) / tps, [&](uint64_t first, uint64_t count) {
+    fn(t.entries + t.chunks + first, 0u, dim3((uint32_t)count * tps), Mixed(),
+       (uint64_t)t.chunks * kChunkSegments + first);
+  });
+}
+// Segments, and elements up to the padding of tensors' ends, that a table covers.
+inline uint64_t table_segments(const ChunkTable& t) { return (uint64_t)t.chunks * kChunkSegments + t.segments; }
+inline uint64_t table_elems(const ChunkTable& t) { return table_segments(t) * (uint64_t)kSegment; }
+
 // Whether an array's tiles begin inside a 128-byte line (its address as device_rec gives it; tiles are
 // multiples of 512 bytes).
 inline bool off_line(const void* p) { return reinterpret_cast<uintptr_t>(p) % 128 != 0; }
@@ -134,34 +163,35 @@ hipError_t launch_simulate_one(const TensorRec& rec, const ParamRec& prm, int th
                                uint64_t seed, uint32_t step, bool runs, hipStream_t stream);
 hipError_t launch_backward_one(const TensorRec& rec, const ParamRec& prm, int grad_dtype, float lambda,
                                uint64_t seed, uint32_t step, bool runs, hipStream_t stream);
-hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
-                                 int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, bool runs, hipStream_t stream);
-hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
+hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, const ChunkTable& table,
+                                 int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, bool runs,
+                                 hipStream_t stream);
+hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, const ChunkTable& table,
                                  int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
                                  bool runs, hipStream_t stream);
 // Graph-capturable forms: seed, step and scale read from `state` in device memory, each tensor's
 // coefficient formed from the scale and its ScaleRec.
 hipError_t launch_simulate_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
-                                     const uint2* chunks, uint32_t nchunks, int theta0_dtype, int out_dtype,
+                                     const ChunkTable& table, int theta0_dtype, int out_dtype,
                                      const StepState* state, bool runs, hipStream_t stream);
 hipError_t launch_backward_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
-                                     const uint2* chunks, uint32_t nchunks, int grad_dtype, bool accumulate,
+                                     const ChunkTable& table, int grad_dtype, bool accumulate,
                                      float lambda, const StepState* state, bool runs, hipStream_t stream);
 // step += increment and the scale of that step, in place (one thread).
 hipError_t launch_step_advance(StepState* state, uint32_t increment, float alpha_min, hipStream_t stream);
 hipError_t launch_adamw_one(const TensorRec& rec, const AdamRec& st, const ParamRec& prm, const AdamConsts& A,
                             int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
                             const float* dev_scale, bool runs, hipStream_t stream);
-hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, const ParamRec* prms, const uint2* chunks,
-                              uint32_t nchunks, const AdamConsts& A, int grad_dtype, bool accumulate, float lambda,
-                              uint64_t seed, uint32_t step, const float* dev_scale, bool runs, hipStream_t stream);
+hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, const ParamRec* prms,
+                              const ChunkTable& table, const AdamConsts& A, int grad_dtype, bool accumulate,
+                              float lambda, uint64_t seed, uint32_t step, const float* dev_scale, bool runs, hipStream_t stream);
 // Squared norm of the simulated step's expert gradient over the list: one fp32 partial per
-// one-wave block of kNormQuads quads per thread (kNormPartialsPerChunk per chunk), their fp64 block
+// one-wave block of kNormQuads quads per thread (one segment), their fp64 block
 // sums (at most kNormSums doubles), then sumsq and/or the clipping factor.
 constexpr int kNormQuads = 8;
-constexpr uint32_t kNormPartialsPerChunk = (uint32_t)tiles_per_chunk(kNormQuads);
+static_assert(tile_elems(kNormQuads) == kSegment, "one norm partial per segment");
 constexpr uint32_t kNormSums = 256;
-hipError_t launch_sqnorm_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
+hipError_t launch_sqnorm_multi(const TensorRec* recs, const ParamRec* prms, const ChunkTable& table,
                                float* partials, double* sums, int grad_dtype, bool accumulate, float lambda,
                                uint64_t seed, uint32_t step, double* sumsq, float* clip_coef, float max_norm,
                                hipStream_t stream);
@@ -169,11 +199,11 @@ hipError_t launch_sqnorm_multi(const TensorRec* recs, const ParamRec* prms, cons
 // `state`; the optimizer's learning rate and step count from `adam_state`, turned into the step's
 // constants in `consts` (device memory of the plan) by a one-thread launch ahead of the update.
 hipError_t launch_sqnorm_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
-                                   const uint2* chunks, uint32_t nchunks, float* partials, double* sums,
+                                   const ChunkTable& table, float* partials, double* sums,
                                    int grad_dtype, bool accumulate, float lambda, const StepState* state,
                                    double* sumsq, float* clip_coef, float max_norm, hipStream_t stream);
 hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, const ParamRec* prms,
-                                  const ScaleRec* scales, const uint2* chunks, uint32_t nchunks, const AdamHyper& h,
+                                  const ScaleRec* scales, const ChunkTable& table, const AdamHyper& h,
                                   const AdamStepState* adam_state, AdamConsts* consts, int grad_dtype,
                                   bool accumulate, float lambda, const StepState* state, const float* dev_scale,
                                   bool runs, hipStream_t stream);
@@ -240,7 +270,7 @@ struct MergeArgs {
 hipError_t launch_merge_one(const TensorRec& rec, const MergeArgs& args, int nexp, int expert_dtype, int theta0_dtype,
                             int out_dtype, bool plain, bool runs, hipStream_t stream);
 hipError_t launch_merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
-                              const uint2* chunks, uint32_t nchunks, int nexp, int expert_dtype, int theta0_dtype,
+                              const ChunkTable& table, int nexp, int expert_dtype, int theta0_dtype,
                               int out_dtype, bool plain, bool runs, hipStream_t stream);
 
 // Plain streaming copy of n16 16-byte vectors (the measured HBM reference).

@@ -145,27 +145,26 @@ template <typename TE, typename T0, typename TO, int Q, bool AHEAD, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_merge_one(TensorRec R, MergeArgs A, int nexp) {
   raise_priority();
   constexpr int64_t tile = tile_elems(Q);
-  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(Q)) * tile;
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, gridDim.x, tiles_per_chunk(Q)) * tile;
   merge_tile<TE, T0, TO, Q, AHEAD>(
       advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)), R.elem_offset + (uint64_t)begin,
       tile_len(R.n, begin, tile), begin == 0 ? R.sflags >> kHeadShift : 0u, R.tensor_id, (R.sflags & kVecMerge) != 0,
       nexp, [&](int j) { return advance<TE>(A.x[j], begin); }, [&](int j) { return A.r[j]; });
 }
 
-template <typename TE, typename T0, typename TO, int Q, bool AHEAD, bool RUNS>
+template <typename TE, typename T0, typename TO, int Q, bool AHEAD, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_merge_multi(const TensorRec* __restrict__ recs,
                                                         const void* const* __restrict__ experts,
                                                         const MergeRec* __restrict__ terms,
-                                                        const uint2* __restrict__ chunks, int nexp) {
+                                                        const uint2* __restrict__ entries, uint32_t chunks,
+                                                        int nexp) {
   raise_priority();
   constexpr int64_t tile = tile_elems(Q);
-  constexpr uint32_t tpc = tiles_per_chunk(Q);
-  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
-  const uint2 ch = chunks[block / tpc];
-  const TensorRec R = recs[ch.x];
-  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(block % tpc) * tile;
-  if (begin >= R.n) return;  // unused tile of a tensor's last chunk
-  const size_t row = (size_t)ch.x * (size_t)nexp;
+  const ListBlock B = list_block<Q, ORDER>(entries, chunks);
+  const TensorRec R = recs[B.tensor];
+  const int64_t begin = (int64_t)B.tile * tile;
+  if (begin >= R.n) return;  // unused tile of a tensor's last segment
+  const size_t row = (size_t)B.tensor * (size_t)nexp;
   merge_tile<TE, T0, TO, Q, AHEAD>(
       advance<T0>(R.theta0, begin), const_cast<void*>(advance<TO>(R.out, begin)), R.elem_offset + (uint64_t)begin,
       tile_len(R.n, begin, tile), begin == 0 ? R.sflags >> kHeadShift : 0u, R.tensor_id, (R.sflags & kVecMerge) != 0,
@@ -194,15 +193,12 @@ static hipError_t merge_one_as(const TensorRec& rec, const MergeArgs& args, int 
 
 template <typename TE, typename T0, typename TO, int Q, bool AHEAD>
 static hipError_t merge_multi_as(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
-                                 const uint2* chunks, uint32_t nchunks, int nexp, uint32_t lds, bool runs,
+                                 const ChunkTable& table, int nexp, uint32_t lds, bool runs,
                                  hipStream_t stream) {
-  constexpr uint32_t tpc = tiles_per_chunk(Q);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    with_flag(runs, [&](auto rn) {
-      k_merge_multi<TE, T0, TO, Q, AHEAD, decltype(rn)::value>
-          <<<grid, block, lds, stream>>>(recs, experts, terms, chunks + first, nexp);
-    });
+  return for_table<Q>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
+    const dim3 block(kBlock);
+    k_merge_multi<TE, T0, TO, Q, AHEAD, decltype(order)::value>
+        <<<grid, block, lds, stream>>>(recs, experts, terms, entries, chunks, nexp);
   });
 }
 
@@ -246,11 +242,11 @@ static hipError_t merge_one(const TensorRec& rec, const MergeArgs& args, int nex
 
 template <typename TE, typename T0, typename TO>
 static hipError_t merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
-                              const uint2* chunks, uint32_t nchunks, int nexp, bool plain, bool runs,
+                              const ChunkTable& table, int nexp, bool plain, bool runs,
                               hipStream_t stream) {
-  const uint64_t bytes = merge_bytes<TE, T0, TO>((uint64_t)nchunks * kChunk, nexp);
+  const uint64_t bytes = merge_bytes<TE, T0, TO>(table_elems(table), nexp);
   return merge_form<TE>(nexp, plain, bytes, [&](auto q, auto ahead, uint32_t lds) {
-    return merge_multi_as<TE, T0, TO, q(), ahead()>(recs, experts, terms, chunks, nchunks, nexp, lds, runs, stream);
+    return merge_multi_as<TE, T0, TO, q(), ahead()>(recs, experts, terms, table, nexp, lds, runs, stream);
   });
 }
 
@@ -273,9 +269,9 @@ hipError_t launch_merge_one(const TensorRec& rec, const MergeArgs& args, int nex
 }
 
 hipError_t launch_merge_multi(const TensorRec* recs, const void* const* experts, const MergeRec* terms,
-                              const uint2* chunks, uint32_t nchunks, int nexp, int expert_dtype, int theta0_dtype,
+                              const ChunkTable& table, int nexp, int expert_dtype, int theta0_dtype,
                               int out_dtype, bool plain, bool runs, hipStream_t stream) {
-  SMAT_MERGE_DISPATCH(merge_multi, recs, experts, terms, chunks, nchunks, nexp, plain, runs, stream)
+  SMAT_MERGE_DISPATCH(merge_multi, recs, experts, terms, table, nexp, plain, runs, stream)
 }
 
 #undef SMAT_MERGE_DISPATCH

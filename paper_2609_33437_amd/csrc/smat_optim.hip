@@ -117,58 +117,56 @@ __global__ __launch_bounds__(kBlock) void k_adamw_one(TensorRec R, AdamRec S, Pa
                                                       uint32_t step, float lambda, const float* dev_scale) {
   constexpr int64_t tile = tile_elems(kAdamQuads);
   if (dev_scale) A.grad_scale *= *dev_scale;
-  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, tiles_per_chunk(kAdamQuads)) * tile;
+  const int64_t begin = (int64_t)block_order<RUNS>(blockIdx.x, gridDim.x, tiles_per_chunk(kAdamQuads)) * tile;
   Tile T = tensor_tile<float, float>(R, begin, tile);
   T.grad_sim = advance<TG>(R.grad_sim, begin);
   T.grad_theta = R.grad_theta ? R.grad_theta + begin : nullptr;
   adamw_tile<TG, kAdamQuads, ACC>(T, S.exp_avg + begin, S.exp_avg_sq + begin, P, A, K, step, lambda);
 }
 
-template <typename TG, bool ACC, bool RUNS>
+template <typename TG, bool ACC, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_adamw_multi(const TensorRec* __restrict__ recs,
                                                         const AdamRec* __restrict__ states,
                                                         const ParamRec* __restrict__ prms,
-                                                        const uint2* __restrict__ chunks, AdamConsts A, PhiloxKeys K,
+                                                        const uint2* __restrict__ entries, uint32_t chunks,
+                                                        AdamConsts A, PhiloxKeys K,
                                                         uint32_t step, float lambda, const float* dev_scale) {
   constexpr int64_t tile = tile_elems(kAdamQuads);
   if (dev_scale) A.grad_scale *= *dev_scale;
-  constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
-  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
-  const uint2 ch = chunks[block / tpc];
-  const TensorRec R = recs[ch.x];
-  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(block % tpc) * tile;
-  const Tile T = list_tile<float, float, TG>(R, ch.y, block % tpc, tile);
+  const ListBlock B = list_block<kAdamQuads, ORDER>(entries, chunks);
+  const TensorRec R = recs[B.tensor];
+  const int64_t begin = (int64_t)B.tile * tile;
+  const Tile T = list_tile<float, float, TG>(R, B.tile, tile);
   if (T.len == 0) return;
-  const AdamRec S = states[ch.x];
-  adamw_tile<TG, kAdamQuads, ACC>(T, S.exp_avg + begin, S.exp_avg_sq + begin, rec_at(prms, ch.x), A, K, step, lambda);
+  const AdamRec S = states[B.tensor];
+  adamw_tile<TG, kAdamQuads, ACC>(T, S.exp_avg + begin, S.exp_avg_sq + begin, rec_at(prms, B.tensor), A, K, step,
+                                  lambda);
 }
 
 // The same list kernel with seed, step and scale read from device memory (each tensor's coefficient
 // formed as the simulate forms it) and the step's constants from `Ad`, which k_adam_consts writes
 // from the device-side learning rate and step count: a captured graph replays it for every step.
-template <typename TG, bool ACC, bool RUNS>
+template <typename TG, bool ACC, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_adamw_multi_dev(const TensorRec* __restrict__ recs,
                                                             const AdamRec* __restrict__ states,
                                                             const ParamRec* __restrict__ prms,
                                                             const ScaleRec* __restrict__ scales,
-                                                            const uint2* __restrict__ chunks,
+                                                            const uint2* __restrict__ entries, uint32_t chunks,
                                                             const AdamConsts* __restrict__ Ad,
                                                             const StepState* __restrict__ state, float lambda,
                                                             const float* dev_scale) {
   constexpr int64_t tile = tile_elems(kAdamQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
-  const uint32_t block = block_order<RUNS>(blockIdx.x, tpc);
-  const uint2 ch = chunks[block / tpc];
-  const TensorRec R = recs[ch.x];
-  const int64_t begin = (int64_t)ch.y * kChunk + (int64_t)(block % tpc) * tile;
-  const Tile T = list_tile<float, float, TG>(R, ch.y, block % tpc, tile);
+  const ListBlock B = list_block<kAdamQuads, ORDER>(entries, chunks);
+  const TensorRec R = recs[B.tensor];
+  const int64_t begin = (int64_t)B.tile * tile;
+  const Tile T = list_tile<float, float, TG>(R, B.tile, tile);
   if (T.len == 0) return;
   AdamConsts A = *Ad;
   if (dev_scale) A.grad_scale *= *dev_scale;
   const StepState S = *state;
-  ParamRec P = prms[ch.x];
-  P.t = device_coefficient(S.scale, scales[ch.x]);
-  const AdamRec M = states[ch.x];
+  ParamRec P = prms[B.tensor];
+  P.t = device_coefficient(S.scale, scales[B.tensor]);
+  const AdamRec M = states[B.tensor];
   adamw_tile<TG, kAdamQuads, ACC>(T, M.exp_avg + begin, M.exp_avg_sq + begin, P, A, philox_keys(S.seed), S.step, lambda);
 }
 
@@ -299,36 +297,36 @@ __device__ __forceinline__ T block_sum(T v) {
   }
 }
 
-template <typename TG, bool ACC>
+template <typename TG, bool ACC, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_sqnorm_multi(const TensorRec* __restrict__ recs,
                                                          const ParamRec* __restrict__ prms,
-                                                         const uint2* __restrict__ chunks, float* partials,
+                                                         const uint2* __restrict__ entries, uint32_t chunks,
+                                                         float* partials,
                                                          uint64_t seed, uint32_t step, float lambda) {
   constexpr int64_t tile = tile_elems(kNormQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kNormQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
-  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, blockIdx.x % tpc, tile);
+  const ListBlock B = list_block<kNormQuads, ORDER>(entries, chunks);
+  const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
   float s = 0.0f;
-  if (T.len > 0) s = tile_sqnorm<TG, ACC>(T, rec_at(prms, ch.x), seed, step, lambda);
+  if (T.len > 0) s = tile_sqnorm<TG, ACC>(T, rec_at(prms, B.tensor), seed, step, lambda);
   s = block_sum<float, kBlock>(s);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-template <typename TG, bool ACC>
+template <typename TG, bool ACC, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_sqnorm_multi_dev(const TensorRec* __restrict__ recs,
                                                              const ParamRec* __restrict__ prms,
                                                              const ScaleRec* __restrict__ scales,
-                                                             const uint2* __restrict__ chunks, float* partials,
+                                                             const uint2* __restrict__ entries, uint32_t chunks,
+                                                             float* partials,
                                                              const StepState* __restrict__ state, float lambda) {
   constexpr int64_t tile = tile_elems(kNormQuads);
-  constexpr uint32_t tpc = tiles_per_chunk(kNormQuads);
-  const uint2 ch = chunks[blockIdx.x / tpc];
-  const Tile T = list_tile<float, float, TG>(rec_at(recs, ch.x), ch.y, blockIdx.x % tpc, tile);
+  const ListBlock B = list_block<kNormQuads, ORDER>(entries, chunks);
+  const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
   float s = 0.0f;
   if (T.len > 0) {
     const StepState S = *state;
-    ParamRec P = prms[ch.x];
-    P.t = device_coefficient(S.scale, scales[ch.x]);
+    ParamRec P = prms[B.tensor];
+    P.t = device_coefficient(S.scale, scales[B.tensor]);
     s = tile_sqnorm<TG, ACC>(T, P, S.seed, S.step, lambda);
   }
   s = block_sum<float, kBlock>(s);
@@ -396,21 +394,19 @@ hipError_t launch_adamw_one(const TensorRec& rec, const AdamRec& st, const Param
   });
 }
 
-hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, const ParamRec* prms, const uint2* chunks,
-                              uint32_t nchunks, const AdamConsts& A, int grad_dtype, bool accumulate, float lambda,
-                              uint64_t seed, uint32_t step, const float* dev_scale, bool runs, hipStream_t stream) {
+hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, const ParamRec* prms,
+                              const ChunkTable& table, const AdamConsts& A, int grad_dtype, bool accumulate,
+                              float lambda, uint64_t seed, uint32_t step, const float* dev_scale, bool runs,
+                              hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
-  const uint32_t lds = adamw_lds(grad_dtype, accumulate, (uint64_t)nchunks * kChunk);
-  constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
+  const uint32_t lds = adamw_lds(grad_dtype, accumulate, table_elems(table));
+  return for_table<kAdamQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order,
+                                                uint64_t) {
+    const dim3 block(kBlock);
     with_type(grad_dtype, [&](auto tg) {
       with_flag(accumulate, [&](auto acc) {
-        with_flag(runs, [&](auto rn) {
-          k_adamw_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
-              <<<grid, block, lds, stream>>>(recs, states, prms, ch, A, K, step, lambda, dev_scale);
-        });
+        k_adamw_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
+            <<<grid, block, lds, stream>>>(recs, states, prms, entries, chunks, A, K, step, lambda, dev_scale);
       });
     });
   });
@@ -427,70 +423,62 @@ static hipError_t launch_sqnorm_reduce(const float* partials, uint32_t npart, do
   return hipGetLastError();
 }
 
-// One partial per block: a piece starting at chunk `first` writes partials from first * kNormPartialsPerChunk.
-hipError_t launch_sqnorm_multi(const TensorRec* recs, const ParamRec* prms, const uint2* chunks, uint32_t nchunks,
+// One partial per block, in table order: a piece starting at segment `first` writes partials from there.
+hipError_t launch_sqnorm_multi(const TensorRec* recs, const ParamRec* prms, const ChunkTable& table,
                                float* partials, double* sums, int grad_dtype, bool accumulate, float lambda,
                                uint64_t seed, uint32_t step, double* sumsq, float* clip_coef, float max_norm,
                                hipStream_t stream) {
-  constexpr uint32_t tpc = kNormPartialsPerChunk;
-  const hipError_t e = for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    float* part = partials + first * tpc;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (grad_dtype == 1 && accumulate)
-      k_sqnorm_multi<Bf16, true><<<grid, block, 0, stream>>>(recs, prms, ch, part, seed, step, lambda);
-    else if (grad_dtype == 1)
-      k_sqnorm_multi<Bf16, false><<<grid, block, 0, stream>>>(recs, prms, ch, part, seed, step, lambda);
-    else if (accumulate)
-      k_sqnorm_multi<float, true><<<grid, block, 0, stream>>>(recs, prms, ch, part, seed, step, lambda);
-    else
-      k_sqnorm_multi<float, false><<<grid, block, 0, stream>>>(recs, prms, ch, part, seed, step, lambda);
+  const hipError_t e = for_table<kNormQuads>(table, false, [&](const uint2* entries, uint32_t chunks, dim3 grid,
+                                                               auto order, uint64_t first) {
+    float* part = partials + first;
+    const dim3 block(kBlock);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(accumulate, [&](auto acc) {
+        k_sqnorm_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
+            <<<grid, block, 0, stream>>>(recs, prms, entries, chunks, part, seed, step, lambda);
+      });
+    });
   });
   if (e != hipSuccess) return e;
-  return launch_sqnorm_reduce(partials, nchunks * tpc, sums, sumsq, clip_coef, max_norm, stream);
+  return launch_sqnorm_reduce(partials, (uint32_t)table_segments(table), sums, sumsq, clip_coef, max_norm, stream);
 }
 
 hipError_t launch_sqnorm_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
-                                   const uint2* chunks, uint32_t nchunks, float* partials, double* sums,
+                                   const ChunkTable& table, float* partials, double* sums,
                                    int grad_dtype, bool accumulate, float lambda, const StepState* state,
                                    double* sumsq, float* clip_coef, float max_norm, hipStream_t stream) {
-  constexpr uint32_t tpc = kNormPartialsPerChunk;
-  const hipError_t e = for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    float* part = partials + first * tpc;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
-    if (grad_dtype == 1 && accumulate)
-      k_sqnorm_multi_dev<Bf16, true><<<grid, block, 0, stream>>>(recs, prms, scales, ch, part, state, lambda);
-    else if (grad_dtype == 1)
-      k_sqnorm_multi_dev<Bf16, false><<<grid, block, 0, stream>>>(recs, prms, scales, ch, part, state, lambda);
-    else if (accumulate)
-      k_sqnorm_multi_dev<float, true><<<grid, block, 0, stream>>>(recs, prms, scales, ch, part, state, lambda);
-    else
-      k_sqnorm_multi_dev<float, false><<<grid, block, 0, stream>>>(recs, prms, scales, ch, part, state, lambda);
+  const hipError_t e = for_table<kNormQuads>(table, false, [&](const uint2* entries, uint32_t chunks, dim3 grid,
+                                                               auto order, uint64_t first) {
+    float* part = partials + first;
+    const dim3 block(kBlock);
+    with_type(grad_dtype, [&](auto tg) {
+      with_flag(accumulate, [&](auto acc) {
+        k_sqnorm_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
+            <<<grid, block, 0, stream>>>(recs, prms, scales, entries, chunks, part, state, lambda);
+      });
+    });
   });
   if (e != hipSuccess) return e;
-  return launch_sqnorm_reduce(partials, nchunks * tpc, sums, sumsq, clip_coef, max_norm, stream);
+  return launch_sqnorm_reduce(partials, (uint32_t)table_segments(table), sums, sumsq, clip_coef, max_norm, stream);
 }
 
 hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, const ParamRec* prms,
-                                  const ScaleRec* scales, const uint2* chunks, uint32_t nchunks, const AdamHyper& h,
+                                  const ScaleRec* scales, const ChunkTable& table, const AdamHyper& h,
                                   const AdamStepState* adam_state, AdamConsts* consts, int grad_dtype,
                                   bool accumulate, float lambda, const StepState* state, const float* dev_scale,
                                   bool runs, hipStream_t stream) {
   k_adam_consts<<<dim3(1), dim3(64), 0, stream>>>(adam_state, h, consts);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const uint32_t lds = adamw_lds(grad_dtype, accumulate, (uint64_t)nchunks * kChunk);
-  constexpr uint32_t tpc = tiles_per_chunk(kAdamQuads);
-  return for_pieces(nchunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const uint2* ch = chunks + first;
-    const dim3 grid((uint32_t)count * tpc), block(kBlock);
+  const uint32_t lds = adamw_lds(grad_dtype, accumulate, table_elems(table));
+  return for_table<kAdamQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order,
+                                                uint64_t) {
+    const dim3 block(kBlock);
     with_type(grad_dtype, [&](auto tg) {
       with_flag(accumulate, [&](auto acc) {
-        with_flag(runs, [&](auto rn) {
-          k_adamw_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(rn)::value>
-              <<<grid, block, lds, stream>>>(recs, states, prms, scales, ch, consts, state, lambda, dev_scale);
-        });
+        k_adamw_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
+            <<<grid, block, lds, stream>>>(recs, states, prms, scales, entries, chunks, consts, state, lambda,
+                                           dev_scale);
       });
     });
   });

@@ -65,21 +65,42 @@ __device__ __forceinline__ const R& rec_at(const R* base, uint32_t i) {
 // to 32 bytes off a line, 1.30 -> 1.13 ms 64 off, but 1.088 -> 1.115 on it (the 1.5B list: 3-7 % slower);
 // optimizer step 2.65 -> 2.35, 3-expert merge 0.74 -> 0.67.
 template <bool RUNS>
-__device__ __forceinline__ uint32_t block_order(uint32_t b, uint32_t tpc) {
+__device__ __forceinline__ uint32_t block_order(uint32_t b, uint32_t blocks, uint32_t tpc) {
   const uint32_t group = 8u * tpc;
-  if (!RUNS || b >= gridDim.x / group * group) return b;
+  if (!RUNS || b >= blocks / group * group) return b;
   return b / group * group + (b % 8u) * tpc + b / 8u % tpc;
 }
 
-// Tile b of a list launch: tile (b mod tiles-per-chunk) of chunk (b / tiles-per-chunk), the chunk
-// table giving (tensor index, chunk index within the tensor).  The chunk table (8 B per 16K
-// elements) and the tensor records (64 B per tensor) are small enough to stay in L2 while the
-// kernel streams the tensors.  len is 0 when the tile lies past the end of a tensor.  It comes from
+// The tensor and tile of a block of a list launch; `chunks` is read by kMixed only.  The table (8 B per
+// entry) and the tensor records (64 B per tensor) are small enough to stay in L2 while the kernel
+// streams the tensors.
+struct ListBlock {
+  uint32_t tensor, tile;
+};
+template <int Q, int ORDER>
+__device__ __forceinline__ ListBlock list_block(const uint2* entries, uint32_t chunks) {
+  constexpr uint32_t tps = tiles_per_segment(Q), tpc = tiles_per_chunk(Q);
+  uint32_t b = blockIdx.x;
+  if (ORDER == kMixed) {
+    const uint32_t count = chunks & ~kMixedRuns, blocks = count * tpc;
+    if (b >= blocks) {
+      b -= blocks;
+      const uint2 e = entries[count + b / tps];
+      return {e.x, e.y * tps + b % tps};
+    }
+    if (chunks & kMixedRuns) b = block_order<true>(b, blocks, tpc);
+  } else {
+    b = block_order<ORDER == kRuns>(b, gridDim.x, tpc);
+  }
+  const uint2 e = entries[b / tpc];
+  return {e.x, e.y * tps + b % tpc};
+}
+
+// Tile ti of a list's tensor.  len is 0 when the tile lies past the end of the tensor.  It comes from
 // 32-bit scalar arithmetic: a plan holds fewer than 2^31 one-quad tiles in all, so a tile's index
 // within its tensor and the tensor's count of whole tiles stay below 2^31.
 template <typename T0, typename TO, typename TG>
-__device__ __forceinline__ Tile list_tile(const TensorRec& R, uint32_t chunk, uint32_t tile_in_chunk, int64_t tile) {
-  const uint32_t ti = chunk * (uint32_t)(kChunk / tile) + tile_in_chunk;
+__device__ __forceinline__ Tile list_tile(const TensorRec& R, uint32_t ti, int64_t tile) {
   const uint64_t n = (uint64_t)R.n;
   const uint32_t whole = (uint32_t)(n / (uint64_t)tile), tail = (uint32_t)n % (uint32_t)tile;
   const int64_t begin = (int64_t)ti * tile;
