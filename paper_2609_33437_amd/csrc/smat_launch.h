@@ -184,7 +184,8 @@ hipError_t launch_adamw_one(const TensorRec& rec, const AdamRec& st, const Param
                             const float* dev_scale, bool runs, hipStream_t stream);
 hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, const ParamRec* prms,
                               const ChunkTable& table, const AdamConsts& A, int grad_dtype, bool accumulate,
-                              float lambda, uint64_t seed, uint32_t step, const float* dev_scale, bool runs, hipStream_t stream);
+                              float lambda, uint64_t seed, uint32_t step, const float* dev_scale, bool runs,
+                              hipStream_t stream);
 // Squared norm of the simulated step's expert gradient over the list: one fp32 partial per
 // one-wave block of kNormQuads quads per thread (one segment), their fp64 block
 // sums (at most kNormSums doubles), then sumsq and/or the clipping factor.

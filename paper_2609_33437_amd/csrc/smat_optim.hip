@@ -167,7 +167,8 @@ __global__ __launch_bounds__(kBlock) void k_adamw_multi_dev(const TensorRec* __r
   ParamRec P = prms[B.tensor];
   P.t = device_coefficient(S.scale, scales[B.tensor]);
   const AdamRec M = states[B.tensor];
-  adamw_tile<TG, kAdamQuads, ACC>(T, M.exp_avg + begin, M.exp_avg_sq + begin, P, A, philox_keys(S.seed), S.step, lambda);
+  adamw_tile<TG, kAdamQuads, ACC>(T, M.exp_avg + begin, M.exp_avg_sq + begin, P, A, philox_keys(S.seed), S.step,
+                                  lambda);
 }
 
 // One thread forms the step's constants from the learning rate and step count in device memory.
@@ -188,7 +189,9 @@ __global__ __launch_bounds__(64) void k_adam_consts(const AdamStepState* __restr
 // and adds the squares; short-lived blocks let the chip overlap one block's draws with another's
 // loads.  Each block writes one fp32 partial (zero past a tensor's end); the partials are then added
 // in fp64 in a fixed order (at most kNormSums blocks over contiguous ranges, then one block), so the
-// result does not depend on scheduling and is the same from run to run.
+// result does not depend on scheduling and is the same from run to run.  Bound by the draws' vector
+// instructions (8 x 38 a wave for Philox of about 490), so a tile of whole quads runs without clamps and
+// guards: 590 -> 541 us over 1.54e9 bf16 elements (5.7 TB/s).
 constexpr int kSumBlock = 256;
 static_assert(kNormSums <= (uint32_t)kSumBlock, "the final block holds one block sum per thread");
 
@@ -234,13 +237,15 @@ __device__ __forceinline__ float tile_sqnorm(const Tile& T, const ParamRec& P, u
     for (int u = 0; u < kNormQuads; ++u) edge(u * kBlock + threadIdx.x);
     return s;
   }
-  const WholeQuads W = whole_quads(len, T.head);
-  if (W.any()) {
+  // FULL: every quad of the tile is whole, so no lane's address is clamped and no quad tested
+  auto quads = [&](auto full, const WholeQuads W) {
+    constexpr bool FULL = decltype(full)::value;
     typename QuadIO<TG>::Raw rg[kNormQuads];
     typename QuadIO<float>::Raw ra[kNormQuads];
 #pragma unroll
     for (int u = 0; u < kNormQuads; ++u) {
-      const uint32_t qc = W.clamp(u * kBlock + threadIdx.x);
+      const uint32_t q = u * kBlock + threadIdx.x;
+      const uint32_t qc = FULL ? q : W.clamp(q);
       rg[u] = QuadIO<TG>::load_raw(gs, qc);
       if (ACC) ra[u] = QuadIO<float>::load_raw(ga, qc);
     }
@@ -260,8 +265,7 @@ __device__ __forceinline__ float tile_sqnorm(const Tile& T, const ParamRec& P, u
     }
 #pragma unroll
     for (int u = 0; u < kNormQuads; ++u) {
-      const uint32_t q = u * kBlock + threadIdx.x;
-      if (W.has(q)) {
+      if (FULL || W.has(u * kBlock + threadIdx.x)) {
         float a[4], b[4] = {0.f, 0.f, 0.f, 0.f};
         QuadIO<TG>::unpack(rg[u], a);
         if (ACC) QuadIO<float>::unpack(ra[u], b);
@@ -273,7 +277,13 @@ __device__ __forceinline__ float tile_sqnorm(const Tile& T, const ParamRec& P, u
         }
       }
     }
+  };
+  const WholeQuads W = whole_quads(len, T.head);
+  if (W.end == kNormQuads * kBlock && W.first == 0) {
+    quads(std::true_type(), W);
+    return s;
   }
+  if (W.any()) quads(std::false_type(), W);
   for_edges(len, T.head, edge);
   return s;
 }
@@ -343,18 +353,34 @@ __global__ __launch_bounds__(kSumBlock) void k_sum_partials(const float* __restr
   if (threadIdx.x == 0) sums[blockIdx.x] = s;
 }
 
-// Total of the m block sums; the squared norm and/or the clipping factor min(1, max_norm /
-// (norm + 1e-6)), the rule of torch.nn.utils.clip_grad_norm_ for the L2 norm.
+// The squared norm and/or the clipping factor min(1, max_norm / (norm + 1e-6)), the rule of
+// torch.nn.utils.clip_grad_norm_ for the L2 norm.
+__device__ __forceinline__ void write_norm(double s, double* sumsq, float* clip_coef, float max_norm) {
+  if (sumsq) *sumsq = s;
+  if (clip_coef) {
+    const double c = (double)max_norm / (sqrt(s) + 1e-6);
+    *clip_coef = (float)(c < 1.0 ? c : 1.0);
+  }
+}
+
+// Total of the m block sums.
 __global__ __launch_bounds__(kSumBlock) void k_sqnorm_finalize(const double* __restrict__ sums, uint32_t m,
                                                                double* sumsq, float* clip_coef, float max_norm) {
   const double s = block_sum<double, kSumBlock>(threadIdx.x < m ? sums[threadIdx.x] : 0.0);
-  if (threadIdx.x == 0) {
-    if (sumsq) *sumsq = s;
-    if (clip_coef) {
-      const double c = (double)max_norm / (sqrt(s) + 1e-6);
-      *clip_coef = (float)(c < 1.0 ? c : 1.0);
-    }
-  }
+  if (threadIdx.x == 0) write_norm(s, sumsq, clip_coef, max_norm);
+}
+
+// Both at once, one block over all partials, for lists of up to 8,192 (16.8M elements): the clipped step of
+// 2.1M elements 17.5 -> 15.9 us, of 9.6M 53.1 -> 52.1; from 15,000 on the two launches are as fast.
+constexpr int kFinishBlock = 1024;
+constexpr uint32_t kFinishPartials = 8192;
+__global__ __launch_bounds__(kFinishBlock) void k_sqnorm_finish(const float* __restrict__ partials, uint32_t n,
+                                                                double* sumsq, float* clip_coef, float max_norm) {
+  double s = 0.0;
+#pragma unroll 8
+  for (uint32_t i = threadIdx.x; i < n; i += kFinishBlock) s += (double)partials[i];
+  s = block_sum<double, kFinishBlock>(s);
+  if (threadIdx.x == 0) write_norm(s, sumsq, clip_coef, max_norm);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -416,6 +442,10 @@ hipError_t launch_adamw_multi(const TensorRec* recs, const AdamRec* states, cons
 // outputs.
 static hipError_t launch_sqnorm_reduce(const float* partials, uint32_t npart, double* sums, double* sumsq,
                                        float* clip_coef, float max_norm, hipStream_t stream) {
+  if (npart <= kFinishPartials) {
+    k_sqnorm_finish<<<dim3(1), dim3(kFinishBlock), 0, stream>>>(partials, npart, sumsq, clip_coef, max_norm);
+    return hipGetLastError();
+  }
   const uint32_t per = (npart + kNormSums - 1) / kNormSums;
   const uint32_t m = per ? (npart + per - 1) / per : 0;
   if (m > 0) k_sum_partials<<<dim3(m), dim3(kSumBlock), 0, stream>>>(partials, npart, per, sums);
