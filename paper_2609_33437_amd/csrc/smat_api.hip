@@ -71,6 +71,7 @@ smat_status make_param(const smat_op_params& p, ParamRec* out, const char* where
   } else {
     r.flags |= smat::kFlagMask;
     r.thr = (uint32_t)std::floor((double)p.keep * 4294967296.0);
+    if (r.thr < smat::kSparseThr) r.flags |= smat::kFlagSparse;
     r.t = p.rescale ? (float)((double)p.s / (double)p.keep) : p.s;
   }
   if (p.sigma > 0.f) {

@@ -20,6 +20,7 @@ enum : uint32_t {
   kFlagNoise = 4u,    // sigma > 0: draw the noise
   kFlagUniform = 8u,  // uniform noise instead of Gaussian
   kFlagLaplace = 16u, // Laplace noise instead of Gaussian
+  kFlagSparse = 192u, // the mask keeps less than 1 in 8 (both kSector bits)
 };
 
 // Noise forms (smat_noise_kind).
@@ -37,6 +38,8 @@ enum NoiseKind : int { kGaussian = 0, kUniform = 1, kLaplace = 2 };
 // first one, n counts them, and bits kHeadShift.. of sflags hold head.  Quads then are Philox groups for
 // every offset; the first quad's leading `head` elements belong to nobody and are never accessed.
 enum : uint32_t { kVecSim = 1u, kVecBwd = 2u, kSimWhole = 32u };
+// theta, or grad_theta, begins on a 64-byte sector (as do its tiles).
+enum : uint32_t { kSectorSim = 64u, kSectorBwd = 128u };
 constexpr uint32_t kHeadShift = 8u;
 
 struct alignas(16) TensorRec {
@@ -377,6 +380,20 @@ __device__ __forceinline__ void philox_tile_pair(uint64_t p0, uint32_t hi, uint3
   }
   A = {c0a, c1a, c2a, c3a};
   B = {c0b, c1b, c2b, c3b};
+}
+
+// Sparse masks.  At a low keep probability a good part of the 64-byte sectors of an fp32 array (16
+// elements, four lanes' quads) hold no kept element: 1 in 5 at 0.1, 4 in 9 at 0.05, 3 in 4 at 0.02.  The
+// simulate need not read theta there, nor the accumulating backward grad_theta and g~, nor write.  The
+// draws then come before the loads, so below 1/8 it pays (a step of 1.54e9 elements: keep 0.02 4.10 ->
+// 3.27 ms, 0.05 4.11 -> 3.58, 0.1 4.13 -> 4.07, 0.12 4.15 -> 4.13) and above it is not worth it (0.15
+// 4.17 -> 4.16, 0.2 4.20 -> 4.23).  Only tensors that begin on a sector: a list packed off it lost 7 %.
+// One bit says both (of ParamRec::flags and TensorRec::sflags).
+constexpr uint32_t kSparseThr = 1u << 29;
+// Whether any of the four lanes of this lane's sector keeps an element.
+__device__ __forceinline__ bool sector_kept(const bool kept[4]) {
+  const uint64_t lanes = __ballot(kept[0] || kept[1] || kept[2] || kept[3]);
+  return ((lanes >> (threadIdx.x & 60u)) & 0xFu) != 0u;
 }
 
 __device__ __forceinline__ uint32_t pick(const Words& w, uint32_t lane) {

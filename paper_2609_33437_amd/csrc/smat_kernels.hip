@@ -77,41 +77,57 @@ __device__ __forceinline__ void simulate_tile_case(const Tile& T, const ParamRec
   // stores, to the same place, and no branch splits the phases.
   const uint32_t nq = len >> 2;
   const uint32_t q = min((uint32_t)threadIdx.x, nq - 1u);
+  bool kept[4] = {all_kept, all_kept, all_kept, all_kept};
+  float z[4];
+  auto draw = [&]() {
+    const TileGroups G = tile_groups(e0);
+    const uint64_t p0 = philox_p0(G.lo + q);
+    if (MASK && NOISE) {
+      Words wm, wn;
+      philox_tile_pair(p0, G.hi, tensor_id, cmask, cnoise, K, wm, wn);
+      kept[0] = wm.w0 < thr;
+      kept[1] = wm.w1 < thr;
+      kept[2] = wm.w2 < thr;
+      kept[3] = wm.w3 < thr;
+      quad_noise<KIND>(wn, z);
+    } else if (MASK) {
+      const Words w = philox_tile(p0, G.hi, tensor_id, cmask, K);
+      kept[0] = w.w0 < thr;
+      kept[1] = w.w1 < thr;
+      kept[2] = w.w2 < thr;
+      kept[3] = w.w3 < thr;
+    } else if (NOISE) {
+      quad_noise<KIND>(philox_tile(p0, G.hi, tensor_id, cnoise, K), z);
+    }
+  };
+  auto finish = [&](const typename QuadIO<float>::Raw& ra, const typename QuadIO<T0>::Raw& rb) {
+    float a[4], b[4], y[4];
+    QuadIO<float>::unpack(ra, a);
+    QuadIO<T0>::unpack(rb, b);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = sim_value(a[j], b[j], kept[j], t);
+    if (NOISE) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) y[j] = __builtin_fmaf(sigma, z[j], y[j]);
+    }
+    QuadIO<TO>::store(out, q, y);
+  };
+  if (MASK && (P.flags & T.sflags & kSectorSim)) {
+    // a sparse mask: theta is loaded after the draws, only the sectors that hold a kept element
+    const typename QuadIO<T0>::Raw rb = QuadIO<T0>::load_raw(t0, q);
+    normal_priority();
+    draw();
+    typename QuadIO<float>::Raw ra = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (sector_kept(kept)) ra = QuadIO<float>::load_raw(th, q);
+    finish(ra, rb);
+    return;
+  }
   const typename QuadIO<float>::Raw ra = QuadIO<float>::load_raw(th, q);
   const typename QuadIO<T0>::Raw rb = QuadIO<T0>::load_raw(t0, q);
   normal_priority();
-  const TileGroups G = tile_groups(e0);
-  const uint64_t p0 = philox_p0(G.lo + q);
-  bool kept[4] = {all_kept, all_kept, all_kept, all_kept};
-  float z[4];
-  if (MASK && NOISE) {
-    Words wm, wn;
-    philox_tile_pair(p0, G.hi, tensor_id, cmask, cnoise, K, wm, wn);
-    kept[0] = wm.w0 < thr;
-    kept[1] = wm.w1 < thr;
-    kept[2] = wm.w2 < thr;
-    kept[3] = wm.w3 < thr;
-    quad_noise<KIND>(wn, z);
-  } else if (MASK) {
-    const Words w = philox_tile(p0, G.hi, tensor_id, cmask, K);
-    kept[0] = w.w0 < thr;
-    kept[1] = w.w1 < thr;
-    kept[2] = w.w2 < thr;
-    kept[3] = w.w3 < thr;
-  } else if (NOISE) {
-    quad_noise<KIND>(philox_tile(p0, G.hi, tensor_id, cnoise, K), z);
-  }
+  draw();
   __builtin_amdgcn_sched_barrier(0);
-  float a[4], b[4], y[4];
-  QuadIO<float>::unpack(ra, a);
-  QuadIO<T0>::unpack(rb, b);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) y[j] = sim_value(a[j], b[j], kept[j], t);
-  if (NOISE) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) y[j] = __builtin_fmaf(sigma, z[j], y[j]);
-  }
-  QuadIO<TO>::store(out, q, y);
+  finish(ra, rb);
 }
 
 // Dispatch on the tensor's flags once per block: mask or not, and no noise or one of the three noise
@@ -192,8 +208,28 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
     for (int u = 0; u < Q; ++u) edge(u * kBlock + threadIdx.x);
     return;
   }
-  // loads first (clamped, unguarded), the regenerated mask while they are in flight, then the update
   const WholeQuads W = whole_quads(len, T.head);
+  if (ACC && Q == 1 && use_mask && (flags & T.sflags & kSectorBwd)) {
+    // a sparse mask first, then only the sectors of grad_theta that hold a kept element (and their g~):
+    // the rest is neither read nor written
+    const uint32_t q = threadIdx.x;
+    const TileGroups G = tile_groups(e0);
+    const Words w = philox_tile(philox_p0(G.lo + q), G.hi, tensor_id, cmask, K);
+    const bool kept[4] = {w.w0 < thr, w.w1 < thr, w.w2 < thr, w.w3 < thr};
+    if (sector_kept(kept) && W.has(q)) {
+      const typename QuadIO<TG>::Raw ra = QuadIO<TG>::load_raw(gs, q);
+      const typename QuadIO<float>::Raw rb = QuadIO<float>::load_raw(gt, q);
+      float a[4], b[4], o[4];
+      QuadIO<TG>::unpack(ra, a);
+      QuadIO<float>::unpack(rb, b);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] = kept[j] ? __builtin_fmaf(c, a[j], b[j]) : b[j];
+      QuadIO<float>::store(gt, q, o);
+    }
+    for_edges(len, T.head, edge);
+    return;
+  }
+  // loads first (clamped, unguarded), the regenerated mask while they are in flight, then the update
   if (W.any()) {
     typename QuadIO<TG>::Raw ra[Q];
     typename QuadIO<float>::Raw rb[Q];

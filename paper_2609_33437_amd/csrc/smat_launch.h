@@ -120,8 +120,8 @@ inline P* back_ptr(P* p, uint64_t elems, size_t bytes) {
 // Elements before a tensor's first one in its first Philox group.
 inline uint32_t group_head(uint64_t elem_offset) { return (uint32_t)elem_offset & 3u; }
 
-// A tensor's record as the kernels read it: from the start of its first Philox group, with the head in
-// sflags (see TensorRec::sflags in smat_device.h).  A record without a head is unchanged.
+// A tensor's record as the kernels read it: from the start of its first Philox group, with the head and
+// the sector bits in sflags (see TensorRec::sflags in smat_device.h).
 inline TensorRec device_rec(const TensorRec& R, int t0_dtype, int out_dtype, int g_dtype) {
   const uint32_t head = R.n > 0 ? group_head(R.elem_offset) : 0u;
   TensorRec r = R;
@@ -132,7 +132,8 @@ inline TensorRec device_rec(const TensorRec& R, int t0_dtype, int out_dtype, int
   r.grad_theta = back_ptr(R.grad_theta, head, 4);
   r.n = R.n + head;
   r.elem_offset = R.elem_offset - head;
-  r.sflags = R.sflags | (head << kHeadShift);
+  r.sflags = R.sflags | (head << kHeadShift) | (reinterpret_cast<uintptr_t>(r.theta) % 64 ? 0u : kSectorSim) |
+             (reinterpret_cast<uintptr_t>(r.grad_theta) % 64 ? 0u : kSectorBwd);
   return r;
 }
 inline AdamRec device_adam(const AdamRec& A, const TensorRec& R) {
