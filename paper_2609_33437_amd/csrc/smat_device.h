@@ -171,7 +171,7 @@ enum : uint32_t { kVecAdam = 4u, kVecAdamAcc = 8u };
 // that streams fastest on MI355X.
 constexpr int kBlock = 64;
 constexpr int kSimQuads = 1;
-constexpr int kBwdQuads = 1;
+constexpr int kBwdQuads = 1;  // 2 where a bf16 gradient is written, not accumulated (bwd_quads)
 constexpr int kAdamQuads = 1;
 constexpr int64_t kChunk = 16384;
 constexpr int64_t kSegment = 2048;

@@ -269,7 +269,6 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
   for_edges(len, T.head, edge);
 }
 
-// ---------------------------------------------------------------- kernels
 template <typename T0, typename TO, bool RUNS>
 __global__ __launch_bounds__(kBlock) void k_simulate_one(TensorRec R, ParamRec P, PhiloxKeys K, uint32_t step) {
   raise_priority();
@@ -303,17 +302,17 @@ __global__ __launch_bounds__(kBlock) void k_simulate_multi(const TensorRec* __re
   simulate_tile<T0, TO>(T, rec_at(prms, B.tensor), K, step);
 }
 
-template <typename TG, bool ACC, int ORDER>
+template <typename TG, bool ACC, int Q, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_backward_multi(const TensorRec* __restrict__ recs,
                                                            const ParamRec* __restrict__ prms,
                                                            const uint2* __restrict__ entries, uint32_t chunks,
                                                            PhiloxKeys K,
                                                            uint32_t step, float lambda) {
-  constexpr int64_t tile = tile_elems(kBwdQuads);
-  const ListBlock B = list_block<kBwdQuads, ORDER>(entries, chunks);
+  constexpr int64_t tile = tile_elems(Q);
+  const ListBlock B = list_block<Q, ORDER>(entries, chunks);
   const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
   if (T.len == 0) return;
-  backward_tile<TG, kBwdQuads, ACC>(T, rec_at(prms, B.tensor), K, step, lambda);
+  backward_tile<TG, Q, ACC>(T, rec_at(prms, B.tensor), K, step, lambda);
 }
 
 // The same list kernels with the step's seed, step and scale read from device memory, so that a
@@ -336,20 +335,20 @@ __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* 
   simulate_tile<T0, TO>(T, P, philox_keys(S.seed), S.step);
 }
 
-template <typename TG, bool ACC, int ORDER>
+template <typename TG, bool ACC, int Q, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_backward_multi_dev(const TensorRec* __restrict__ recs,
                                                                const ParamRec* __restrict__ prms,
                                                                const ScaleRec* __restrict__ scales,
                                                                const uint2* __restrict__ entries, uint32_t chunks,
                                                                const StepState* __restrict__ state, float lambda) {
-  constexpr int64_t tile = tile_elems(kBwdQuads);
-  const ListBlock B = list_block<kBwdQuads, ORDER>(entries, chunks);
+  constexpr int64_t tile = tile_elems(Q);
+  const ListBlock B = list_block<Q, ORDER>(entries, chunks);
   const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
   if (T.len == 0) return;
   const StepState S = *state;
   ParamRec P = rec_at(prms, B.tensor);
   P.t = device_coefficient(S.scale, rec_at(scales, B.tensor));
-  backward_tile<TG, kBwdQuads, ACC>(T, P, philox_keys(S.seed), S.step, lambda);
+  backward_tile<TG, Q, ACC>(T, P, philox_keys(S.seed), S.step, lambda);
 }
 
 // One thread advances the step state: step += increment modulo 2^30 (the range of the counter's step
@@ -442,17 +441,37 @@ hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, co
   });
 }
 
+// go(gradient type, ACC, quads per thread) of a list backward.  A wave of the overwriting backward on bf16
+// gradients loads 512 bytes a quad, so 32 of them keep only 16 KB in flight on a CU; two quads double
+// that: step of 518M elements 1.321 -> 1.298 ms, of 31.5M 76.0 -> 74.7 us.  In runs it gains nothing
+// (23M packed elements 58.1 -> 58.8 us), and every other backward, which loads 1-2 KB a quad, is 2-3 %
+// slower with two.
+template <typename F>
+static hipError_t backward_form(int grad_dtype, bool accumulate, bool runs, F&& go) {
+  hipError_t e = hipSuccess;
+  with_type(grad_dtype, [&](auto tg) {
+    with_flag(accumulate, [&](auto acc) {
+      if constexpr (std::is_same<typename decltype(tg)::type, Bf16>::value && !decltype(acc)::value) {
+        if (!runs) {
+          e = go(tg, acc, std::integral_constant<int, 2>());
+          return;
+        }
+      }
+      e = go(tg, acc, std::integral_constant<int, kBwdQuads>());
+    });
+  });
+  return e;
+}
+
 hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, const ChunkTable& table,
                                  int grad_dtype, bool accumulate, float lambda, uint64_t seed, uint32_t step,
                                  bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
-  return for_table<kBwdQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
-    const dim3 block(kBlock);
-    with_type(grad_dtype, [&](auto tg) {
-      with_flag(accumulate, [&](auto acc) {
-        k_backward_multi<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
-            <<<grid, block, 0, stream>>>(recs, prms, entries, chunks, K, step, lambda);
-      });
+  return backward_form(grad_dtype, accumulate, runs, [&](auto tg, auto acc, auto quads) {
+    constexpr int Q = decltype(quads)::value;
+    return for_table<Q>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
+      k_backward_multi<typename decltype(tg)::type, decltype(acc)::value, Q, decltype(order)::value>
+          <<<grid, dim3(kBlock), 0, stream>>>(recs, prms, entries, chunks, K, step, lambda);
     });
   });
 }
@@ -474,13 +493,11 @@ hipError_t launch_simulate_multi_dev(const TensorRec* recs, const ParamRec* prms
 hipError_t launch_backward_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
                                      const ChunkTable& table, int grad_dtype, bool accumulate,
                                      float lambda, const StepState* state, bool runs, hipStream_t stream) {
-  return for_table<kBwdQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
-    const dim3 block(kBlock);
-    with_type(grad_dtype, [&](auto tg) {
-      with_flag(accumulate, [&](auto acc) {
-        k_backward_multi_dev<typename decltype(tg)::type, decltype(acc)::value, decltype(order)::value>
-            <<<grid, block, 0, stream>>>(recs, prms, scales, entries, chunks, state, lambda);
-      });
+  return backward_form(grad_dtype, accumulate, runs, [&](auto tg, auto acc, auto quads) {
+    constexpr int Q = decltype(quads)::value;
+    return for_table<Q>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
+      k_backward_multi_dev<typename decltype(tg)::type, decltype(acc)::value, Q, decltype(order)::value>
+          <<<grid, dim3(kBlock), 0, stream>>>(recs, prms, scales, entries, chunks, state, lambda);
     });
   });
 }
