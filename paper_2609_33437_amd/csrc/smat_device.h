@@ -38,9 +38,10 @@ enum NoiseKind : int { kGaussian = 0, kUniform = 1, kLaplace = 2 };
 // first one, n counts them, and bits kHeadShift.. of sflags hold head.  Quads then are Philox groups for
 // every offset; the first quad's leading `head` elements belong to nobody and are never accessed.
 enum : uint32_t { kVecSim = 1u, kVecBwd = 2u, kSimWhole = 32u };
-// theta, or grad_theta, begins on a 64-byte sector (as do its tiles).
-enum : uint32_t { kSectorSim = 64u, kSectorBwd = 128u };
-constexpr uint32_t kHeadShift = 8u;
+// theta, or grad_theta, begins on a 64-byte sector (as do its tiles); kBwdWhole is kSimWhole's condition
+// for the backward's arrays.
+enum : uint32_t { kSectorSim = 64u, kSectorBwd = 128u, kBwdWhole = 256u };
+constexpr uint32_t kHeadShift = 30u;
 
 struct alignas(16) TensorRec {
   const float* theta;

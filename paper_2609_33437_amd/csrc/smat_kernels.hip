@@ -203,12 +203,15 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
     }
   };
 
-  if (!(T.sflags & kVecBwd) || groups_wrap(e0, Q * kBlock)) {
+  // one bit for a tensor whose tiles all are whole quads with a common high counter word: the conditions
+  // below cost the device-driven backward, whose waves also form their round keys, 1 %
+  const bool whole = (T.sflags & kBwdWhole) != 0;
+  if (!whole && (!(T.sflags & kVecBwd) || groups_wrap(e0, Q * kBlock))) {
 #pragma unroll
     for (int u = 0; u < Q; ++u) edge(u * kBlock + threadIdx.x);
     return;
   }
-  const WholeQuads W = whole_quads(len, T.head);
+  const WholeQuads W = whole_quads(len, whole ? 0u : T.head);
   if (ACC && Q == 1 && use_mask && (flags & T.sflags & kSectorBwd)) {
     // a sparse mask first, then only the sectors of grad_theta that hold a kept element (and their g~):
     // the rest is neither read nor written
@@ -230,7 +233,7 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
     return;
   }
   // loads first (clamped, unguarded), the regenerated mask while they are in flight, then the update
-  if (W.any()) {
+  auto quads = [&](const WholeQuads W) {
     typename QuadIO<TG>::Raw ra[Q];
     typename QuadIO<float>::Raw rb[Q];
 #pragma unroll
@@ -265,7 +268,12 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
         QuadIO<float>::store(gt, q, o);
       }
     }
+  };
+  if (whole) {
+    quads(WholeQuads{0u, len >> 2});
+    return;
   }
+  if (W.any()) quads(W);
   for_edges(len, T.head, edge);
 }
 
@@ -392,10 +400,19 @@ __global__ __launch_bounds__(kDebugBlock) void k_debug_draws(uint64_t seed, uint
 // one-tensor job into element ranges, a list job into ranges of its chunk table.
 static inline uint32_t blocks_for(int64_t n, int64_t per_block) { return (uint32_t)((n + per_block - 1) / per_block); }
 
+// Resident blocks of a simulate, by the bytes a wave loads: with fp32 theta0 2 KB, so 25 blocks of 32 (a
+// step of 305M fp32 elements with an overwriting backward 936 -> 930 us, of 518M with a bf16 buffer 2.067 ->
+// 2.047 ms); with bf16 theta0 1.5 KB, uncapped (25 blocks cost it 4 %).
+static inline uint32_t sim_lds(int theta0_dtype, int out_dtype, uint64_t elems) {
+  const size_t loaded = sizeof(float) + storage_bytes(theta0_dtype);
+  return lds_for_loads((uint32_t)(tile_elems(kSimQuads) * loaded), elems * (loaded + storage_bytes(out_dtype)));
+}
+
 hipError_t launch_simulate_one(const TensorRec& rec, const ParamRec& prm, int theta0_dtype, int out_dtype,
                                uint64_t seed, uint32_t step, bool runs, hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
   constexpr int64_t tile = tile_elems(kSimQuads);
+  const uint32_t lds = sim_lds(theta0_dtype, out_dtype, (uint64_t)rec.n);
   return for_pieces((uint64_t)rec.n, (uint64_t)max_grid_blocks(kBlock) * tile, [&](uint64_t off, uint64_t len) {
     const TensorRec r = rec_piece(rec, off, len, theta0_dtype, out_dtype, 0);
     const dim3 grid(blocks_for((int64_t)len, tile)), block(kBlock);
@@ -403,7 +420,7 @@ hipError_t launch_simulate_one(const TensorRec& rec, const ParamRec& prm, int th
       with_type(out_dtype, [&](auto to) {
         with_flag(runs, [&](auto rn) {
           k_simulate_one<typename decltype(t0)::type, typename decltype(to)::type, decltype(rn)::value>
-              <<<grid, block, 0, stream>>>(r, prm, K, step);
+              <<<grid, block, lds, stream>>>(r, prm, K, step);
         });
       });
     });
@@ -430,12 +447,13 @@ hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, co
                                  int theta0_dtype, int out_dtype, uint64_t seed, uint32_t step, bool runs,
                                  hipStream_t stream) {
   const PhiloxKeys K = philox_keys(seed);
+  const uint32_t lds = sim_lds(theta0_dtype, out_dtype, table_elems(table));
   return for_table<kSimQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
     const dim3 block(kBlock);
     with_type(theta0_dtype, [&](auto t0) {
       with_type(out_dtype, [&](auto to) {
         k_simulate_multi<typename decltype(t0)::type, typename decltype(to)::type, decltype(order)::value>
-            <<<grid, block, 0, stream>>>(recs, prms, entries, chunks, K, step);
+            <<<grid, block, lds, stream>>>(recs, prms, entries, chunks, K, step);
       });
     });
   });
@@ -443,7 +461,7 @@ hipError_t launch_simulate_multi(const TensorRec* recs, const ParamRec* prms, co
 
 // go(gradient type, ACC, quads per thread) of a list backward.  A wave of the overwriting backward on bf16
 // gradients loads 512 bytes a quad, so 32 of them keep only 16 KB in flight on a CU; two quads double
-// that: step of 518M elements 1.321 -> 1.298 ms, of 31.5M 76.0 -> 74.7 us.  In runs it gains nothing
+// that: step of 518M elements 1.310 -> 1.276 ms, of 31.5M 75.6 -> 74.3 us.  In runs it gains nothing
 // (23M packed elements 58.1 -> 58.8 us), and every other backward, which loads 1-2 KB a quad, is 2-3 %
 // slower with two.
 template <typename F>
@@ -479,12 +497,13 @@ hipError_t launch_backward_multi(const TensorRec* recs, const ParamRec* prms, co
 hipError_t launch_simulate_multi_dev(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
                                      const ChunkTable& table, int theta0_dtype, int out_dtype,
                                      const StepState* state, bool runs, hipStream_t stream) {
+  const uint32_t lds = sim_lds(theta0_dtype, out_dtype, table_elems(table));
   return for_table<kSimQuads>(table, runs, [&](const uint2* entries, uint32_t chunks, dim3 grid, auto order, uint64_t) {
     const dim3 block(kBlock);
     with_type(theta0_dtype, [&](auto t0) {
       with_type(out_dtype, [&](auto to) {
         k_simulate_multi_dev<typename decltype(t0)::type, typename decltype(to)::type, decltype(order)::value>
-            <<<grid, block, 0, stream>>>(recs, prms, scales, entries, chunks, state);
+            <<<grid, block, lds, stream>>>(recs, prms, scales, entries, chunks, state);
       });
     });
   });

@@ -134,6 +134,7 @@ inline TensorRec device_rec(const TensorRec& R, int t0_dtype, int out_dtype, int
   r.elem_offset = R.elem_offset - head;
   r.sflags = R.sflags | (head << kHeadShift) | (reinterpret_cast<uintptr_t>(r.theta) % 64 ? 0u : kSectorSim) |
              (reinterpret_cast<uintptr_t>(r.grad_theta) % 64 ? 0u : kSectorBwd);
+  if ((R.sflags & kVecBwd) && R.n % 4 == 0 && R.elem_offset % (uint64_t)kSegment == 0) r.sflags |= kBwdWhole;
   return r;
 }
 inline AdamRec device_adam(const AdamRec& A, const TensorRec& R) {
