@@ -182,8 +182,8 @@ smat_status smat_adamw_fused(const void* grad_sim, smat_dtype grad_dtype, const 
  * A plan covers a fixed list of parameter tensors processed by one launch per operation
  * (the grouping of tensors of Sec. 4.3, "Kernel fusion").  It holds host-side tables only; its device tables live
  * in a caller-allocated workspace.  One launch per operation covers the whole list, split
- * into equal-sized chunks so that thousands of small vectors and a few huge matrices share
- * the GPU evenly. */
+ * into chunks of 16384 elements (and, where many tensors are small, segments of 2048) so that thousands
+ * of small vectors and a few huge matrices share the GPU evenly. */
 typedef struct smat_plan smat_plan;
 
 /* One tensor of a plan.  Pointers are device pointers unless stated. */
@@ -254,7 +254,7 @@ smat_status smat_simulate_multi(smat_plan* plan, uint64_t seed, uint32_t step, h
  * Same validation as smat_plan_create (resident mode; grad pointers are not read) and
  * smat_plan_set_params (per_tensor[i] for descs[i]), the same kernels and the same output bits.
  * The tensor records, per-tensor constants and chunk table live in one static device array of the
- * library, 8 MiB per GPU, held until the process ends: at most 8192 tensors, and at most
+ * library, 8 MiB and 64 KiB per GPU, held until the process ends: at most 8192 tensors, and at most
  * (8 MiB - the records) / 8 chunks of 16384 elements (about 15.8e9 elements at 8192 tensors, 17e9
  * for a few hundred).  The call allocates nothing; it builds the tables in static host memory and
  * copies them with one synchronous host-to-device copy ordered on `stream` (so it blocks until
@@ -383,12 +383,12 @@ smat_status smat_adamw_fused_multi(smat_plan* plan, uint64_t seed, uint32_t step
  *   sumsq = sum over tensors and elements of g^2,  g = [grad_acc +] lambda t m (.) grad_sim
  * (Eq. smat-gradient weighted by lambda; grad_acc = desc.grad_theta when accumulate is 1), with the
  * mask regenerated as in smat_backward_accum_multi.  Reads grad_sim (and grad_acc) only: 2 B per
- * element for bf16 gradients.  Outputs, written on `stream` by the last of three small launches:
+ * element for bf16 gradients.  Outputs, written on `stream` by the last of two or three launches:
  *   sumsq       device fp64 scalar, or NULL
  *   clip_coef   device fp32 scalar min(1, max_norm / (sqrt(sumsq) + 1e-6)), the factor
  *               torch.nn.utils.clip_grad_norm_ applies, or NULL; then max_norm must be finite and > 0.
  *               Pass it as grad_scale_dev of smat_adamw_fused_multi to clip without a host sync.
- * At least one output must be given.  Per-chunk fp32 partial sums (in the plan's workspace) are
+ * At least one output must be given.  The fp32 partial sums of 2048 elements each (in the plan's workspace) are
  * added in fp64 in a fixed order: the result is the same on every call.  Any storage may be active.
  * Norm calls on one plan share those partials: calls that overlap (on different streams) race.
  * Errors: SMAT_ERR_INVALID, SMAT_ERR_STATE (no workspace or params, gradient arrays not set),

@@ -1226,15 +1226,18 @@ extern "C" smat_status smat_plan_destroy(smat_plan* p) {
 namespace {
 constexpr size_t kScratchBytes = size_t(8) << 20;
 constexpr int32_t kScratchMaxTensors = 8192;
+// room behind the tables for the one chunk more that a tensor whose elem_offset is not a multiple of 4 may
+// need (it is cut from the start of its first group), so that the accepted lists don't depend on offsets
+constexpr size_t kScratchHeadBytes = kScratchMaxTensors * sizeof(uint2);
 constexpr int kMaxDevices = 64;
 }  // namespace
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchHeadBytes];
 
 namespace {
 std::mutex g_scratch_mu;                    // guards the host tables and the address cache
 void* g_scratch_dev[kMaxDevices] = {};      // per-device address of `scratch`
-alignas(256) unsigned char g_scratch_host[kScratchBytes];  // host image of the tables
+alignas(256) unsigned char g_scratch_host[kScratchBytes + kScratchHeadBytes];  // host image of the tables
 Span g_scratch_spans[3 * kScratchMaxTensors];
 std::pair<uint32_t, std::pair<uint64_t, uint64_t>> g_scratch_ranges[kScratchMaxTensors];
 
@@ -1309,7 +1312,7 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
                                        reinterpret_cast<uintptr_t>(d.theta0) + n * dtype_bytes(theta0_dtype), false, i,
                                        "theta0"};
     g_scratch_ranges[nranges++] = {d.tensor_id, {d.elem_offset, d.elem_offset + (uint64_t)d.n}};
-    nchunks += (size_t)chunk_count(d.elem_offset, d.n);
+    nchunks += (size_t)chunk_count(0, d.n);
     if (nchunks > max_chunks)
       return fail(SMAT_ERR_INVALID, "%s: the list needs more than the %zu chunks of %lld elements that the %zu-byte "
                   "static tables hold for %d tensors (use a plan)", where0, max_chunks, (long long)smat::kChunk,
@@ -1326,7 +1329,8 @@ extern "C" smat_status smat_simulate_multi_static(const smat_tensor_desc* descs,
   if (smat_status st = refuse_capture(stream, where0); st != SMAT_OK) return st;
   void* dev = nullptr;
   if (smat_status st = scratch_address(&dev); st != SMAT_OK) return st;
-  // a list whose segments would not fit keeps its remainders in chunks, whose count was checked above
+  // a list whose segments would not fit keeps its remainders in chunks, whose count was checked above and
+  // whose heads have room of their own
   bool split = split_table(descs, count);
   if (split) {
     size_t used = 0;

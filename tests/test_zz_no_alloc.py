@@ -129,3 +129,22 @@ def test_static_list_rejects_lists_beyond_its_tables():
     assert st == _lib.SMAT_ERR_INVALID
     st = lib.smat_simulate_multi_static(big, 1, _lib.SMAT_BF16, _lib.SMAT_BF16, pp, 0, 1 << 30, None)
     assert st == _lib.SMAT_ERR_INVALID
+
+
+def test_static_list_limit_does_not_depend_on_the_offset():
+    """The table's limit counts chunks of n elements, for offsets inside a Philox group too: a list that
+    fills it exactly passes that check (and then fails the next one, a tensor id given twice, so nothing
+    is launched), one chunk more does not."""
+    lib = smat.lib()
+    p = smat.op_params_array(2, 1.0, 1.0, 0.0)
+    pp = p.ctypes.data_as(ctypes.POINTER(_lib.smat_op_params))
+    room = ((8 << 20) - 2 * 256) // 8  # two tensors: a 256-byte part of records and one of params
+    for offset in (0, 1, 3, 4):
+        for n1, said in ((1, b"given twice"), (16384, b"given twice"), (16385, b"use a plan")):
+            two = (_lib.smat_tensor_desc * 2)()
+            two[0].n, two[1].n = (room - 1) * 16384, n1
+            for i in range(2):
+                two[i].theta, two[i].theta0, two[i].out = (1 + 3 * i) << 44, (2 + 3 * i) << 44, (3 + 3 * i) << 44
+                two[i].elem_offset = offset
+            st = lib.smat_simulate_multi_static(two, 2, _lib.SMAT_BF16, _lib.SMAT_BF16, pp, 0, 0, None)
+            assert st == _lib.SMAT_ERR_INVALID and said in lib.smat_last_error(), (offset, n1, lib.smat_last_error())
