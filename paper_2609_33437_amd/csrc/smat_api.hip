@@ -8,7 +8,6 @@
 #include <cstring>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <utility>
 #include <vector>
 
@@ -191,71 +190,48 @@ smat_status check_simulate_ptrs(const float* theta, const void* theta0, int t0_d
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Pinned staging of a plan's per-step tables: up to eight slots, used in turn, that upload kernels read
-// in place.  Each kernel writes its slot's sequence number to the slot's words once it has read it, so
-// reuse waits for exactly the upload that used the slot, whatever streams the calls name, and the
-// stream carries no event for it.  Eight slots let the host issue that many steps ahead of the GPU;
-// tables over 1 MB get two.
-struct Staging {
-  static constexpr uint32_t kMaxSlots = 8;
-  char* mem = nullptr;
-  size_t slot_bytes = 0;
-  uint32_t slots = 0, next = 0;
-  uint32_t seq[kMaxSlots] = {}, blocks[kMaxSlots] = {};
-
-  hipError_t init(size_t bytes) {
-    if (mem) return hipSuccess;
-    slot_bytes = align256(std::max<size_t>(bytes, 256));
-    slots = slot_bytes <= (size_t(1) << 20) ? kMaxSlots : 2;
-    const size_t words = slots * smat::kUploadBlocks * sizeof(uint32_t);
-    char* p = nullptr;
-    const hipError_t e = hipHostMalloc((void**)&p, slots * slot_bytes + words, hipHostMallocPortable | hipHostMallocMapped);
-    if (e != hipSuccess) return e;
-    std::memset(p + slots * slot_bytes, 0, words);
-    mem = p;
-    return hipSuccess;
-  }
-  char* data() const { return mem + next * slot_bytes; }
-  uint32_t* words(uint32_t slot) const {
-    return reinterpret_cast<uint32_t*>(mem + slots * slot_bytes) + slot * smat::kUploadBlocks;
-  }
-  bool read(uint32_t slot) const {
-    for (uint32_t b = 0; b < blocks[slot]; ++b)
-      if (__atomic_load_n(words(slot) + b, __ATOMIC_ACQUIRE) != seq[slot]) return false;
-    return true;
-  }
-  // Wait until the slot's last upload has read it.  A wait of seconds asks the runtime, which reports a
-  // device that will not finish.
-  hipError_t wait(uint32_t slot) const {
-    using clock = std::chrono::steady_clock;
-    auto until = clock::now() + std::chrono::seconds(2);
-    for (uint32_t k = 1; !read(slot); ++k) {
-      if (k % 1024) continue;
-      std::this_thread::yield();
-      if (clock::now() < until) continue;
-      if (const hipError_t e = hipDeviceSynchronize(); e != hipSuccess) return e;
-      until = clock::now() + std::chrono::seconds(2);
-    }
-    return hipSuccess;
-  }
-  // The next slot, free to be written: fill data(), launch its last upload with signal(), then sent().
-  hipError_t take() const { return wait(next); }
-  smat::UploadSignal signal() const { return {words(next), seq[next] + 1}; }
-  void sent(uint32_t used_blocks) {
-    ++seq[next];
-    blocks[next] = used_blocks;
-    next = (next + 1) % slots;
-  }
-  void release() {
-    if (!mem) return;
-    for (uint32_t k = 0; k < slots; ++k) (void)wait(k);
-    (void)hipHostFree(mem);
-    mem = nullptr;
-  }
+// The runtime's calls of the pinned staging (smat_staging.h).  Other threads may be capturing graphs, in
+// the mode that forbids queries and waits everywhere: this thread's are marked as unrelated to them.
+struct UnrelatedToCaptures {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  UnrelatedToCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~UnrelatedToCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
+struct HipStaging {
+  using Error = hipError_t;
+  using Stream = hipStream_t;
+  static constexpr Error kOk = hipSuccess;
+  static Error alloc(void** p, size_t bytes) {
+    return hipHostMalloc(p, bytes, hipHostMallocPortable | hipHostMallocMapped);
+  }
+  static void free(void* p) { (void)hipHostFree(p); }
+  static int device_of(Stream stream) {
+    int device = 0;
+    if (!stream || hipStreamGetDevice(stream, &device) != hipSuccess) (void)hipGetDevice(&device);
+    return device;
+  }
+  static Error failed(Stream stream) {
+    UnrelatedToCaptures scope;
+    const Error e = hipStreamQuery(stream);
+    if (e != hipErrorNotReady) return e;
+    (void)hipGetLastError();  // an answer, which the next launch's check must not take for its own error
+    return kOk;
+  }
+  static Error drain(int device) {
+    UnrelatedToCaptures scope;
+    int before = 0;
+    (void)hipGetDevice(&before);
+    Error e = hipSetDevice(device);
+    if (e == kOk) e = hipDeviceSynchronize();
+    (void)hipSetDevice(before);
+    return e;
+  }
+  static std::chrono::milliseconds patience() { return std::chrono::seconds(2); }
+};
+using Staging = smat::StagingOf<HipStaging>;
 
-// Calls that upload host tables through pinned staging (reused by the next call) and wait on their
-// own events cannot be recorded into a graph: a replay would copy whatever the staging holds then.
+// Calls that upload host tables through pinned staging (whose slots are used again by later calls) cannot
+// be recorded into a graph: a replay would upload whatever the staging holds then.
 smat_status refuse_capture(hipStream_t stream, const char* where) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   SMAT_HIP(hipStreamIsCapturing(stream, &cs));
@@ -804,7 +780,7 @@ extern "C" smat_status smat_plan_set_params(smat_plan* p, const smat_op_params* 
   }
   if (first < last) {
     Staging& st = p->params_staging;
-    SMAT_HIP(st.take());
+    SMAT_HIP(st.take(stream));
     // params and scale records are adjacent in the workspace: one upload carries the changed span
     std::memcpy(st.data(), recs.data(), prm_bytes);
     std::memcpy(st.data() + prm_bytes, scales.data(), sizeof(ScaleRec) * p->count);
@@ -812,7 +788,7 @@ extern "C" smat_status smat_plan_set_params(smat_plan* p, const smat_op_params* 
     const size_t lo = first * sizeof(ParamRec), hi = last * sizeof(ParamRec);
     p->params_set = false;  // until the upload is enqueued: a failed one leaves the plan without params
     SMAT_HIP(smat::launch_upload(st.data() + lo, p->ws + p->off_params + lo, hi - lo, st.signal(), stream));
-    st.sent(smat::upload_blocks((hi - lo) / 8));
+    st.sent(smat::upload_blocks((hi - lo) / 8), stream);
     p->dev_params = recs;
     p->dev_scales = scales;
   }
@@ -981,14 +957,14 @@ extern "C" smat_status smat_plan_bind_adam_state(smat_plan* p, const smat_adam_s
   const size_t rec_bytes = sizeof(TensorRec) * p->count, adam_bytes = sizeof(AdamRec) * p->count;
   Staging& stage = p->recs_staging;
   SMAT_HIP(stage.init(rec_bytes + adam_bytes));
-  SMAT_HIP(stage.take());
+  SMAT_HIP(stage.take(stream));
   device_recs(p, recs, &adam, stage.data());
   AdamRec* staged = reinterpret_cast<AdamRec*>(stage.data() + rec_bytes);
   for (int32_t i = 0; i < p->count; ++i) staged[i] = smat::device_adam(adam[i], recs[i]);
   if (p->count > 0) {
     SMAT_HIP(smat::launch_upload(stage.data(), p->ws + p->off_recs, rec_bytes, {}, stream));
     SMAT_HIP(smat::launch_upload(stage.data() + rec_bytes, p->ws + p->off_adam, adam_bytes, stage.signal(), stream));
-    stage.sent(smat::upload_blocks(adam_bytes / 8));
+    stage.sent(smat::upload_blocks(adam_bytes / 8), stream);
   }
   p->recs = recs;
   p->adam = adam;
@@ -1033,11 +1009,11 @@ extern "C" smat_status smat_plan_set_grads(smat_plan* p, const void* const* grad
   const size_t rec_bytes = sizeof(TensorRec) * p->count, adam_bytes = sizeof(AdamRec) * p->count;
   Staging& stage = p->recs_staging;
   SMAT_HIP(stage.init(rec_bytes + adam_bytes));
-  SMAT_HIP(stage.take());
+  SMAT_HIP(stage.take(stream));
   device_recs(p, recs, p->adam_bound ? &p->adam : nullptr, stage.data());
   if (p->count > 0) {
     SMAT_HIP(smat::launch_upload(stage.data(), p->ws + p->off_recs, rec_bytes, stage.signal(), stream));
-    stage.sent(smat::upload_blocks(rec_bytes / 8));
+    stage.sent(smat::upload_blocks(rec_bytes / 8), stream);
   }
   for (int32_t i = 0; i < p->count; ++i) {
     p->descs[i].grad_sim = recs[i].grad_sim;
@@ -1649,11 +1625,11 @@ extern "C" smat_status smat_merge_multi(smat_merge_plan* p, const smat_merge_ter
   }
   if (cells > 0) {
     Staging& st = p->terms_staging;
-    SMAT_HIP(st.take());
+    SMAT_HIP(st.take(stream));
     std::memcpy(st.data(), recs.data(), sizeof(MergeTerm) * cells);
     SMAT_HIP(smat::launch_upload_terms(reinterpret_cast<const MergeTerm*>(st.data()),
                                        reinterpret_cast<MergeRec*>(p->ws + p->off_terms), cells, st.signal(), stream));
-    st.sent(smat::upload_blocks(cells));
+    st.sent(smat::upload_blocks(cells), stream);
   }
   if (!p->entries.empty())
     SMAT_HIP(smat::launch_merge_multi(reinterpret_cast<const TensorRec*>(p->ws + p->off_recs),

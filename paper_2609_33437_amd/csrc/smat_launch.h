@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "smat_device.h"
+#include "smat_staging.h"
 
 namespace smat {
 
@@ -211,17 +212,6 @@ hipError_t launch_adamw_multi_dev(const TensorRec* recs, const AdamRec* states, 
                                   bool accumulate, float lambda, const StepState* state, const float* dev_scale,
                                   bool runs, hipStream_t stream);
 // ---------------------------------------------------------------- table uploads
-// What an upload kernel writes once it has read its staging: block b stores seq to done[b] (pinned host
-// memory; null: nothing).
-struct UploadSignal {
-  uint32_t* done;
-  uint32_t seq;
-};
-// Blocks of an upload of n items (16 blocks of 256 threads saturate the host link with 8-byte loads).
-constexpr uint32_t kUploadBlocks = 16;
-inline uint32_t upload_blocks(uint64_t n) {
-  return (uint32_t)(n >= kUploadBlocks * 256u ? kUploadBlocks : n ? (n + 255) / 256 : 1);
-}
 // Per-step tables from pinned host memory (`staged`, device-accessible) into a workspace; bytes is a
 // multiple of 8.
 hipError_t launch_upload(const void* staged, void* dst, size_t bytes, UploadSignal sig, hipStream_t stream);
