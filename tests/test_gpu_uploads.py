@@ -1,15 +1,23 @@
-"""Per-step tables of lists of 1 to 1,025 tensors reach the kernels whole: list results equal the
+"""Per-step tables of lists of 1 to 33,000 tensors reach the kernels whole: list results equal the
 single-tensor calls, which take their parameters as arguments.  Counts sit around the upload kernels'
-256-thread blocks; repeated calls reuse both staging slots while earlier steps are still queued."""
+256-thread blocks.  Every test uploads more often than a plan's staging has slots (eight, or two for
+tables over 1 MB) while the first upload is still queued behind a long run of copies, so that the host has
+to wait for a slot before it writes the next table."""
+import contextlib
+
+import numpy as np
 import pytest
 import torch
 
 import paper_2609_33437_amd as smat
+from paper_2609_33437_amd import _lib
 from helpers import bits
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 SEED = 77
+ROUNDS = 18       # two turns of eight slots and two more
+LARGE_ROUNDS = 5  # two turns of two slots and one more
 
 
 def arrays(count, std, seed, dtype=torch.float32):
@@ -17,58 +25,171 @@ def arrays(count, std, seed, dtype=torch.float32):
     return list((torch.randn(count, 8, device=DEV, generator=g) * std).to(dtype))
 
 
+def whole(rows):
+    """The rows of arrays() as the one tensor they are views of."""
+    return rows[0]._base
+
+
+class Busy:
+    """Copies of about 60 ms (times `times`) queued on the current stream."""
+
+    def __init__(self):
+        self.src = torch.zeros(1 << 30, dtype=torch.uint8, device=DEV)
+        self.dst = torch.empty_like(self.src)
+        self.done = torch.cuda.Event()
+
+    def queue(self, times=1):
+        for _ in range(180 * times):
+            smat.smat_stream_copy(self.src, self.dst)
+        self.done.record()
+
+
+def records(count, k):
+    return smat.op_params_array(count, [0.3 + 0.001 * (i % 300) + 0.1 * (k % 5) for i in range(count)],
+                                [0.2 + 0.7 * i / count for i in range(count)], 1e-3 * (1 + k))
+
+
+def rows(params):
+    return [dict(zip(params.dtype.names, r)) for r in params.tolist()]
+
+
 @pytest.mark.parametrize("count", [1, 31, 64, 65, 257, 1025])
-def test_parameters_and_gradient_tables(count):
+@pytest.mark.parametrize("two_streams", [False, True])
+def test_parameters_and_gradient_tables(count, two_streams):
     th, t0 = arrays(count, 0.02, 1), arrays(count, 0.02, 2, torch.bfloat16)
     out, gt = arrays(count, 1.0, 3, torch.bfloat16), arrays(count, 1e-3, 4)
     m1, m2 = arrays(count, 1e-3, 5), [x.square_() for x in arrays(count, 1e-3, 6)]
     hp = dict(lr=1e-3, beta1=0.9, beta2=0.99, eps=1e-8, weight_decay=0.0, step=2)
-    rounds = [[dict(s=0.3 + 0.001 * i + 0.1 * k, keep=0.2 + 0.7 * i / count, sigma=1e-3 * (1 + k)) for i in range(count)]
-              for k in range(4)]
-    grads = [arrays(count, 1e-2, 10 + k, torch.bfloat16) for k in range(4)]
+    params = [records(count, k) for k in range(ROUNDS)]
+    grads = [arrays(count, 1e-2, 10 + k, torch.bfloat16) for k in range(ROUNDS)]
     want = []
     ref = [[x.clone() for x in a] for a in (th, gt, m1, m2)]
-    for k, prm in enumerate(rounds):
+    for k, prm in enumerate(params):
         tilde = [torch.empty_like(o) for o in out]
-        for i in range(count):
-            smat.smat_simulate(ref[0][i], t0[i], tilde[i], prm[i], SEED, k, i)
-            smat.smat_backward_accum(grads[k][i], ref[1][i], prm[i], 0.5, SEED, k, i)
-            smat.smat_adamw_fused(grads[k][i], ref[0][i], ref[2][i], ref[3][i], prm[i], 0.5, hp, SEED, k, i)
+        for i, p in enumerate(rows(prm)):
+            smat.smat_simulate(ref[0][i], t0[i], tilde[i], p, SEED, k, i)
+            smat.smat_backward_accum(grads[k][i], ref[1][i], p, 0.5, SEED, k, i)
+            smat.smat_adamw_fused(grads[k][i], ref[0][i], ref[2][i], ref[3][i], p, 0.5, hp, SEED, k, i)
         want.append(tilde)
-    got = []
+    busy = Busy()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()] if two_streams else [None]
+    got, early = [None] * ROUNDS, []
     with smat.Plan(th, out, t0, grads[0], gt) as plan:
         plan.bind_adam_state(m1, m2)
-        for k, prm in enumerate(rounds):       # nothing waits between the rounds
-            plan.set_params(prm)
-            plan.set_grads(grad_sims=grads[k])
-            plan.simulate(SEED, k)
-            plan.backward_accum(SEED, k, 0.5)
-            plan.adamw_fused(SEED, k, 0.5, hp)
-            got.append(torch.stack(out))
         torch.cuda.synchronize()
-    for k in range(4):
+        last = None
+        for k, prm in enumerate(params):       # nothing waits between the rounds but the staging
+            stream = streams[k % len(streams)]
+            with torch.cuda.stream(stream) if stream else contextlib.nullcontext():
+                if last:
+                    torch.cuda.current_stream().wait_event(last)
+                if k == 0:
+                    busy.queue()
+                plan.set_params(prm)
+                early.append(not busy.done.query())
+                plan.set_grads(grad_sims=grads[k])
+                plan.simulate(SEED, k)
+                plan.backward_accum(SEED, k, 0.5)
+                plan.adamw_fused(SEED, k, 0.5, hp)
+                got[k] = whole(out).clone()
+                if stream:
+                    last = torch.cuda.Event()
+                    last.record()
+        torch.cuda.synchronize()
+    # the first eight uploads went ahead of the copies, the ninth (every slot in use) waited for them
+    assert early[0] and not any(early[8:])
+    for k in range(ROUNDS):
         assert torch.equal(bits(got[k]), bits(torch.stack(want[k]))), k
     for a, b in zip((th, gt, m1, m2), ref):
-        assert torch.equal(bits(torch.stack(a)), bits(torch.stack(b)))
+        assert torch.equal(bits(whole(a)), bits(torch.stack(b)))
+
+
+def terms_of(count, nexp, k):
+    return [[dict(gamma=0.2 + 0.001 * (i % 300) + 0.1 * (k % 7), keep=0.3 + 0.1 * j, seed=(1 << 40) * (j + 1) + i, step=k)
+             for j in range(nexp)] for i in range(count)]
 
 
 @pytest.mark.parametrize("count,nexp", [(1, 1), (85, 3), (64, 4), (257, 1), (300, 5)])
 def test_merge_terms(count, nexp):
     t0, out = arrays(count, 0.02, 1, torch.bfloat16), arrays(count, 1.0, 2, torch.bfloat16)
     ex = [arrays(count, 0.02, 20 + j, torch.bfloat16) for j in range(nexp)]
-    rounds = [[[dict(gamma=0.2 + 0.001 * i + 0.1 * k, keep=0.3 + 0.1 * j, seed=(1 << 40) * (j + 1) + i, step=k)
-                for j in range(nexp)] for i in range(count)] for k in range(4)]
-    got, want = [], []
+    rounds = [terms_of(count, nexp, k) for k in range(ROUNDS)]
+    busy = Busy()
+    got, early = [], []
     with smat.MergePlan(t0, out, ex) as plan:
+        busy.queue()
         for terms in rounds:
             plan.merge(terms)
-            got.append(torch.stack(out))
+            early.append(not busy.done.query())
+            got.append(whole(out).clone())
         torch.cuda.synchronize()
-    for terms in rounds:
+    assert early[0] and not any(early[8:])
+    for k, terms in enumerate(rounds):
         o = [torch.empty_like(x) for x in out]
         for i in range(count):
             smat.smat_merge([e[i] for e in ex], t0[i], o[i], terms[i], i)
-        want.append(torch.stack(o))
-    torch.cuda.synchronize()
-    for k in range(4):
-        assert torch.equal(bits(got[k]), bits(want[k])), k
+        assert torch.equal(bits(got[k]), bits(torch.stack(o))), k
+
+
+def test_tables_over_a_megabyte():
+    """Two slots: 33,000 tensors (1.06 MB of parameters, 2.6 MB of records), five uploads of each, against
+    plans of up to 1,000 of the tensors with one upload each."""
+    count = 33000
+    th, t0 = arrays(count, 0.02, 1), arrays(count, 0.02, 2, torch.bfloat16)
+    out, gt = arrays(count, 1.0, 3, torch.bfloat16), arrays(count, 1e-3, 4)
+    params = [records(count, k) for k in range(LARGE_ROUNDS)]
+    grads = [arrays(count, 1e-2, 10 + k, torch.bfloat16) for k in range(LARGE_ROUNDS)]
+    busy = Busy()
+    got, early = [], []
+    with smat.Plan(th, out, t0, grads[0], gt) as plan:
+        torch.cuda.synchronize()
+        busy.queue(5)
+        for k in range(LARGE_ROUNDS):
+            plan.set_params(params[k])
+            early.append(not busy.done.query())
+            plan.set_grads(grad_sims=grads[k])
+            plan.simulate(SEED, k)
+            plan.backward(SEED, k, 0.5, False)
+            got.append((whole(out).clone(), whole(gt).clone()))
+        torch.cuda.synchronize()
+    assert early[0] and not any(early[2:])
+    for k in range(LARGE_ROUNDS):
+        for a in range(0, count, 1000):
+            part = slice(a, a + 1000)
+            with smat.Plan(th[part], out[part], t0[part], grads[k][part], gt[part],
+                           tensor_ids=list(range(count))[part]) as plan:
+                plan.set_params(np.ascontiguousarray(params[k][part]))
+                plan.simulate(SEED, k)
+                plan.backward(SEED, k, 0.5, False)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(got[k][0]), bits(whole(out))), k
+        assert torch.equal(bits(got[k][1]), bits(whole(gt))), k
+
+
+def test_merge_terms_over_a_megabyte():
+    """Two slots: 11,000 tensors of four experts (1.06 MB of terms), five merges, against plans of up to
+    1,000 of the tensors."""
+    count, nexp = 11000, 4
+    t0, out = arrays(count, 0.02, 1, torch.bfloat16), arrays(count, 1.0, 2, torch.bfloat16)
+    ex = [arrays(count, 0.02, 20 + j, torch.bfloat16) for j in range(nexp)]
+    terms = [[[_lib.merge_term(t) for t in row] for row in terms_of(count, nexp, k)] for k in range(LARGE_ROUNDS)]
+    busy = Busy()
+    got, early = [], []
+    with smat.MergePlan(t0, out, ex) as plan:
+        torch.cuda.synchronize()
+        for k in range(LARGE_ROUNDS):
+            if k == 0:
+                busy.queue(5)
+            plan.merge(terms[k])
+            early.append(not busy.done.query())
+            got.append(whole(out).clone())
+        torch.cuda.synchronize()
+    assert early[0] and not any(early[2:])
+    for k in range(LARGE_ROUNDS):
+        for a in range(0, count, 1000):
+            part = slice(a, a + 1000)
+            with smat.MergePlan(t0[part], out[part], [e[part] for e in ex],
+                                tensor_ids=list(range(count))[part]) as plan:
+                plan.merge(terms[k][part])
+        torch.cuda.synchronize()
+        assert torch.equal(bits(got[k]), bits(whole(out))), k
