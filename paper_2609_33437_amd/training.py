@@ -96,16 +96,18 @@ def adam_hparams(optimizer: torch.optim.Optimizer, params: Sequence[torch.nn.Par
         hps.append((float(g["lr"]), float(b1), float(b2), float(g["eps"]), wd))
     if len(set(hps)) > 1:
         raise SmatError(SMAT_ERR_INVALID, "parameters of the fused update must share lr, betas, eps and weight decay")
-    steps, on_gpu = set(), []
+    steps, on_gpu = set(), {}
     for p in params:
         st = optimizer.state.get(p)
         count = st["step"] if st and "step" in st else 0
         if isinstance(count, torch.Tensor) and count.is_cuda:
-            on_gpu.append(count)
+            on_gpu.setdefault((count.dtype, count.get_device()), []).append(count if count.dim() == 0 else
+                                                                            count.reshape(()))
         else:
             steps.add(int(float(count)))
-    if on_gpu:  # fused and capturable optimizers count on the GPU: one read for all of them
-        steps.update(int(c) for c in torch.stack([c.reshape(()).float() for c in on_gpu]).tolist())
+    # fused and capturable optimizers count on the GPU: one read for all of them (of each type and GPU)
+    for counts in on_gpu.values():
+        steps.update(int(float(c)) for c in torch.stack(counts).tolist())
     if len(steps) > 1:
         raise SmatError(SMAT_ERR_INVALID, "parameters of the fused update must share the optimizer step count")
     lr, b1, b2, eps, wd = hps[0] if hps else (0.0, 0.9, 0.999, 1e-8, 0.0)

@@ -14,7 +14,7 @@ import torch
 
 import oracle
 import paper_2609_33437_amd as smat
-from paper_2609_33437_amd.training import SimulatedMergeTraining
+from paper_2609_33437_amd.training import SimulatedMergeTraining, adam_hparams
 from helpers import host
 from tolerances import SQNORM_ULPS, U, check_adam, check_grad, check_sqnorm, check_theta_tilde, ordered
 from workloads.model import TINY, make_decoder, token_batches
@@ -206,6 +206,20 @@ def test_mixed_objective_adds_both_gradients(fused):
     w.abort()
     assert all(torch.equal(p.grad, b) for p, b in zip(w.params, before))
     w.close()
+
+
+@pytest.mark.parametrize("dtypes", [(torch.int64,), (torch.float64,), (torch.int64, torch.float64), (torch.float32,)])
+def test_step_counts_on_the_gpu_keep_their_type(dtypes):
+    """Counts past 2^24, which fp32 does not hold, are read exactly, also where one parameter's differs by 1."""
+    params = [torch.nn.Parameter(torch.zeros(3, device=DEV)) for _ in range(5)]
+    opt = torch.optim.AdamW(params, lr=1e-3, capturable=True)
+    count = 2 ** 24 + (0 if torch.float32 in dtypes else 1)
+    for i, p in enumerate(params):
+        opt.state[p]["step"] = torch.tensor(count, dtype=dtypes[i % len(dtypes)], device=DEV)
+    assert adam_hparams(opt, params)["step"] == count + 1
+    opt.state[params[4]]["step"].sub_(1)
+    with pytest.raises(smat.SmatError):
+        adam_hparams(opt, params)
 
 
 def test_fused_update_creates_missing_optimizer_state():
