@@ -101,7 +101,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "smat_plan_create": [POINTER(smat_tensor_desc), c_int32, c_int32, c_int32, c_int32, c_int32, POINTER(P)],
         "smat_plan_workspace_bytes": [P, POINTER(c_size_t)],
         "smat_plan_bind_workspace": [P, P, c_size_t, P],
-        "smat_plan_set_params": [P, P, P],
+        "smat_plan_set_params": [P, POINTER(smat_op_params), P],
         "smat_simulate_multi": [P, c_uint64, c_uint32, P],
         "smat_backward_accum_multi": [P, c_uint64, c_uint32, c_float, P],
         "smat_switch_storage": [P, c_int32, P],
@@ -313,6 +313,20 @@ def op_params(p) -> smat_op_params:
                           int(p.get("noise_kind", SMAT_NOISE_GAUSSIAN)))
 
 
+def _op_params_arg(params):
+    """A sequence of dicts / smat_op_params, or an op_params_array, as the argument that the library reads."""
+    if not isinstance(params, np.ndarray):
+        return (smat_op_params * max(len(params), 1))(*[op_params(p) for p in params])
+    if params.dtype != OP_PARAMS_DTYPE:
+        raise SmatError(SMAT_ERR_INVALID, "a parameter array must have OP_PARAMS_DTYPE records")
+    if not len(params):
+        return None
+    flags = params.flags
+    if not (flags.c_contiguous and flags.writeable):    # from_buffer takes neither strides nor read-only memory
+        params = params.copy()
+    return smat_op_params.from_buffer(params)           # the first record; it keeps the array alive
+
+
 def rng_key(seed: int, step: int, tensor_id: int = 0, elem_offset: int = 0) -> smat_rng_key:
     return smat_rng_key(int(seed), int(step), int(tensor_id), int(elem_offset))
 
@@ -451,14 +465,7 @@ class Plan:
         """Per-tensor parameters: a sequence of dicts / smat_op_params, or an op_params_array."""
         if len(params) != self.count:
             raise SmatError(SMAT_ERR_INVALID, "one parameter record per tensor")
-        if isinstance(params, np.ndarray):
-            if params.dtype != OP_PARAMS_DTYPE:
-                raise SmatError(SMAT_ERR_INVALID, "a parameter array must have OP_PARAMS_DTYPE records")
-            arr = params if params.flags.c_contiguous else np.ascontiguousarray(params)
-            ptr = arr.ctypes.data if self.count else None
-        else:
-            ptr = (smat_op_params * max(self.count, 1))(*[op_params(p) for p in params])
-        _check(lib().smat_plan_set_params(self._plan, ptr, _stream_handle(stream)))
+        _check(lib().smat_plan_set_params(self._plan, _op_params_arg(params), _stream_handle(stream)))
 
     def simulate(self, seed: int, step: int, stream=None) -> None:
         _check(lib().smat_simulate_multi(self._plan, int(seed), int(step), _stream_handle(stream)))

@@ -90,3 +90,24 @@ def test_op_params_array_matches_the_c_records():
     assert a.tobytes() == ctypes.string_at(recs, ctypes.sizeof(recs))
     assert smat.OP_PARAMS_DTYPE.itemsize == ctypes.sizeof(_lib.smat_op_params)
     assert np.all(a["keep"] == np.float32(keeps))
+
+
+def test_parameter_records_reach_the_library_typed():
+    import ctypes
+    import numpy as np
+    from paper_2609_33437_amd import _lib
+    a = smat.op_params_array(6, [0.1, 0.2, 0.3, 0.4, 0.5, 0.6], 0.5, 1e-3)
+    frozen = a.copy()
+    frozen.flags.writeable = False
+    for arr in (a, frozen, a[::2], a[::-1], a[2:], a.reshape(6, 1)):
+        arg = _lib._op_params_arg(arr)
+        assert ctypes.string_at(ctypes.addressof(arg), arr.nbytes) == arr.tobytes()
+    assert _lib._op_params_arg(a[:0]) is None
+    assert status_of(lambda: _lib._op_params_arg(np.zeros(6))) == SMAT_ERR_INVALID
+    # the library's own call refuses anything but records (the null plan is refused by the library)
+    lib = smat.lib()
+    for good in (_lib._op_params_arg(a), (_lib.smat_op_params * 2)(), a.ctypes.data_as(ctypes.POINTER(_lib.smat_op_params))):
+        assert lib.smat_plan_set_params(None, good, None) == SMAT_ERR_INVALID
+    for bad in ((ctypes.c_float * 30)(), (_lib.smat_merge_term * 2)(), a.ctypes.data, b"records"):
+        with pytest.raises(ctypes.ArgumentError):
+            lib.smat_plan_set_params(None, bad, None)
