@@ -168,19 +168,19 @@ __device__ __forceinline__ void simulate_tile(const Tile& T, const ParamRec& P, 
 // element for bf16 g~).  !ACC: grad_theta = lambda t m g~ everywhere, zero where dropped, without
 // reading grad_theta (6 B per element): the same bits as accumulating into zeros, for a step whose
 // simulated-loss gradient is the only one.
-template <typename TG, int Q, bool ACC>
-__device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, const PhiloxKeys& K, uint32_t step,
-                                              float lambda) {
+template <typename TG, int Q, bool ACC, typename STEP>
+__device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, const STEP& Y, float lambda) {
   const uint32_t flags = P.flags;
   if (ACC && (flags & kFlagDropAll)) return;  // every coordinate dropped: the gradient is left as it is
-  const uint32_t cmask = (step << 2) | kStreamMask;
+  const uint32_t cmask = (Y.step << 2) | kStreamMask;
   const uint32_t tensor_id = T.tensor_id;
   const uint32_t len = T.len;
   const bool use_mask = (flags & kFlagMask) != 0;
   // ACC has returned above on DropAll, so there a coordinate without a mask is always kept
   const bool all_kept = ACC || (flags & (kFlagMask | kFlagDropAll)) == 0;
   const uint32_t thr = P.thr;
-  const float c = lambda * P.t;
+  const float early = STEP::LATE ? 0.0f : lambda * Y.coefficient(P);
+  auto weight = [&]() { return STEP::LATE ? lambda * Y.coefficient(P) : early; };
 
   const void* gs = T.grad_sim;
   float* gt = T.grad_theta;
@@ -190,8 +190,9 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
   auto edge = [&](uint32_t q) {
     const uint32_t lo = max(4u * q, T.head), hi = min(4u * q + 4u, len);
     if (lo >= hi) return;
+    const float c = weight();
     Words w;
-    if (use_mask) w = group_words((e0 >> 2) + q, tensor_id, cmask, K);
+    if (use_mask) w = group_words((e0 >> 2) + q, tensor_id, cmask, Y.keys());
     for (uint32_t i = lo; i < hi; ++i) {
       const bool kept = use_mask ? pick(w, i & 3u) < thr : all_kept;
       if (ACC) {
@@ -217,7 +218,8 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
     // the rest is neither read nor written
     const uint32_t q = threadIdx.x;
     const TileGroups G = tile_groups(e0);
-    const Words w = philox_tile(philox_p0(G.lo + q), G.hi, tensor_id, cmask, K);
+    const Words w = philox_tile(philox_p0(G.lo + q), G.hi, tensor_id, cmask, Y.keys());
+    const float c = weight();
     const bool kept[4] = {w.w0 < thr, w.w1 < thr, w.w2 < thr, w.w3 < thr};
     if (sector_kept(kept) && W.has(q)) {
       const typename QuadIO<TG>::Raw ra = QuadIO<TG>::load_raw(gs, q);
@@ -243,13 +245,14 @@ __device__ __forceinline__ void backward_tile(const Tile& T, const ParamRec& P, 
       if (ACC) rb[u] = QuadIO<float>::load_raw(gt, qc);
     }
     const TileGroups G = tile_groups(e0);
+    const float c = weight();
     bool kept[Q][4];
 #pragma unroll
     for (int u = 0; u < Q; ++u) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) kept[u][j] = all_kept;
       if (use_mask) {
-        const Words w = philox_tile(philox_p0(G.lo + u * kBlock + threadIdx.x), G.hi, tensor_id, cmask, K);
+        const Words w = philox_tile(philox_p0(G.lo + u * kBlock + threadIdx.x), G.hi, tensor_id, cmask, Y.keys());
         kept[u][0] = w.w0 < thr;
         kept[u][1] = w.w1 < thr;
         kept[u][2] = w.w2 < thr;
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_one(TensorRec R, ParamRec P
   Tile T = tensor_tile<float, float>(R, begin, tile);
   T.grad_sim = advance<TG>(R.grad_sim, begin);
   T.grad_theta = R.grad_theta + begin;
-  backward_tile<TG, kBwdQuads, true>(T, P, K, step, lambda);
+  backward_tile<TG, kBwdQuads, true>(T, P, HostStep{K, step}, lambda);
 }
 
 template <typename T0, typename TO, int ORDER>
@@ -320,12 +323,16 @@ __global__ __launch_bounds__(kBlock) void k_backward_multi(const TensorRec* __re
   const ListBlock B = list_block<Q, ORDER>(entries, chunks);
   const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
   if (T.len == 0) return;
-  backward_tile<TG, Q, ACC>(T, rec_at(prms, B.tensor), K, step, lambda);
+  backward_tile<TG, Q, ACC>(T, rec_at(prms, B.tensor), HostStep{K, step}, lambda);
 }
 
 // The same list kernels with the step's seed, step and scale read from device memory, so that a
 // captured graph replays them with whatever the caller last wrote there.  Each block forms its
-// tensor's coefficient from that scale and the tensor's ScaleRec exactly as the host forms it.
+// tensor's coefficient from that scale and the tensor's ScaleRec exactly as the host forms it, and the
+// round keys from the seed: the backward, which has little else to do, once its loads are issued, the
+// simulate, whose time after them goes to the draws, before (a captured step of 125M parameters 343.2 ->
+// 338.1 us together with device_recs, on another box 345.3 -> 343.6; a simulate that forms them late is
+// 1.5-2 % slower).
 template <typename T0, typename TO, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* __restrict__ recs,
                                                                const ParamRec* __restrict__ prms,
@@ -335,12 +342,12 @@ __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* 
   raise_priority();
   constexpr int64_t tile = tile_elems(kSimQuads);
   const ListBlock B = list_block<kSimQuads, ORDER>(entries, chunks);
-  const Tile T = list_tile<T0, TO, float>(rec_at(recs, B.tensor), B.tile, tile);
+  const DeviceRecs D = device_recs(recs, prms, scales, state, B.tensor, 0.0f);
+  const Tile T = list_tile<T0, TO, float>(D.R, B.tile, tile);
   if (T.len == 0) return;
-  const StepState S = *state;
-  ParamRec P = rec_at(prms, B.tensor);
-  P.t = device_coefficient(S.scale, rec_at(scales, B.tensor));
-  simulate_tile<T0, TO>(T, P, philox_keys(S.seed), S.step);
+  ParamRec P = D.P;
+  P.t = device_coefficient(D.S.scale, D.C);
+  simulate_tile<T0, TO>(T, P, philox_keys(D.S.seed), D.S.step);
 }
 
 template <typename TG, bool ACC, int Q, int ORDER>
@@ -351,12 +358,10 @@ __global__ __launch_bounds__(kBlock) void k_backward_multi_dev(const TensorRec* 
                                                                const StepState* __restrict__ state, float lambda) {
   constexpr int64_t tile = tile_elems(Q);
   const ListBlock B = list_block<Q, ORDER>(entries, chunks);
-  const Tile T = list_tile<float, float, TG>(rec_at(recs, B.tensor), B.tile, tile);
+  const DeviceRecs D = device_recs(recs, prms, scales, state, B.tensor, lambda);
+  const Tile T = list_tile<float, float, TG>(D.R, B.tile, tile);
   if (T.len == 0) return;
-  const StepState S = *state;
-  ParamRec P = rec_at(prms, B.tensor);
-  P.t = device_coefficient(S.scale, rec_at(scales, B.tensor));
-  backward_tile<TG, Q, ACC>(T, P, philox_keys(S.seed), S.step, lambda);
+  backward_tile<TG, Q, ACC>(T, D.P, DeviceStep{D.S.seed, D.S.step, D.S.scale, D.C}, lambda);
 }
 
 // One thread advances the step state: step += increment modulo 2^30 (the range of the counter's step

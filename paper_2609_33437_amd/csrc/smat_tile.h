@@ -96,6 +96,26 @@ __device__ __forceinline__ ListBlock list_block(const uint2* entries, uint32_t c
   return {e.x, e.y * tps + b % tpc};
 }
 
+// What a block of a device-driven list launch reads about its tensor and its step.  All of it is fetched in
+// one round of scalar loads (the empty asm needs every field at once): left to itself the compiler reads
+// the fields where branches first use them, in five rounds one after the other, before the wave's first
+// vector load.
+struct DeviceRecs {
+  TensorRec R;
+  ParamRec P;
+  ScaleRec C;
+  StepState S;
+};
+__device__ __forceinline__ DeviceRecs device_recs(const TensorRec* recs, const ParamRec* prms, const ScaleRec* scales,
+                                                  const StepState* state, uint32_t tensor, float lambda) {
+  DeviceRecs D{rec_at(recs, tensor), rec_at(prms, tensor), rec_at(scales, tensor), *state};
+  asm volatile("" ::"s"(D.R.theta), "s"(D.R.theta0), "s"(D.R.out), "s"(D.R.grad_sim), "s"(D.R.grad_theta),
+               "s"(D.R.n), "s"(D.R.elem_offset), "s"(D.R.tensor_id), "s"(D.R.sflags), "s"(D.P.thr), "s"(D.P.sigma),
+               "s"(D.P.flags), "s"(D.C.s), "s"(D.C.keep), "s"(D.C.divide), "s"(D.S.seed), "s"(D.S.step),
+               "s"(D.S.scale), "s"(lambda));
+  return D;
+}
+
 // Tile ti of a list's tensor.  len is 0 when the tile lies past the end of the tensor.  It comes from
 // 32-bit scalar arithmetic: a plan holds fewer than 2^31 one-quad tiles in all, so a tile's index
 // within its tensor and the tensor's count of whole tiles stay below 2^31.
@@ -115,6 +135,26 @@ __device__ __forceinline__ Tile list_tile(const TensorRec& R, uint32_t ti, int64
               R.sflags,
               ti == 0u ? R.sflags >> kHeadShift : 0u};
 }
+
+// Where a tile takes its Philox keys and its tensor's coefficient t from.  A launch whose step the host
+// knows has both in its arguments; a device-driven one forms them per wave, LATE: once the tile has issued
+// its loads.
+struct HostStep {
+  static constexpr bool LATE = false;
+  const PhiloxKeys& K;
+  uint32_t step;
+  __device__ __forceinline__ const PhiloxKeys& keys() const { return K; }
+  __device__ __forceinline__ float coefficient(const ParamRec& P) const { return P.t; }
+};
+struct DeviceStep {
+  static constexpr bool LATE = true;
+  uint64_t seed;
+  uint32_t step;
+  float scale;
+  ScaleRec C;
+  __device__ __forceinline__ PhiloxKeys keys() const { return philox_keys(seed); }
+  __device__ __forceinline__ float coefficient(const ParamRec&) const { return device_coefficient(scale, C); }
+};
 
 // The whole quads [first, end) of a tile, which move as vectors, and edge(q) for the partial ones: the
 // first quad of a tensor with a head, and the quad that holds a tensor's last 1-3 elements, each given
