@@ -101,6 +101,28 @@ def test_static_list_matches_the_plan_on_two_calls_the_second_smaller():
         assert not bool(torch.isnan(o.float()).any())
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("offset", [0, 6])
+def test_static_list_of_many_small_tensors_matches_the_plan(offset):
+    """Their remainders run in segments (they spare well over 16,384 one-quad blocks, a third of all)."""
+    sizes = [1, 5, 255, 256, 257, 2047, 2048, 2049, 4097, 6000, 14336, 14337, 16383, 16384, 16385, 18432] * 60
+    spans = [n + offset % 4 for n in sizes]
+    spared = sum(64 - 8 * -(-(s % 16384) // 2048) for s in spans if s % 16384)
+    assert spared > 16384 and 3 * spared > sum(64 * -(-s // 16384) for s in spans)
+    gen, rng = torch.Generator(DEV).manual_seed(13), np.random.default_rng(13)
+    th, t0, out_s, out_p = _ragged(gen, sizes, torch.bfloat16, misalign=(2, 7))
+    ids, offs, params = list(range(len(sizes))), [offset] * len(sizes), _params(rng, len(sizes))
+    _static(th, t0, out_s, ids, offs, params, seed=0x5EED, step=7)
+    _planned(th, t0, out_p, ids, offs, params, seed=0x5EED, step=7)
+    torch.cuda.synchronize()
+    _same_bits(out_s, out_p)
+    for i in list(range(0, 32)) + list(range(len(sizes) - 16, len(sizes))):     # and both the single-tensor call
+        one = torch.full_like(out_s[i], float("nan"))
+        smat.smat_simulate(th[i], t0[i], one, _lib.smat_op_params(*params[i].item()), 0x5EED, 7, ids[i], offset)
+        torch.cuda.synchronize()
+        _same_bits([out_s[i]], [one])
+
+
 def test_static_list_rejects_lists_beyond_its_tables():
     """Host-side checks: they fail before any HIP call (the descriptors below point nowhere)."""
     lib = smat.lib()
