@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "smat_table.h"
+
 namespace smat {
 
 // ---------------------------------------------------------------- records
@@ -162,24 +164,9 @@ __host__ __device__ inline AdamConsts adam_consts(const AdamHyper& h, float lr, 
 // Static flag: theta, the moments, grad_sim (and grad_theta when accumulating) aligned to their elements.
 enum : uint32_t { kVecAdam = 4u, kVecAdamAcc = 8u };
 
-// Work decomposition: a block of kBlock threads (one wave) handles one tile of Q quads per
-// thread (tile = 4 * kBlock * Q elements); thread x owns quads x, x + kBlock, ... of the tile,
-// so every load/store instruction of the wave covers one contiguous span and consecutive blocks
-// stream consecutive memory.  A list is cut into chunks of kChunk elements
-// through a table that keeps its entries few; where many small tensors would leave most blocks of
-// their chunks without a tile, the remainders go in segments of kSegment elements instead (ChunkTable).  The simulate, the backward and the fused optimizer step take one
-// quad per thread: each wave then keeps one 64-lane piece of every array in flight, the access shape
-// that streams fastest on MI355X.
-constexpr int kBlock = 64;
 constexpr int kSimQuads = 1;
-constexpr int kBwdQuads = 1;  // 2 where a bf16 gradient is written, not accumulated (bwd_quads)
+constexpr int kBwdQuads = 1;  // 2 where a bf16 gradient is written, not accumulated (backward_form)
 constexpr int kAdamQuads = 1;
-constexpr int64_t kChunk = 16384;
-constexpr int64_t kSegment = 2048;
-constexpr uint32_t kChunkSegments = (uint32_t)(kChunk / kSegment);
-constexpr int64_t tile_elems(int quads) { return 4 * kBlock * quads; }
-constexpr uint32_t tiles_per_segment(int quads) { return (uint32_t)(kSegment / tile_elems(quads)); }
-constexpr uint32_t tiles_per_chunk(int quads) { return kChunkSegments * tiles_per_segment(quads); }
 static_assert(kSegment % tile_elems(kSimQuads) == 0 && kSegment % tile_elems(kBwdQuads) == 0 &&
                   kSegment % tile_elems(kAdamQuads) == 0,
               "tiles split segments");
@@ -190,10 +177,6 @@ struct ChunkTable {
   const uint2* entries;
   uint32_t chunks, segments;
 };
-// How a list launch finds its tiles: chunks in linear block order or in runs per XCD (block_order), or a
-// table that also has segments.
-enum TableOrder : int { kLinear = 0, kRuns = 1, kMixed = 2 };
-constexpr uint32_t kMixedRuns = 1u << 31;  // on the chunk count of a kMixed launch: its chunks in runs
 
 constexpr uint32_t kStreamMask = 0u;
 constexpr uint32_t kStreamNoise = 1u;

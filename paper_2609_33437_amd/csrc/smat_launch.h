@@ -11,13 +11,6 @@
 
 namespace smat {
 
-// ---------------------------------------------------------------- launch size
-// A dispatch packet holds the grid's total work-items (blocks x threads per block) in 32 bits, and a
-// grid past that wraps without an error.  The launchers split larger jobs into several launches of
-// at most this many blocks each (for one-wave blocks 2^26 - 1, i.e. 17.2e9 elements at one quad per
-// thread).
-constexpr uint32_t max_grid_blocks(int threads) { return 0xFFFFFFFFu / (uint32_t)threads; }
-
 // ---------------------------------------------------------------- resident blocks
 // HBM streams fastest when the loads in flight on a compute unit hold about 50 KB: with less the
 // memory system idles between requests, with more the waves of many tiles compete for open DRAM rows.
@@ -71,29 +64,21 @@ void with_flag(bool flag, F&& fn) {
 }
 
 // fn(entries, chunks, grid, order, first segment) for the launches of a list's table with tiles of Q
-// quads, in pieces that each fit one launch, stopping at the first launch error.
+// quads (table_pieces), stopping at the first launch error.
 template <int Q, typename F>
 hipError_t for_table(const ChunkTable& t, bool runs, F&& fn) {
-  constexpr uint32_t tps = tiles_per_segment(Q), tpc = tiles_per_chunk(Q);
-  using Mixed = std::integral_constant<int, kMixed>;
-  const uint32_t mark = runs ? kMixedRuns : 0u;
-  const uint64_t blocks = (uint64_t)t.chunks * tpc + (uint64_t)t.segments * tps;
-  if (t.segments > 0 && blocks <= max_grid_blocks(kBlock)) {
-    fn(t.entries, t.chunks | mark, dim3((uint32_t)blocks), Mixed(), 0);
-    return hipGetLastError();
-  }
-  const hipError_t e = for_pieces(t.chunks, max_grid_blocks(kBlock) / tpc, [&](uint64_t first, uint64_t count) {
-    const dim3 grid((uint32_t)count * tpc);
-    if (runs)
-      fn(t.entries + first, 0u, grid, std::integral_constant<int, kRuns>(), first * kChunkSegments);
+  hipError_t e = hipSuccess;
+  table_pieces(t.chunks, t.segments, Q, runs, max_grid_blocks(kBlock), [&](const TablePiece& p) {
+    const uint2* entries = t.entries + p.entry;
+    if (p.order == kMixed)
+      fn(entries, p.chunks, dim3(p.blocks), std::integral_constant<int, kMixed>(), p.segment);
+    else if (p.order == kRuns)
+      fn(entries, p.chunks, dim3(p.blocks), std::integral_constant<int, kRuns>(), p.segment);
     else
-      fn(t.entries + first, 0u, grid, std::integral_constant<int, kLinear>(), first * kChunkSegments);
+      fn(entries, p.chunks, dim3(p.blocks), std::integral_constant<int, kLinear>(), p.segment);
+    return (e = hipGetLastError()) == hipSuccess;
   });
-  if (e != hipSuccess) return e;
-  return for_pieces(t.segments, max_grid_blocks(kBlock) / tps, [&](uint64_t first, uint64_t count) {
-    fn(t.entries + t.chunks + first, 0u, dim3((uint32_t)count * tps), Mixed(),
-       (uint64_t)t.chunks * kChunkSegments + first);
-  });
+  return e != hipSuccess ? e : hipGetLastError();
 }
 // Segments, and elements up to the padding of tensors' ends, that a table covers.
 inline uint64_t table_segments(const ChunkTable& t) { return (uint64_t)t.chunks * kChunkSegments + t.segments; }

@@ -56,21 +56,6 @@ __device__ __forceinline__ const R& rec_at(const R* base, uint32_t i) {
   return *reinterpret_cast<const R*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(R));
 }
 
-// Block order.  Consecutive blocks go to the eight XCDs in turn, each with an L2 of its own.  With tiles
-// that begin on a 128-byte line that is the best order: the chip streams one contiguous window of every
-// array.  Where tiles begin inside a line (tensors packed end to end), neighbouring tiles share a line at
-// their border, which two XCDs then fetch, and write in part, each for itself.  RUNS gives an XCD whole
-// runs of tpc tiles (16,384 elements) of eight runs at a time, so that borders meet in one L2.  Step of
-// six 67M-element tensors in one buffer, linear order -> runs: 1.37 -> 1.16 ms when the tensors begin 2
-// to 32 bytes off a line, 1.30 -> 1.13 ms 64 off, but 1.088 -> 1.115 on it (the 1.5B list: 3-7 % slower);
-// optimizer step 2.65 -> 2.35, 3-expert merge 0.74 -> 0.67.
-template <bool RUNS>
-__device__ __forceinline__ uint32_t block_order(uint32_t b, uint32_t blocks, uint32_t tpc) {
-  const uint32_t group = 8u * tpc;
-  if (!RUNS || b >= blocks / group * group) return b;
-  return b / group * group + (b % 8u) * tpc + b / 8u % tpc;
-}
-
 // The tensor and tile of a block of a list launch; `chunks` is read by kMixed only.  The table (8 B per
 // entry) and the tensor records (64 B per tensor) are small enough to stay in L2 while the kernel
 // streams the tensors.
@@ -79,21 +64,9 @@ struct ListBlock {
 };
 template <int Q, int ORDER>
 __device__ __forceinline__ ListBlock list_block(const uint2* entries, uint32_t chunks) {
-  constexpr uint32_t tps = tiles_per_segment(Q), tpc = tiles_per_chunk(Q);
-  uint32_t b = blockIdx.x;
-  if (ORDER == kMixed) {
-    const uint32_t count = chunks & ~kMixedRuns, blocks = count * tpc;
-    if (b >= blocks) {
-      b -= blocks;
-      const uint2 e = entries[count + b / tps];
-      return {e.x, e.y * tps + b % tps};
-    }
-    if (chunks & kMixedRuns) b = block_order<true>(b, blocks, tpc);
-  } else {
-    b = block_order<ORDER == kRuns>(b, gridDim.x, tpc);
-  }
-  const uint2 e = entries[b / tpc];
-  return {e.x, e.y * tps + b % tpc};
+  const EntryTile t = entry_tile<Q, ORDER>(blockIdx.x, gridDim.x, chunks);
+  const uint2 e = entries[t.entry];
+  return {e.x, e.y * tiles_per_segment(Q) + t.tile};
 }
 
 // What a block of a device-driven list launch reads about its tensor and its step.  All of it is fetched in
