@@ -31,9 +31,10 @@ PEAK_HBM_GBPS = 8000.0  # MI355X HBM3E
 # per 64 calls, i.e. 1024 x 2.4e9 x 64 / 174 calls/s.
 PEAK_PHILOX_CALLS = 1024 * 2.4e9 * 64 / 174
 KERNEL_SOURCES = ("paper_2609_33437_amd/csrc/smat_kernels.hip", "paper_2609_33437_amd/csrc/smat_device.h",
-                  "paper_2609_33437_amd/csrc/smat_tile.h")
+                  "paper_2609_33437_amd/csrc/smat_tile.h", "paper_2609_33437_amd/csrc/smat_table.h")
 MERGE_SOURCES = ("paper_2609_33437_amd/csrc/smat_merge.hip", "paper_2609_33437_amd/csrc/smat_device.h",
-                 "paper_2609_33437_amd/csrc/smat_tile.h", "paper_2609_33437_amd/csrc/smat_launch.h")
+                 "paper_2609_33437_amd/csrc/smat_tile.h", "paper_2609_33437_amd/csrc/smat_table.h",
+                 "paper_2609_33437_amd/csrc/smat_launch.h")
 
 
 def log(msg: str) -> None:
@@ -98,6 +99,19 @@ def parse_args():
                     help="also run a plain elementwise copy of 2^28 fp32 values (1 GiB read, 1 GiB written) "
                          "three times, whose HBM counters scale the kernels' counter readings")
     return ap.parse_args()
+
+
+def skipped_bytes(numels, params, grad_bytes: int):
+    """Bytes that the simulate and the accumulating backward are expected to leave unmoved on tensors that
+    begin on a 64-byte sector and keep less than 1 element in 8: the sectors (16 fp32 elements) without a
+    kept element of theta, and of grad_theta (read and written) with g~'s sectors there."""
+    sim = bwd = 0.0
+    for n, p in zip(numels, params):
+        if 0.0 < p["keep"] < 0.125:
+            empty = lambda elems: n * (1.0 - p["keep"]) ** elems  # noqa: E731  elements in empty sectors
+            sim += 4 * empty(16)
+            bwd += 8 * empty(16) + grad_bytes * empty(64 // grad_bytes)
+    return round(sim), round(bwd)
 
 
 # Worker threads of the CPU baseline: one per host core the process may run on, at most 16, the host
@@ -1178,9 +1192,12 @@ def main() -> int:
     P = cfg.numel
     sim_bytes = P * (4 + nbytes[cfg.theta0_dtype] + nbytes[cfg.out_dtype])
     bwd_bytes = P * (nbytes[cfg.grad_dtype] + 4 + 4)
-    step_gbps = (sim_bytes + bwd_bytes) / (ms_step * 1e6)
-    sim_gbps = sim_bytes / (sim_avg * 1e6)
-    bwd_gbps = bwd_bytes / (bwd_avg * 1e6)
+    # rates are of the bytes that move: the algorithmic ones less the empty sectors of sparse masks
+    sim_skip, bwd_skip = skipped_bytes([s.numel for s in cfg.specs], params[W], nbytes[cfg.grad_dtype])
+    sim_moved, bwd_moved = sim_bytes - sim_skip, bwd_bytes - bwd_skip
+    step_gbps = (sim_moved + bwd_moved) / (ms_step * 1e6)
+    sim_gbps = sim_moved / (sim_avg * 1e6)
+    bwd_gbps = bwd_moved / (bwd_avg * 1e6)
 
     if args.calibrate_copy:
         src = torch.ones(1 << 28, dtype=torch.float32, device="cuda")
@@ -1234,6 +1251,9 @@ def main() -> int:
         "cpu_baseline": None,
         "parity": None,
     }
+    if sim_skip + bwd_skip:
+        result["config"]["moved_bytes_per_param_per_step"] = round((sim_moved + bwd_moved) / P, 3)
+        roofline["moved_bytes_per_launch"] = sim_moved if dominant == "simulate" else bwd_moved
     if cfg.period > 1:
         result["config"]["ms_per_training_step_avg"] = round(ms_step / cfg.period, 4)
     if prefetch is not None:

@@ -4,6 +4,7 @@ changed dropped gradient, a kept gradient off by 1e-5 relative) are each counted
 import argparse
 
 import numpy as np
+import pytest
 import torch
 
 import bench
@@ -60,3 +61,23 @@ def test_default_steps_scale_with_the_list():
     assert k2 * workloads.config("c2").numel >= 20 * workloads.config("c4").numel and w2 == k2 // 4
     assert bench.default_steps(a, workloads.config("c1"))[0] == 2000
     assert bench.default_steps(argparse.Namespace(steps=7, warmup=2), workloads.config("c2")) == (7, 2)
+
+
+def test_rates_leave_out_the_sectors_of_sparse_masks_that_do_not_move():
+    sizes = [16 * 1000, 16 * 1000, 160, 160]
+    keeps = [0.1, 0.125, 1.0, 0.0]                      # only the first one skips sectors
+    params = [dict(keep=k) for k in keeps]
+    sim, bwd = bench.skipped_bytes(sizes, params, 2)
+    assert sim == round(4 * 16000 * 0.9 ** 16)
+    assert bwd == round(8 * 16000 * 0.9 ** 16 + 2 * 16000 * 0.9 ** 32)
+    assert bench.skipped_bytes(sizes, params, 4) == (sim, round(12 * 16000 * 0.9 ** 16))
+    # against masks as they are drawn: 2^20 elements at keep 0.1, whose share of empty sectors is 0.185
+    kept = oracle.keep_mask(7, 3, 1, 0, 1 << 20, 0.1).reshape(-1, 16)
+    share = 1.0 - kept.any(axis=1).mean()
+    assert abs(4 * 2 ** 20 * share - bench.skipped_bytes([1 << 20], params, 2)[0]) < 0.03 * 4 * 2 ** 20 * share
+    # of the benchmark's lists only the sparse one skips much, one of them 0.4 % on its sparsest tensor
+    for name in workloads.ALL:
+        cfg = workloads.config(name)
+        step = workloads.step_params(cfg, workloads.static_settings(cfg, [1e-3] * cfg.count), 3)
+        skipped = sum(bench.skipped_bytes([s.numel for s in cfg.specs], step, 2))
+        assert {"c2": 0.004, "c3": 0.108}.get(name, 0.0) == pytest.approx(skipped / (18 * cfg.numel), abs=5e-4)
