@@ -956,14 +956,19 @@ extern "C" smat_status smat_plan_bind_adam_state(smat_plan* p, const smat_adam_s
   if (smat_status st = check_plan_spans(p, recs, &adam, "smat_plan_bind_adam_state"); st != SMAT_OK) return st;
   const size_t rec_bytes = sizeof(TensorRec) * p->count, adam_bytes = sizeof(AdamRec) * p->count;
   Staging& stage = p->recs_staging;
-  SMAT_HIP(stage.init(rec_bytes + adam_bytes));
-  SMAT_HIP(stage.take(stream));
-  device_recs(p, recs, &adam, stage.data());
-  AdamRec* staged = reinterpret_cast<AdamRec*>(stage.data() + rec_bytes);
-  for (int32_t i = 0; i < p->count; ++i) staged[i] = smat::device_adam(adam[i], recs[i]);
+  SMAT_HIP(stage.init(rec_bytes));
   if (p->count > 0) {
-    SMAT_HIP(smat::launch_upload(stage.data(), p->ws + p->off_recs, rec_bytes, {}, stream));
-    SMAT_HIP(smat::launch_upload(stage.data() + rec_bytes, p->ws + p->off_adam, adam_bytes, stage.signal(), stream));
+    // a slot and a signal for each of the two uploads: if the second cannot be launched, the first one's
+    // slot still is not written before its kernel has read it
+    static_assert(sizeof(AdamRec) <= sizeof(TensorRec), "a slot holds either table");
+    SMAT_HIP(stage.take(stream));
+    device_recs(p, recs, &adam, stage.data());
+    SMAT_HIP(smat::launch_upload(stage.data(), p->ws + p->off_recs, rec_bytes, stage.signal(), stream));
+    stage.sent(smat::upload_blocks(rec_bytes / 8), stream);
+    SMAT_HIP(stage.take(stream));
+    AdamRec* staged = reinterpret_cast<AdamRec*>(stage.data());
+    for (int32_t i = 0; i < p->count; ++i) staged[i] = smat::device_adam(adam[i], recs[i]);
+    SMAT_HIP(smat::launch_upload(staged, p->ws + p->off_adam, adam_bytes, stage.signal(), stream));
     stage.sent(smat::upload_blocks(adam_bytes / 8), stream);
   }
   p->recs = recs;
@@ -1006,12 +1011,12 @@ extern "C" smat_status smat_plan_set_grads(smat_plan* p, const void* const* grad
   if (smat_status st = check_plan_spans(p, recs, p->adam_bound ? &p->adam : nullptr, "smat_plan_set_grads");
       st != SMAT_OK)
     return st;
-  const size_t rec_bytes = sizeof(TensorRec) * p->count, adam_bytes = sizeof(AdamRec) * p->count;
+  const size_t rec_bytes = sizeof(TensorRec) * p->count;
   Staging& stage = p->recs_staging;
-  SMAT_HIP(stage.init(rec_bytes + adam_bytes));
-  SMAT_HIP(stage.take(stream));
-  device_recs(p, recs, p->adam_bound ? &p->adam : nullptr, stage.data());
+  SMAT_HIP(stage.init(rec_bytes));
   if (p->count > 0) {
+    SMAT_HIP(stage.take(stream));
+    device_recs(p, recs, p->adam_bound ? &p->adam : nullptr, stage.data());
     SMAT_HIP(smat::launch_upload(stage.data(), p->ws + p->off_recs, rec_bytes, stage.signal(), stream));
     stage.sent(smat::upload_blocks(rec_bytes / 8), stream);
   }

@@ -22,7 +22,6 @@ __device__ __forceinline__ uint64_t load_host(const uint64_t* p) {
 // The block has read its part of the staging: every wave's stores, which carry the loaded values, are
 // issued before the barrier, so the staging is free once the word is written.
 __device__ __forceinline__ void signal_read(UploadSignal sig) {
-  if (!sig.done) return;
   __syncthreads();
   if (threadIdx.x == 0)
     __hip_atomic_store(sig.done + blockIdx.x, sig.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -24,7 +24,7 @@
 namespace smat {
 
 // What an upload kernel writes once it has read its staging: block b stores seq to done[b] (pinned host
-// memory; null: nothing).
+// memory).
 struct UploadSignal {
   uint32_t* done;
   uint32_t seq;
