@@ -115,7 +115,7 @@ def skipped_bytes(numels, params, grad_bytes: int):
 
 
 # Worker threads of the CPU baseline: one per host core the process may run on, at most 16, the host
-# share that goes with one GPU on the MI355X boxes this runs on.
+# share that goes with one GPU on an eight-GPU MI355X host.
 CPU_WORKER_CAP = 16
 
 

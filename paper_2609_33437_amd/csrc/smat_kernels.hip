@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_multi(const TensorRec* __re
 // tensor's coefficient from that scale and the tensor's ScaleRec exactly as the host forms it, and the
 // round keys from the seed: the backward, which has little else to do, once its loads are issued, the
 // simulate, whose time after them goes to the draws, before (a captured step of 125M parameters 343.2 ->
-// 338.1 us together with device_recs, on another box 345.3 -> 343.6; a simulate that forms them late is
+// 338.1 us together with device_recs, on another card 345.3 -> 343.6; a simulate that forms them late is
 // 1.5-2 % slower).
 template <typename T0, typename TO, int ORDER>
 __global__ __launch_bounds__(kBlock) void k_simulate_multi_dev(const TensorRec* __restrict__ recs,

@@ -391,7 +391,7 @@ static inline uint32_t blocks_for(int64_t n, int64_t per_block) { return (uint32
 // A wave of the fused optimizer step loads theta, both moments, g~ and, when accumulating, grad_theta:
 // 3.5 KB (bf16 g~) to 5 KB (fp32 g~, accumulating).  Uncapped, 32 such waves keep 112-160 KB in flight
 // per CU, twice what streams best, and the rate then depends on where the arrays happen to lie: on
-// 1.54e9 parameters (40.1 GB) 6.24-6.69 ms over two boxes uncapped, 6.07-6.20 ms with the 14 blocks this
+// 1.54e9 parameters (40.1 GB) 6.24-6.69 ms on two cards uncapped, 6.07-6.20 ms with the 14 blocks this
 // gives; on 124M parameters accumulating (3.7 GB) 0.585 against 0.55 ms with 11.  16 or 12 blocks are
 // within 1.5 % of 14, 9 lose 5 %.
 static inline uint32_t adamw_lds(int grad_dtype, bool accumulate, uint64_t elems) {
