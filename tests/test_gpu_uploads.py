@@ -4,6 +4,8 @@ single-tensor calls, which take their parameters as arguments.  Counts sit aroun
 tables over 1 MB) while the first upload is still queued behind a long run of copies, so that the host has
 to wait for a slot before it writes the next table."""
 import contextlib
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -192,4 +194,63 @@ def test_merge_terms_over_a_megabyte():
                                 tensor_ids=list(range(count))[part]) as plan:
                 plan.merge(terms[k][part])
         torch.cuda.synchronize()
+        assert torch.equal(bits(got[k]), bits(whole(out))), k
+
+
+@pytest.mark.parametrize("capturing", [False, True])
+def test_a_wait_of_seconds(capturing):
+    """The ninth upload waits more than two seconds, after which the library asks the runtime whether the
+    device still runs: the answer is no error, the uploads are whole, and a graph that another thread is
+    capturing meanwhile (in the mode that forbids waits and queries to all threads) is not disturbed."""
+    count = 40
+    th, t0 = arrays(count, 0.02, 1), arrays(count, 0.02, 2, torch.bfloat16)
+    out = arrays(count, 1.0, 3, torch.bfloat16)
+    params = [records(count, k) for k in range(10)]
+    got = torch.empty(10, count, 8, dtype=torch.bfloat16, device=DEV)
+    busy, x, graph, errors = Busy(), torch.ones(4, device=DEV), torch.cuda.CUDAGraph(), []
+    began, ended = threading.Event(), threading.Event()
+
+    def capture():
+        try:
+            with torch.cuda.graph(graph, capture_error_mode="global"):
+                x.add_(1.0)
+                began.set()
+                ended.wait(60)
+                x.mul_(3.0)
+        except Exception as e:  # noqa: BLE001  reported by the test
+            errors.append(e)
+        finally:
+            began.set()
+
+    with smat.Plan(th, out, t0) as plan:
+        torch.cuda.synchronize()
+        if capturing:
+            thread = threading.Thread(target=capture)
+            thread.start()
+            began.wait(60)
+        stream = torch.cuda.Stream()
+        start, end = time.perf_counter(), None
+        with torch.cuda.stream(stream):
+            busy.queue(45)                          # about 2.7 s
+            for k in range(10):
+                plan.set_params(params[k])
+                if k == 8:
+                    end = time.perf_counter()
+                plan.simulate(SEED, k)
+                got[k].copy_(whole(out))
+        ended.set()
+        if capturing:
+            thread.join()
+        torch.cuda.synchronize()
+    assert not errors and end - start > 2.0
+    if capturing:
+        for want in (6.0, 21.0):                    # (1 + 1) * 3, (6 + 1) * 3
+            graph.replay()
+            torch.cuda.synchronize()
+            assert x.tolist() == [want] * 4
+    for k in range(10):
+        with smat.Plan(th, out, t0) as plan:
+            plan.set_params(params[k])
+            plan.simulate(SEED, k)
+            torch.cuda.synchronize()
         assert torch.equal(bits(got[k]), bits(whole(out))), k
